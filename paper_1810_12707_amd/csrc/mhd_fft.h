@@ -17,11 +17,13 @@
 // accumulated in FP32 by v_mfma_f32_16x16x32_bf16 (the lo*lo term, about 2^-16
 // relative, is dropped).  Twiddles stay FP32 on the VALU.
 //
-// Twiddles come from a table of exp(-2 pi i j / N), j < N, computed in FP64
-// on the host and rounded once to T; the inverse uses the conjugates.
+// Twiddles come from a table made for the plan on the host in FP64 and rounded
+// once to T (make_twiddles); the inverse uses the conjugates.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <cmath>
 
 #include "mhd_internal.h"
 
@@ -50,6 +52,20 @@ template <typename X> __device__ __forceinline__ X ctimes_i(X a) { X r; r.x = -a
 template <typename X> __device__ __forceinline__ X ctimes_mi(X a) { X r; r.x = a.y; r.y = -a.x; return r; }
 // multiply by i^s: sign s = -1 gives -i (forward), +1 gives +i (inverse)
 template <int S, typename X> __device__ __forceinline__ X ctimes_si(X a) { return S < 0 ? ctimes_mi(a) : ctimes_i(a); }
+
+// s a + b for a real s
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <typename X, typename T> __device__ __forceinline__ X cfma(T s, X a, X b) {
+  X r; r.x = fma_(s, a.x, b.x); r.y = fma_(s, a.y, b.y); return r;
+}
+// (1 + S i) a, i.e. sqrt(2) exp(S i pi / 4) a
+template <int S, typename X> __device__ __forceinline__ X cdiag(X a) { return cadd(a, ctimes_si<S>(a)); }
+// (1 -+ i t) a: upper sign for the inverse
+template <int S, typename X, typename T> __device__ __forceinline__ X ctan(X a, T t) {
+  const T u = S < 0 ? t : -t;
+  X r; r.x = fma_(-u, a.y, a.x); r.y = fma_(u, a.x, a.y); return r;
+}
 
 // cos(2 pi m / 16), m = 0..15 (sin(2 pi m/16) = cos(2 pi (m - 4)/16))
 __device__ constexpr double kCos16[16] = {
@@ -93,21 +109,17 @@ template <int S, typename X> __device__ __forceinline__ void dft4(X* v) {
 template <int S, typename X> __device__ __forceinline__ void dft8_combine(X* v, X (&e)[4], X (&o)[4]) {
   using T = decltype(v[0].x);
   const T h = T(0.70710678118654752440084436210485);
-  // o[q] *= exp(S * i * pi * q / 4)
-  X o1 = o[1], o3 = o[3];
-  if (S < 0) {
-    o[1].x = (o1.x + o1.y) * h; o[1].y = (o1.y - o1.x) * h;
-    o[3].x = (o3.y - o3.x) * h; o[3].y = -(o3.x + o3.y) * h;
-  } else {
-    o[1].x = (o1.x - o1.y) * h; o[1].y = (o1.x + o1.y) * h;
-    o[3].x = -(o3.x + o3.y) * h; o[3].y = (o3.x - o3.y) * h;
-  }
-  o[2] = ctimes_si<S>(o[2]);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    v[q] = cadd(e[q], o[q]);
-    v[q + 4] = csub(e[q], o[q]);
-  }
+  // o[q] *= exp(S * i * pi * q / 4), the 1/sqrt(2) of q = 1, 3 folded into the
+  // last additions
+  const X p1 = cdiag<S>(o[1]), p3 = ctimes_si<S>(cdiag<S>(o[3])), o2 = ctimes_si<S>(o[2]);
+  v[0] = cadd(e[0], o[0]);
+  v[4] = csub(e[0], o[0]);
+  v[1] = cfma(h, p1, e[1]);
+  v[5] = cfma(-h, p1, e[1]);
+  v[2] = cadd(e[2], o2);
+  v[6] = csub(e[2], o2);
+  v[3] = cfma(h, p3, e[3]);
+  v[7] = cfma(-h, p3, e[3]);
 }
 
 template <int S, typename X> __device__ __forceinline__ void dft8(X* v) {
@@ -175,6 +187,65 @@ template <int R, int S, typename X> __device__ __forceinline__ void dft(X* v) {
 template <int R, int S, unsigned ZM, typename X> __device__ __forceinline__ void dft_z(X* v) {
   if constexpr (R == 8 && ZM == ((1u << 3) | (1u << 4))) dft8_z34<S>(v);
   else dft<R, S>(v);
+}
+
+// ---------------------------------------------------------------- twiddled butterflies
+// A Stockham pass multiplies sample r of its butterfly by w_r = exp(-+ i theta_r)
+// before the R-point DFT.  For R = 4 and 8 the multiplication is folded into
+// the butterfly's additions: with w_r = c_r (1 - i t_r), c = cos, t = tan, only
+// x_r = (1 - i t_r) v_r is formed (two FMAs instead of the four operations of
+// a complex product); the factors c_r stay pending and enter the additions
+// that follow as FMA coefficients -- c_b / c_a where two pending values meet,
+// the first one's c where a pending value meets a plain one.  69 instead of 84
+// operations for R = 8, 24 instead of 28 for R = 4.  The middle sample
+// (r = R/2, whose angle passes pi/2, where the tangent has a pole) is
+// multiplied out; for a power of two NS no other cosine vanishes.  A large
+// tangent does not cost accuracy: the rounding of (1 - i t) v is relative to
+// |t v|, and the pending cosine scales it back to |v|.
+// Other radices, and passes whose NS is no power of two, take plain products.
+template <int R, int NS> constexpr bool tan_form() { return (R == 4 || R == 8) && NS > 1 && (NS & (NS - 1)) == 0; }
+
+// R-point DFT of the twiddled samples; t[0 .. R - 2] as make_twiddles stores them.
+template <int R, int NS, int S, typename X> __device__ __forceinline__ void dft_tw(X* v, const X* t) {
+  if constexpr (tan_form<R, NS>() && R == 4) {
+    // t: (tan 1, tan 3), w_2, (c3 / c1, c1)
+    const X x1 = ctan<S>(v[1], t[0].x), x3 = ctan<S>(v[3], t[0].y);
+    const X y2 = S < 0 ? cmul(v[2], t[1]) : cmulc(v[2], t[1]);
+    const X t0 = cadd(v[0], y2), t1 = csub(v[0], y2);
+    const X t2 = cfma(t[2].x, x3, x1), t3 = ctimes_si<S>(cfma(-t[2].x, x3, x1));
+    v[0] = cfma(t[2].y, t2, t0);
+    v[2] = cfma(-t[2].y, t2, t0);
+    v[1] = cfma(t[2].y, t3, t1);
+    v[3] = cfma(-t[2].y, t3, t1);
+  } else if constexpr (tan_form<R, NS>() && R == 8) {
+    // t: (tan 1, tan 2), (tan 3, tan 5), (tan 6, tan 7), w_4, (c6 / c2, c2),
+    //    (c5 / c1, c7 / c3), (c3 / c1, c1)
+    using T = decltype(v[0].x);
+    const T c2 = t[4].y, c31 = t[6].x, c1 = t[6].y, hc1 = T(0.70710678118654752440084436210485) * c1;
+    const X y4 = S < 0 ? cmul(v[4], t[3]) : cmulc(v[4], t[3]);
+    const X a0 = cadd(v[0], y4), a1 = csub(v[0], y4);
+    const X x2 = ctan<S>(v[2], t[0].y), x6 = ctan<S>(v[6], t[2].x);
+    const X b0 = cfma(t[4].x, x6, x2), b1 = ctimes_si<S>(cfma(-t[4].x, x6, x2));
+    const X e0 = cfma(c2, b0, a0), e2 = cfma(-c2, b0, a0), e1 = cfma(c2, b1, a1), e3 = cfma(-c2, b1, a1);
+    const X x1 = ctan<S>(v[1], t[0].x), x5 = ctan<S>(v[5], t[1].y);
+    const X d0 = cfma(t[5].x, x5, x1), d1 = cfma(-t[5].x, x5, x1);
+    const X x3 = ctan<S>(v[3], t[1].x), x7 = ctan<S>(v[7], t[2].y);
+    const X g0 = cfma(t[5].y, x7, x3), g1 = ctimes_si<S>(cfma(-t[5].y, x7, x3));
+    const X o0 = cfma(c31, g0, d0), o2 = ctimes_si<S>(cfma(-c31, g0, d0));
+    const X p1 = cdiag<S>(cfma(c31, g1, d1)), p3 = ctimes_si<S>(cdiag<S>(cfma(-c31, g1, d1)));
+    v[0] = cfma(c1, o0, e0);
+    v[4] = cfma(-c1, o0, e0);
+    v[1] = cfma(hc1, p1, e1);
+    v[5] = cfma(-hc1, p1, e1);
+    v[2] = cfma(c1, o2, e2);
+    v[6] = cfma(-c1, o2, e2);
+    v[3] = cfma(hc1, p3, e3);
+    v[7] = cfma(-hc1, p3, e3);
+  } else {
+#pragma unroll
+    for (int r = 1; r < R; ++r) v[r] = S < 0 ? cmul(v[r], t[r - 1]) : cmulc(v[r], t[r - 1]);
+    dft<R, S>(v);
+  }
 }
 
 // ---------------------------------------------------------------- radix plans
@@ -257,6 +328,50 @@ template <class PL> constexpr bool plan_ok() {
   int prod = 1;
   for (int i = 0; i < PL::np; ++i) prod *= PL::r[i];
   return prod == PL::N;
+}
+
+// Twiddle table of a plan: pass P >= 1 (radix R, NS = product of the radices
+// before it) has R - 1 rows of NS complex entries, row by row (lanes with
+// adjacent k read adjacent words), from entry NS_P - r_0 on; together N - r_0
+// entries.
+template <class PL> constexpr int tw_entries() { return PL::N - PL::r[0]; }
+template <class PL> constexpr int tw_offset(int p) { return plan_ns<PL>(p) - PL::r[0]; }
+
+// Fills the table (host): for every pass and k < NS the rows dft_tw expects of
+// theta_r = 2 pi k r / (NS R), in FP64, rounded once to T.
+template <typename T, class PL, int P = 1> inline void make_twiddles(T* out) {
+  if constexpr (P < PL::np) {
+    constexpr int R = PL::r[P], NS = plan_ns<PL>(P);
+    T* const o = out + 2 * tw_offset<PL>(P);
+    for (int k = 0; k < NS; ++k) {
+      double re[R], im[R];
+      for (int r = 0; r < R; ++r) {
+        const double a = 6.28318530717958647692528676655900577 * ((double)k * r) / ((double)NS * R);
+        re[r] = std::cos(a);
+        im[r] = -std::sin(a);
+      }
+      auto put = [&](int row, double x, double y) {
+        o[2 * (row * NS + k)] = T(x);
+        o[2 * (row * NS + k) + 1] = T(y);
+      };
+      if constexpr (tan_form<R, NS>() && R == 4) {
+        put(0, im[1] / re[1], im[3] / re[3]);
+        put(1, re[2], im[2]);
+        put(2, re[3] / re[1], re[1]);
+      } else if constexpr (tan_form<R, NS>() && R == 8) {
+        put(0, im[1] / re[1], im[2] / re[2]);
+        put(1, im[3] / re[3], im[5] / re[5]);
+        put(2, im[6] / re[6], im[7] / re[7]);
+        put(3, re[4], im[4]);
+        put(4, re[6] / re[2], re[2]);
+        put(5, re[5] / re[1], re[7] / re[3]);
+        put(6, re[3] / re[1], re[1]);
+      } else {
+        for (int r = 1; r < R; ++r) put(r - 1, re[r], im[r]);
+      }
+    }
+    make_twiddles<T, PL, P + 1>(out);
+  }
 }
 
 // Lane -> (sequence b, butterfly j) assignment of a pass with NBF butterflies
@@ -428,12 +543,14 @@ template <int MAP, int NB, int NBF, int NT, int NS> constexpr bool slot_invarian
   return false;
 }
 
-// Twiddles t[r] = tw[k r N/(NS R)], r = 1..R-1, of butterfly j (k = j mod NS).
-template <typename T, int N, int R, int NS>
-__device__ __forceinline__ void load_pass_twiddles(cx<T> (&t)[R], const cx<T>* tw, int j) {
+// Rows t[0 .. R - 2] of the plan's twiddle table for butterfly j (k = j mod NS)
+// of pass P.
+template <typename T, class PL, int P>
+__device__ __forceinline__ void load_pass_twiddles(cx<T>* t, const cx<T>* tw, int j) {
+  constexpr int R = PL::r[P], NS = plan_ns<PL>(P);
   const int k = j % NS;
 #pragma unroll
-  for (int r = 1; r < R; ++r) t[r] = tw[k * r * (N / (NS * R))];
+  for (int r = 0; r < R - 1; ++r) t[r] = tw[tw_offset<PL>(P) + r * NS + k];
 }
 
 // (sequence b, butterfly j) of slot i of thread tid: lane_map on
@@ -496,7 +613,7 @@ __device__ __forceinline__ void fft_pass_valu(cx<T>* buf, const cx<T>* tw, int t
   if constexpr (TWS) {
     int b0, j0;
     slot_map<NB, NBF, NT, MAP, linear_addr<PADSH>()>(tid, 0, b0, j0);
-    load_pass_twiddles<T, N, R, NS>(tws, tw, j0);
+    load_pass_twiddles<T, PL, P>(tws, tw, j0);
   }
   cx<T> v[CNT][R];
 #pragma unroll
@@ -516,17 +633,16 @@ __device__ __forceinline__ void fft_pass_valu(cx<T>* buf, const cx<T>* tw, int t
         }
       }
       if constexpr (NS > 1) {
-        cx<T> t[R];
         if constexpr (TWS) {
-#pragma unroll
-          for (int r = 1; r < R; ++r) t[r] = tws[r];
+          dft_tw<R, NS, S>(v[i], tws);
         } else {
-          load_pass_twiddles<T, N, R, NS>(t, tw, j);
+          cx<T> t[R];
+          load_pass_twiddles<T, PL, P>(t, tw, j);
+          dft_tw<R, NS, S>(v[i], t);
         }
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[i][r] = (S < 0) ? cmul(v[i][r], t[r]) : cmulc(v[i][r], t[r]);
+      } else {
+        dft<R, S>(v[i]);
       }
-      dft<R, S>(v[i]);
     }
   }
   pass_sync<MAP>();
@@ -615,7 +731,7 @@ __device__ __forceinline__ void fft_pass_mfma(float2* buf, const float2* tw, int
       float2 x = ok ? buf[lds_at<ES, BS, PADSH, PL, P>(b, j + r * NBF)] : make_float2(0.f, 0.f);
       if constexpr (NS > 1) {
         if (r > 0) {
-          const float2 tv = tw[k * r * (N / (NS * R))];
+          const float2 tv = tw[tw_offset<PL>(P) + (r - 1) * NS + k];
           x = (S < 0) ? cmul(x, tv) : cmulc(x, tv);
         }
       }
@@ -701,7 +817,7 @@ __device__ __forceinline__ void fft_pass_mfma_last(const float2* buf, const floa
       const int r = 4 * g + e;
       float2 x = ok ? buf[lds_at<ES, BS, PADSH, PL, P>(b, j + r * NBF)] : make_float2(0.f, 0.f);
       if (r > 0) {
-        const float2 tv = tw[j * r];  // k = j in the last pass
+        const float2 tv = tw[tw_offset<PL>(P) + (r - 1) * NS + j];  // k = j in the last pass
         x = (S < 0) ? cmul(x, tv) : cmulc(x, tv);
       }
       const __bf16 hr = (__bf16)x.x, hi = (__bf16)x.y;
@@ -775,7 +891,7 @@ __device__ __forceinline__ void fft_last_valu(cx<T>* buf, const cx<T>* tw, int t
   if constexpr (TWS) {
     int b0, j0;
     slot_map<NB, NBF, NT, MAP, linear_addr<PADSH>()>(tid, 0, b0, j0);
-    load_pass_twiddles<T, N, R, NBF>(tws, tw, j0);
+    load_pass_twiddles<T, PL, P>(tws, tw, j0);
   }
 #pragma unroll
   for (int i = 0; i < CNT; ++i) {
@@ -791,14 +907,11 @@ __device__ __forceinline__ void fft_last_valu(cx<T>* buf, const cx<T>* tw, int t
         else v[r] = buf[lds_at<ES, BS, PADSH, PL, P>(b, j + r * NBF)];
       }
       if constexpr (TWS) {
-#pragma unroll
-        for (int r = 1; r < R; ++r) t[r] = tws[r];
+        dft_tw<R, NBF, S>(v, tws);
       } else {
-        load_pass_twiddles<T, N, R, NBF>(t, tw, j);  // k = j in the last pass
+        load_pass_twiddles<T, PL, P>(t, tw, j);  // k = j in the last pass
+        dft_tw<R, NBF, S>(v, t);
       }
-#pragma unroll
-      for (int r = 1; r < R; ++r) v[r] = (S < 0) ? cmul(v[r], t[r]) : cmulc(v[r], t[r]);
-      dft<R, S>(v);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if ((GAP >> r) & 1u) continue;

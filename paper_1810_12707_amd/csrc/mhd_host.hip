@@ -1,5 +1,5 @@
 // libmhd host side: the C-ABI of include/mhd.h, workspace carving, twiddle
-// tables, the pass pipelines of the right-hand side and the FP64 reductions.
+// table upload, the pass pipelines of the right-hand side and the FP64 reductions.
 //
 // One right-hand-side evaluation (Eqs. MHD1-MHD4) runs as two phases:
 //   A: rho^, m^ --inverse z, y--> x-pass (u = m/rho, forward x) --forward y, z--> u^ = D F[u]
@@ -586,7 +586,7 @@ Layout make_layout(const Geo& g, size_t tsize) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   const size_t cplx = 2 * tsize;
-  L.tw = take((size_t)g.n * cplx);
+  L.tw = take(2 * (size_t)g.n * cplx);  // the tables of the default and of the alternative schedule's plan
   L.state = take(8 * (size_t)g.sc * cplx);
   L.rprev = take(8 * (size_t)g.sc * cplx);
   L.uhat = take(4 * (size_t)g.sc * cplx);
@@ -713,7 +713,7 @@ struct Engine {
   T* tstate() const { return at(c->L.tstate); }
   T* trhs() const { return at(c->L.trhs); }
   T* force() const { return at(c->L.force); }
-  T* tw() const { return at(c->L.tw); }
+  T* tw() const { return at(c->L.tw) + ((c->p.flags & MHD_FLAG_SCHEDULE_ALT) ? 2 * (size_t)g.n : 0); }
   T* iz(int slot) const { return at(c->L.iz) + 2 * (size_t)slot * g.iz; }
   T* iy(int slot) const { return at(c->L.iy) + 2 * (size_t)slot * g.iy; }
   T* spec_field(T* base, int f) const { return base + 2 * (size_t)f * g.sc; }
@@ -1180,20 +1180,20 @@ static int ctx_setup(mhd_ctx* c, const mhd_params* p, void* d_workspace, size_t 
   c->t = 0.0;
   const int rg = ctx_geometry(c);
   if (rg != MHD_OK) return rg;
-  // twiddles exp(-2 pi i j / n) in FP64, rounded once to the working precision
+  // the plans' twiddle tables, default schedule first (a context may switch)
+  const Registry& reg = registry();
   const int n = p->n;
-  const double two_pi = 6.28318530717958647692528676655900577;
-  double h64[2 * 1024];
-  float h32[2 * 1024];
-  for (int j = 0; j < n; ++j) {
-    const double cr = std::cos(two_pi * j / n), ci = -std::sin(two_pi * j / n);
-    h64[2 * j] = cr;
-    h64[2 * j + 1] = ci;
-    h32[2 * j] = (float)cr;
-    h32[2 * j + 1] = (float)ci;
+  double host[2 * 2 * 1024];
+  const size_t bytes = 4 * (size_t)n * ts;
+  std::memset(host, 0, bytes);
+  if (is_fp32(p->precision)) {
+    float* h = reinterpret_cast<float*>(host);
+    (p->precision == MHD_MIXED ? reg.mx : reg.f32)[n].twiddles(h);
+    if (p->precision == MHD_FP32 && reg.f32s1[n].row) reg.f32s1[n].twiddles(h + 2 * n);
+  } else {
+    reg.f64[n].twiddles(host);
   }
-  const void* src = is_fp32(p->precision) ? static_cast<const void*>(h32) : static_cast<const void*>(h64);
-  hipError_t e = hipMemcpyAsync(c->ws + c->L.tw, src, 2 * (size_t)n * ts, hipMemcpyHostToDevice, c->stream);
+  hipError_t e = hipMemcpyAsync(c->ws + c->L.tw, host, bytes, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host buffer dies with this frame
   return e == hipSuccess ? MHD_OK : MHD_E_HIP;
 }

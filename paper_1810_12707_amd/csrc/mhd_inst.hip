@@ -90,6 +90,7 @@ Kern<T> make() {
   k.n = N;
   k.col_width = col_tile<T, N, MX>();
   k.rhs_width = rhs_tile<T, N, MX>();
+  k.twiddles = make_twiddles<T, PlanOf<N, MX>>;
   k.col_inv = col_inv<T, N, MX>;
   k.col_fwd = col_fwd<T, N, MX>;
   k.rhs = rhs<T, N, MX>;

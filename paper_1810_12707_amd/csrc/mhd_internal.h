@@ -98,7 +98,7 @@ struct ColArgs {
   const T* in[kMaxIn];  // complex arrays (interleaved) in the pass's input layout
   T* out[kMaxOut];
   OutSpec spec[kMaxOut];
-  const T* tw;          // n twiddles exp(-2 pi i j / n), interleaved
+  const T* tw;          // twiddle table of the plan (make_twiddles)
   int32_t kind;         // PassKind
   int32_t nout;
   Geo g;

@@ -101,9 +101,9 @@ __device__ __forceinline__ void st(T* base, int64_t idx, cx<T> v) {
   reinterpret_cast<cx<T>*>(base)[idx] = v;
 }
 
-template <typename T, int N, int NT = kThreads>
+template <typename T, class PL, int NT>
 __device__ __forceinline__ void load_twiddles(cx<T>* stw, const T* tw, int tid) {
-  for (int i = tid; i < N; i += NT) stw[i] = ld(tw, i);
+  for (int i = tid; i < tw_entries<PL>(); i += NT) stw[i] = ld(tw, i);
 }
 
 // Band index of position q on a length-N axis, or -1 in the dropped gap.
@@ -160,7 +160,7 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT>())) k_col(cons
   constexpr int64_t ls_in = zpass ? (int64_t)NBB * NHP : NHP;
   constexpr int64_t os_out = zpass ? 0 : (S > 0 ? (int64_t)N * NHP : (int64_t)NBB * NHP);
   constexpr int64_t ls_out = ls_in;
-  load_twiddles<T, N, NT>(stw, a.tw, tid);
+  load_twiddles<T, PL, NT>(stw, a.tw, tid);
   auto col_ok = [&](int col) { return col < ncols && (!zpass || col - (col / NHP) * NHP < NH); };
 
   struct Item {
@@ -405,7 +405,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
     }
   };
 
-  load_twiddles<T, N, NT>(stw, a.tw, tid);
+  load_twiddles<T, PL, NT>(stw, a.tw, tid);
   cx<T> acc[LP::CNT][LP::R];
 #pragma unroll
   for (int i = 0; i < LP::CNT; ++i)
@@ -694,7 +694,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
   const int nout = (MODE == RM_XFWD_REAL || MODE == RM_XINV_REAL)
                        ? a.nf
                        : ((MODE == RM_XA && a.nf == 4) ? 4 : RowShape<MODE>::NOUT);
-  load_twiddles<T, N, NT>(stw, a.tw, tid);
+  load_twiddles<T, PL, NT>(stw, a.tw, tid);
   auto lds_store = [&](int, int, int fld, int q, cx<T> v) { buf[at(fld, q)] = v; };
 
   // Prefetch registers for the next row pair: the two rows' Hermitian
