@@ -695,6 +695,9 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
                        ? a.nf
                        : ((MODE == RM_XA && a.nf == 4) ? 4 : RowShape<MODE>::NOUT);
   load_twiddles<T, PL, NT>(stw, a.tw, tid);
+  // with wave maps no workgroup barrier comes before the first pass that reads
+  // the twiddles, which other waves loaded
+  if constexpr (WAVE) __syncthreads();
   auto lds_store = [&](int, int, int fld, int q, cx<T> v) { buf[at(fld, q)] = v; };
 
   // Prefetch registers for the next row pair: the two rows' Hermitian
