@@ -612,30 +612,37 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 
 // Threads of a row pass: FP32 rows of N >= 1024 take 512, which keeps the
 // per-thread first-pass work (and registers) of N = 512 on 256 threads.  The
-// FP32 flux pass at N = 512 and 256 also takes 512: with wave maps each wave
-// then owns two fields instead of four, the registers fit 128, and its LDS
+// FP32 flux pass at N = 512, 384 and 256 also takes 512: with wave maps each
+// wave then owns two fields instead of four, the registers fit 128, and its LDS
 // tile still allows two workgroups per CU, so four waves per SIMD run instead
 // of two (13% faster at 512) or three (3% at 256).  The FP32 velocity pass at
 // N = 256 takes 128: two waves of two fields each, whose 32-butterfly radix-8
 // passes then fill every lane (256 threads left half of them idle; 19%).
-// The FP64 flux pass at N = 512 takes 512 too (its 156 KB LDS tile allows
-// one workgroup per CU: two waves per SIMD instead of one, 6.78 -> 5.63 ms).
+// The FP64 flux pass at N = 512 and 384 takes 512 too (one workgroup per CU:
+// two waves per SIMD instead of one, 6.78 -> 5.63 ms at 512).
+// Below 256 (wave maps at 64 and 128): the velocity pass takes one wave per row
+// pair, which then needs no barrier (64: 11.1 -> 9.1 us FP64; 128: 36.6 ->
+// 32.4 us FP64, 22.6 -> 20.3 us FP32), the flux pass as many threads as let
+// every lane of a first pass hold a butterfly (128: 256 threads in FP32, 56.8 ->
+// 55.1 us) or half as many (64, and 128 in FP64 where the registers of two
+// butterflies fit: 20.2 -> 18.5 and 109 -> 89 us; FP32 at 128 would spill).
 template <typename T, int N, int MODE, bool MX> constexpr int row_threads() {
-  if (sizeof(T) == 4 && !MX && MODE == RM_XB && (N == 512 || N == 256)) return 2 * kThreads;
-  if (sizeof(T) == 8 && MODE == RM_XB && N == 512) return 2 * kThreads;
+  if (!MX && MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
+  if (!MX && MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
   if (sizeof(T) == 4 && !MX && MODE == RM_XA && N == 256) return kThreads / 2;
+  if (!MX && MODE == RM_XA && (N == 64 || N == 128 || (sizeof(T) == 8 && N == 192))) return 64;
   return (sizeof(T) == 4 && N >= 1024) ? 2 * kThreads : kThreads;
 }
 
-// Register caps of the FP32 row passes (MFMA variant included), as resident
-// workgroups per CU: two, i.e. two waves per SIMD at 256 threads and four for
-// the 512-thread flux pass at N = 256 and 512 (128 registers), which is what
-// their LDS allows.  Left free, the flux pass can take more than 256 registers
+// Register caps of the FP32 row passes (MFMA variant included): two waves per
+// SIMD from N = 256 on (the 512-thread flux passes come out at 128 registers or
+// fewer, four waves per SIMD, which is what their LDS allows).  Left free, the flux pass can take more than 256 registers
 // and then runs one wave per SIMD (the MFMA variant at N = 512 was 1.3x
 // slower so than capped).
 template <typename T, int N, int MODE, bool MX> constexpr int row_min_blocks() {
-  if (sizeof(T) == 4 && !MX && MODE == RM_XB && (N == 512 || N == 256)) return 2;
-  return sizeof(T) == 4 ? 2 * kThreads / row_threads<T, N, MODE, MX>() : 1;
+  if (sizeof(T) != 4 || row_threads<T, N, MODE, MX>() < kThreads) return 1;
+  if (!MX && MODE == RM_XB && (N == 512 || N == 384 || N == 256)) return 2;
+  return 2 * kThreads / row_threads<T, N, MODE, MX>();
 }
 
 template <typename T, int N, int MODE, bool MX>
@@ -666,13 +673,17 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
   // Wave maps: each field's transforms stay inside one wave, so a wave-level
   // fence replaces the workgroup barrier between passes and only the
   // pointwise stage, which reads every field at one point, is bracketed by
-  // barriers.  Used (measured) by the velocity and flux passes from N = 512
-  // (12% and 5% faster), the FP32 velocity and flux passes at 256 (with 128
-  // and 512 threads) and the mixed velocity pass from 512, whose last-pass
-  // MFMA groups then take the wave's own butterflies (7%); not by the mixed
-  // flux pass (slower) or with fewer fields than waves.
+  // barriers.  Used (measured) by the velocity and flux passes from N = 384
+  // (12% and 5% faster at 512), at 256, 128 and 64 (with the thread counts of
+  // row_threads), by the one-wave FP64 velocity pass at 192 (94 -> 85 us) and by
+  // the mixed velocity pass from 384, whose last-pass MFMA groups then take the
+  // wave's own butterflies (7%); not at 96 and 192 otherwise (their 12 and 32
+  // first-pass butterflies per field leave lanes of a wave idle: 96 FP32 flux
+  // pass 30.8 -> 35.7 us), by the mixed flux pass (slower) or with fewer fields
+  // than waves.
   constexpr bool WAVE = (MX ? (MODE == RM_XA && !mid_mfma<PL>()) : (MODE == RM_XA || MODE == RM_XB)) &&
-                       (N >= 512 || (!MX && N == 256)) && NB >= NT / 64;
+                       (N >= 384 || (!MX && (N == 256 || N == 128 || N == 64 || (N == 192 && NT == 64)))) &&
+                       NB >= NT / 64;
   // MFMA groups overlapped in the mixed last pass (measured: the velocity
   // pass 2, the flux pass 4 at N = 256; the others spill or slow down)
   constexpr int UNR = MODE == RM_XA ? 2 : ((MODE == RM_XB && N <= 256) ? 4 : 1);
@@ -906,58 +917,79 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
       // 4 Pi_xz, 5 Pi_yz, 6-8 F^E, 9-11 e = u x B.
       const T gm1 = T(a.gamma[mem] - 1.0), gam = T(a.gamma[mem]), two_nu = T(2.0 * a.nu[mem]),
               eta = T(a.eta[mem]);
-      for (int x = tid; x < N; x += NT) {
-        cx<T> v[16];
+      auto point = [&](const T (&v)[16], T (&out)[12]) {
+        const T rho = v[0], mx = v[1], my = v[2], mz = v[3];
+        const T Bx = v[4], By = v[5], Bz = v[6], E = v[7];
+        const T Sxx = v[8], Syy = v[9], Sxy = v[10], Sxz = v[11], Syz = v[12];
+        const T Szz = -(Sxx + Syy);
+        const T Jx = v[13], Jy = v[14], Jz = v[15];
+        const T ir = recip_(rho);
+        const T ux = mx * ir, uy = my * ir, uz = mz * ir;
+        const T B2 = Bx * Bx + By * By + Bz * Bz;
+        const T P = gm1 * (E - T(0.5) * (mx * ux + my * uy + mz * uz) - T(0.5) * B2);
+        const T Pt = P + T(0.5) * B2;
+        const T vr = two_nu * rho;
+        out[0] = mx * ux + Pt - Bx * Bx - vr * Sxx;
+        out[1] = my * uy + Pt - By * By - vr * Syy;
+        out[2] = mz * uz + Pt - Bz * Bz - vr * Szz;
+        out[3] = mx * uy - Bx * By - vr * Sxy;
+        out[4] = mx * uz - Bx * Bz - vr * Sxz;
+        out[5] = my * uz - By * Bz - vr * Syz;
+        const T uB = ux * Bx + uy * By + uz * Bz;
+        const T EP = E + Pt;
+        const T uSx = ux * Sxx + uy * Sxy + uz * Sxz;
+        const T uSy = ux * Sxy + uy * Syy + uz * Syz;
+        const T uSz = ux * Sxz + uy * Syz + uz * Szz;
+        out[6] = EP * ux - uB * Bx - vr * uSx - eta * (By * Jz - Bz * Jy);
+        out[7] = EP * uy - uB * By - vr * uSy - eta * (Bz * Jx - Bx * Jz);
+        out[8] = EP * uz - uB * Bz - vr * uSz - eta * (Bx * Jy - By * Jx);
+        out[9] = uy * Bz - uz * By;
+        out[10] = uz * Bx - ux * Bz;
+        out[11] = ux * By - uy * Bx;
+        // fastest signal speed for the CFL limit, and a non-finite check
+        const T umax = fmax(fabs(ux), fmax(fabs(uy), fabs(uz)));
+        const T c = umax + sqrt_((gam * P + B2) * ir);
+        if (!(c <= cfl)) cfl = c;  // NaN propagates
+        const bool fin = finite_(rho) && finite_(mx) && finite_(my) && finite_(mz) && finite_(Bx) &&
+                         finite_(By) && finite_(Bz) && finite_(E);
+        bad += fin ? 0 : 1;
+      };
+      // FP64 rows too short to give every thread a point of both rows: a thread
+      // takes a point of one row (half the serial work and registers per
+      // thread: flux pass at 96 56 -> 48 us, at 64 20.2 -> 19.1 us).  In FP32 the
+      // narrower LDS accesses cost as much as that saves (256: 360 -> 371 us).
+      constexpr bool HSPLIT = sizeof(T) == 8 && (2 * N + NT - 1) / NT < 2 * ((N + NT - 1) / NT);
+      if constexpr (HSPLIT) {
+        T* const bt = reinterpret_cast<T*>(buf);
+        for (int e = tid; e < 2 * N; e += NT) {
+          const int h = e >= N ? 1 : 0, x = e - h * N;
+          T v[16], o[12];
 #pragma unroll
-        for (int f = 0; f < 16; ++f) v[f] = buf[at(f, x)];
-        cx<T> o[12];
+          for (int f = 0; f < 16; ++f) v[f] = bt[2 * at(f, x) + h];
+          point(v, o);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          auto g = [&](int f) -> T { return h == 0 ? v[f].x : v[f].y; };
-          const T rho = g(0), mx = g(1), my = g(2), mz = g(3);
-          const T Bx = g(4), By = g(5), Bz = g(6), E = g(7);
-          const T Sxx = g(8), Syy = g(9), Sxy = g(10), Sxz = g(11), Syz = g(12);
-          const T Szz = -(Sxx + Syy);
-          const T Jx = g(13), Jy = g(14), Jz = g(15);
-          const T ir = recip_(rho);
-          const T ux = mx * ir, uy = my * ir, uz = mz * ir;
-          const T B2 = Bx * Bx + By * By + Bz * Bz;
-          const T P = gm1 * (E - T(0.5) * (mx * ux + my * uy + mz * uz) - T(0.5) * B2);
-          const T Pt = P + T(0.5) * B2;
-          const T vr = two_nu * rho;
-          T out[12];
-          out[0] = mx * ux + Pt - Bx * Bx - vr * Sxx;
-          out[1] = my * uy + Pt - By * By - vr * Syy;
-          out[2] = mz * uz + Pt - Bz * Bz - vr * Szz;
-          out[3] = mx * uy - Bx * By - vr * Sxy;
-          out[4] = mx * uz - Bx * Bz - vr * Sxz;
-          out[5] = my * uz - By * Bz - vr * Syz;
-          const T uB = ux * Bx + uy * By + uz * Bz;
-          const T EP = E + Pt;
-          const T uSx = ux * Sxx + uy * Sxy + uz * Sxz;
-          const T uSy = ux * Sxy + uy * Syy + uz * Syz;
-          const T uSz = ux * Sxz + uy * Syz + uz * Szz;
-          out[6] = EP * ux - uB * Bx - vr * uSx - eta * (By * Jz - Bz * Jy);
-          out[7] = EP * uy - uB * By - vr * uSy - eta * (Bz * Jx - Bx * Jz);
-          out[8] = EP * uz - uB * Bz - vr * uSz - eta * (Bx * Jy - By * Jx);
-          out[9] = uy * Bz - uz * By;
-          out[10] = uz * Bx - ux * Bz;
-          out[11] = ux * By - uy * Bx;
-#pragma unroll
-          for (int k = 0; k < 12; ++k) {
-            if (h == 0) o[k].x = out[k];
-            else o[k].y = out[k];
-          }
-          // fastest signal speed for the CFL limit, and a non-finite check
-          const T umax = fmax(fabs(ux), fmax(fabs(uy), fabs(uz)));
-          const T c = umax + sqrt_((gam * P + B2) * ir);
-          if (!(c <= cfl)) cfl = c;  // NaN propagates
-          const bool fin = finite_(rho) && finite_(mx) && finite_(my) && finite_(mz) && finite_(Bx) &&
-                           finite_(By) && finite_(Bz) && finite_(E);
-          bad += fin ? 0 : 1;
+          for (int k = 0; k < 12; ++k) bt[2 * at(k, x) + h] = o[k];
         }
+      } else {
+        for (int x = tid; x < N; x += NT) {
+          cx<T> v[16], o[12];
 #pragma unroll
-        for (int k = 0; k < 12; ++k) buf[at(k, x)] = o[k];
+          for (int f = 0; f < 16; ++f) v[f] = buf[at(f, x)];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            T vh[16], oh[12];
+#pragma unroll
+            for (int f = 0; f < 16; ++f) vh[f] = h == 0 ? v[f].x : v[f].y;
+            point(vh, oh);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+              if (h == 0) o[k].x = oh[k];
+              else o[k].y = oh[k];
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < 12; ++k) buf[at(k, x)] = o[k];
+        }
       }
     }
 
