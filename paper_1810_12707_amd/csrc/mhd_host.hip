@@ -560,7 +560,8 @@ bool size_ok(int32_t n, int32_t prec) {
   return prec == MHD_FP64 || prec == MHD_FP32 || prec == MHD_MIXED;
 }
 
-Geo make_geo(int n) {
+// tsize: bytes of a real in the working precision
+Geo make_geo(int n, size_t tsize) {
   Geo g;
   g.n = n;
   g.K = (n - 1) / 3;
@@ -568,8 +569,11 @@ Geo make_geo(int n) {
   g.nb = 2 * g.K + 1;
   g.nhp = (g.nh + 7) / 8 * 8;
   g.sc = (int64_t)g.nb * g.nb * g.nhp;
-  g.iz = (int64_t)n * g.nb * g.nhp;
-  g.iy = (int64_t)n * n * g.nhp;
+  const int64_t al = kLineBytes / (2 * (int64_t)tsize);
+  g.py = (int32_t)((g.nh + al - 1) / al * al);
+  g.pz = ((int64_t)g.nb * g.nhp + al - 1) / al * al;
+  g.iz = (int64_t)n * g.pz;
+  g.iy = (int64_t)n * n * g.py;
   g.n3 = (int64_t)n * n * n;
   return g;
 }
@@ -1168,8 +1172,8 @@ static int ctx_geometry(mhd_ctx* c);
 // (synchronously).  The workspace must have been checked by the caller.
 static int ctx_setup(mhd_ctx* c, const mhd_params* p, void* d_workspace, size_t ws_bytes, hipStream_t stream) {
   c->p = *p;
-  c->g = make_geo(p->n);
   const size_t ts = is_fp32(p->precision) ? sizeof(float) : sizeof(double);
+  c->g = make_geo(p->n, ts);
   c->L = make_layout(c->g, ts);
   c->stream = stream;
   c->ws = static_cast<char*>(d_workspace);
@@ -1669,18 +1673,18 @@ int mhd_supported_size(int32_t n, int32_t precision) { return size_ok(n, precisi
 
 int64_t mhd_spectrum_size(int32_t n) {
   if (n < 1) return 0;
-  return make_geo(n).sc;
+  return make_geo(n, sizeof(float)).sc;
 }
 
 int32_t mhd_spectrum_pitch(int32_t n) {
   if (n < 1) return 0;
-  return make_geo(n).nhp;
+  return make_geo(n, sizeof(float)).nhp;
 }
 
 size_t mhd_workspace_bytes(const mhd_params* p) {
   if (validate(p) != MHD_OK) return 0;
   const size_t ts = is_fp32(p->precision) ? sizeof(float) : sizeof(double);
-  return make_layout(make_geo(p->n), ts).total;
+  return make_layout(make_geo(p->n, ts), ts).total;
 }
 
 int mhd_init(const mhd_params* p, void* d_workspace, size_t ws_bytes, void* hip_stream, mhd_ctx** out) {

@@ -2,10 +2,11 @@
 //
 // Data layout in HBM (per field, working precision T, complex = interleaved
 // (re, im) pairs; K = (n-1)/3, nh = K+1, nb = 2K+1, nhp = nh rounded up to a
-// multiple of 8 so that every kx row starts on a 64-byte boundary):
-//   compact spectrum S  [kz: nb][ky: nb][kx: nhp]  (state, history, u^)
-//   z-pass intermediate [z: n][ky: nb][kx: nhp]    ("I_z")
-//   y-pass intermediate [z: n][y: n][kx: nhp]      ("I_y")
+// multiple of 8 so that every kx row starts on a 64-byte boundary; py = nh and
+// pz = nb * nhp rounded up to whole 128-byte lines):
+//   compact spectrum S  [kz: nb][ky: nb][kx: nhp]        (state, history, u^)
+//   z-pass intermediate [z: n, plane stride pz][ky: nb][kx: nhp]  ("I_z")
+//   y-pass intermediate [z: n][y: n][kx: py]             ("I_y")
 // Entries with kx >= nh are padding: never read, never written.
 // Band indices run 0..K then -K..-1; along a length-n axis, band index l sits
 // at position l (l <= K) or l + n - nb (l > K).
@@ -33,6 +34,7 @@
 
 namespace mhd {
 
+constexpr int kLineBytes = 128;  // memory line the intermediates' rows and planes are padded to
 constexpr int kThreads = 256;  // threads per workgroup of every pass kernel
 constexpr int kMaxTerms = 3;   // terms of one spectral linear combination
 constexpr int kMaxOut = 12;    // outputs of one column launch
@@ -69,6 +71,8 @@ enum PassKind { PK_ZINV = 0, PK_YINV = 1, PK_YFWD = 2, PK_ZFWD = 3 };
 struct Geo {
   int32_t n, K, nh, nb;
   int32_t nhp;  // kx pitch: nh rounded up to a multiple of 8
+  int32_t py;   // kx pitch of I_y (depends on the element type)
+  int64_t pz;   // z plane of I_z (likewise)
   int64_t sc;  // complex values per compact spectrum
   int64_t iz;  // complex values per I_z field
   int64_t iy;  // complex values per I_y field

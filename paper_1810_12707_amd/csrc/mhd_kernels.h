@@ -24,6 +24,15 @@ template <int N> struct Band {
   static constexpr int NHP = (NH + 7) / 8 * 8;  // kx pitch of every layout (64-byte rows)
 };
 
+// Pitches of the intermediates, in whole 128-byte lines: the kx row of I_y, and
+// the z plane of I_z (whose rows keep the compact pitch NHP, so that a z pass
+// over flattened (ky, kx) columns transforms no more padding than it has to).
+template <typename T, int N> struct Pitch {
+  static constexpr int AL = kLineBytes / (2 * (int)sizeof(T));
+  static constexpr int Y = (Band<N>::NH + AL - 1) / AL * AL;
+  static constexpr int Z = (Band<N>::NB * Band<N>::NHP + AL - 1) / AL * AL;
+};
+
 // Position of band index l on a length-N axis, and its wavenumber.
 template <int N> __device__ __forceinline__ int band_pos(int l) { return l <= Band<N>::K ? l : l + N - Band<N>::NB; }
 template <int N> __device__ __forceinline__ int band_k(int l) { return l <= Band<N>::K ? l : l - Band<N>::NB; }
@@ -156,10 +165,11 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT>())) k_col(cons
   // strides (complex elements) of the input and output layouts: z passes
   // (either direction) map [kz][ky][kx] onto itself; the inverse y pass reads
   // [kz][ky band][kx] and writes [kz][y][kx], the forward one the reverse
-  constexpr int64_t os_in = zpass ? 0 : (S > 0 ? (int64_t)NBB * NHP : (int64_t)N * NHP);
-  constexpr int64_t ls_in = zpass ? (int64_t)NBB * NHP : NHP;
-  constexpr int64_t os_out = zpass ? 0 : (S > 0 ? (int64_t)N * NHP : (int64_t)NBB * NHP);
-  constexpr int64_t ls_out = ls_in;
+  constexpr int64_t PY = Pitch<T, N>::Y, PZ = Pitch<T, N>::Z;
+  constexpr int64_t os_in = zpass ? 0 : (S > 0 ? PZ : N * PY);
+  constexpr int64_t ls_in = zpass ? (S > 0 ? (int64_t)NBB * NHP : PZ) : (S > 0 ? NHP : PY);
+  constexpr int64_t os_out = zpass ? 0 : (S > 0 ? N * PY : PZ);
+  constexpr int64_t ls_out = zpass ? (S > 0 ? PZ : (int64_t)NBB * NHP) : (S > 0 ? PY : NHP);
   load_twiddles<T, PL, NT>(stw, a.tw, tid);
   auto col_ok = [&](int col) { return col < ncols && (!zpass || col - (col / NHP) * NHP < NH); };
 
@@ -341,7 +351,8 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
   const int mem = tf.tile / ZT;
   const int c0 = (tf.tile - mem * ZT) * C;
   const int64_t sc = a.g.sc;
-  const int64_t LS = NCOLS;  // row stride of I_z (z) and of compact (kz)
+  constexpr int64_t LS = NCOLS;             // plane stride of a compact spectrum (kz)
+  constexpr int64_t LSZ = Pitch<T, N>::Z;  // plane stride of I_z (z)
   const T dt = T(a.dt[mem]), ac = T(a.a_cur[mem]), ap = T(a.a_prev[mem]);
   const bool use_prev = a.a_prev[mem] != 0.0;
   const int64_t ms = a.bt.mstride;
@@ -433,7 +444,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
       const int kx = col - (col / NHP) * NHP;
       if (col >= NCOLS || kx >= NH) return v;
       const int ky = band_k<N>(col / NHP);
-      const int64_t idx = (int64_t)q * LS + col;
+      const int64_t idx = (int64_t)q * LSZ + col;
       const cx<T> x0 = ld(p0, idx);
       const cx<T> x1 = nt > 1 ? ld(p1, idx) : mk<T>(0, 0);
       const cx<T> xs[2] = {x0, x1};
@@ -650,7 +661,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
     k_row(const RowArgs<T> a) {
   using PL = PlanOf<N, MX>;
   constexpr int NT = row_threads<T, N, MODE, MX>();
-  constexpr int K = Band<N>::K, NHP = Band<N>::NHP;
+  constexpr int K = Band<N>::K, PY = Pitch<T, N>::Y;
   constexpr int NH = Band<N>::NH;
   constexpr int NB = RowShape<MODE>::NB;
   // LDS row layout, chosen per pass by measurement.  Linear addressing where
@@ -745,8 +756,8 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
         p1[i][r] = mk<T>(0, 0);
         if ((ZROWS >> r) & 1u) continue;
         if (ok && q <= K) {
-          p0[i][r] = ld(src, row0 * NHP + q);
-          p1[i][r] = ld(src, (row0 + 1) * NHP + q);
+          p0[i][r] = ld(src, row0 * PY + q);
+          p1[i][r] = ld(src, (row0 + 1) * PY + q);
         }
       }
     }
@@ -862,8 +873,8 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
           } else {
             const int q = j + r * FP::NBF;
             if (ok && q >= N - K) {
-              x0 = ld(src, row0 * NHP + (N - q));
-              x1 = ld(src, (row0 + 1) * NHP + (N - q));
+              x0 = ld(src, row0 * PY + (N - q));
+              x1 = ld(src, (row0 + 1) * PY + (N - q));
             }
           }
           v[i][r] = mk<T>(x0.x + x1.y, x1.x - x0.y);
@@ -1046,15 +1057,15 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
         const cx<T> x0 = mk<T>(zk.x + zm.x, zk.y - zm.y);
         const cx<T> x1 = mk<T>(zk.y + zm.y, zm.x - zk.x);
         T* dst = out0 + 2 * fld * ost;
-        st(dst, row0 * NHP + k, x0);
-        st(dst, (row0 + 1) * NHP + k, x1);
+        st(dst, row0 * PY + k, x0);
+        st(dst, (row0 + 1) * PY + k, x1);
       };
       // the same with the field's output row as one wave-uniform pointer
       auto unpack_row = [&](cx<T>* dst, int fld, int k) {
         const cx<T> zk = buf[at(fld, k)];
         const cx<T> zm = buf[at(fld, k == 0 ? 0 : N - k)];
         dst[k] = mk<T>(zk.x + zm.x, zk.y - zm.y);
-        dst[NHP + k] = mk<T>(zk.y + zm.y, zm.x - zk.x);
+        dst[PY + k] = mk<T>(zk.y + zm.y, zm.x - zk.x);
       };
       if constexpr (WAVE) {
         // Each wave unpacks the fields it transformed, field by field: the
@@ -1066,7 +1077,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
         constexpr int W = NT / 64;
         constexpr int KIT = (NH + 63) / 64;
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-        cx<T>* const row_out = reinterpret_cast<cx<T>*>(out0) + row0 * NHP;
+        cx<T>* const row_out = reinterpret_cast<cx<T>*>(out0) + row0 * PY;
 #pragma unroll 1
         for (int fl = 0; fl < seqs_per_wave<NB, NT>(); ++fl) {
           const int fld = fl * W + wv;
