@@ -628,7 +628,7 @@ struct mhd_ctx {
   double t;
   int num_cus = 0;
   int row_blocks[5] = {0, 0, 0, 0, 0};  // resident workgroups of each row-pass mode
-  int col_blocks[3] = {0, 0, 0};        // column passes: forward, inverse (1 term), inverse (3 terms)
+  ColClass col_class[3][2];             // column passes: forward, inverse (1 term), inverse (3 terms); y, z
   std::string last_err;
   // benchmark timing (mhd_profile)
   bool prof_on = false;
@@ -769,9 +769,7 @@ struct Engine {
     }
   }
 
-  int ztiles() const { return (int)(((int64_t)g.nb * g.nhp + k.col_width - 1) / k.col_width); }
   int rtiles() const { return (int)(((int64_t)g.nb * g.nhp + k.rhs_width - 1) / k.rhs_width); }
-  int ytiles() const { return (g.nh + k.col_width - 1) / k.col_width; }
 
   Batch batch() const {
     Batch b;
@@ -805,8 +803,10 @@ struct Engine {
     }
     const bool z = (kind == PK_ZINV || kind == PK_ZFWD);
     const bool inv = (kind == PK_ZINV || kind == PK_YINV);
-    const int64_t items = (int64_t)(z ? ztiles() : g.n * ytiles()) * nout * ms.n;
-    int64_t blocks = (int64_t)(c->col_blocks[inv ? (maxt > 1 ? 2 : 1) : 0] * ms.col_scale);
+    const ColClass& cc = c->col_class[inv ? (maxt > 1 ? 2 : 1) : 0][z];
+    const int64_t tiles = ((z ? (int64_t)g.nb * g.nhp : g.nh) + cc.width - 1) / cc.width;
+    const int64_t items = (z ? tiles : g.n * tiles) * nout * ms.n;
+    int64_t blocks = (int64_t)(cc.blocks * ms.col_scale);
     // at least one workgroup per XCD range of the item walk (or one per item)
     if (blocks < 8) blocks = 8;
     if (blocks > items) blocks = items;
@@ -1218,13 +1218,14 @@ static int ctx_geometry(mhd_ctx* c) {
                         : static_cast<const Kern<double>*>(kv)->row_occupancy(m);
     c->row_blocks[m] = occ * c->num_cus;
   }
-  const int cocc[3] = {f32 ? static_cast<const Kern<float>*>(kv)->col_occupancy(-1, 1)
-                           : static_cast<const Kern<double>*>(kv)->col_occupancy(-1, 1),
-                       f32 ? static_cast<const Kern<float>*>(kv)->col_occupancy(1, 1)
-                           : static_cast<const Kern<double>*>(kv)->col_occupancy(1, 1),
-                       f32 ? static_cast<const Kern<float>*>(kv)->col_occupancy(1, 3)
-                           : static_cast<const Kern<double>*>(kv)->col_occupancy(1, 3)};
-  for (int m = 0; m < 3; ++m) c->col_blocks[m] = cocc[m] * c->num_cus;
+  for (int m = 0; m < 3; ++m) {
+    const int dir = m == 0 ? -1 : 1, maxt = m == 2 ? kMaxTerms : 1;
+    for (int z = 0; z < 2; ++z) {
+      c->col_class[m][z] = f32 ? static_cast<const Kern<float>*>(kv)->col_class(dir, maxt, z != 0)
+                               : static_cast<const Kern<double>*>(kv)->col_class(dir, maxt, z != 0);
+      c->col_class[m][z].blocks *= c->num_cus;
+    }
+  }
   return MHD_OK;
 }
 

@@ -13,9 +13,10 @@ namespace {
 // Column passes: one instantiation per direction, term count and axis (z or y).
 template <typename T, int N, int S, int MAXT, bool MX>
 void col_launch(const ColArgs<T>& a, dim3 g, hipStream_t s) {
-  constexpr int nt = col_threads<T, N, MX, S, MAXT>();
-  if (a.kind == PK_ZINV || a.kind == PK_ZFWD) hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, true>), g, dim3(nt), 0, s, a);
-  else hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, false>), g, dim3(nt), 0, s, a);
+  if (a.kind == PK_ZINV || a.kind == PK_ZFWD)
+    hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, true>), g, dim3(col_threads<T, N, MX, S, MAXT, true>()), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, false>), g, dim3(col_threads<T, N, MX, S, MAXT, false>()), 0, s, a);
 }
 template <typename T, int N, bool MX>
 void col_inv(int maxt, const ColArgs<T>& a, dim3 g, hipStream_t s) {
@@ -26,23 +27,25 @@ template <typename T, int N, bool MX>
 void col_fwd(const ColArgs<T>& a, dim3 g, hipStream_t s) {
   col_launch<T, N, -1, 1, MX>(a, g, s);
 }
-// Resident workgroups per CU of a column-pass class: the smaller of its z and
-// y instantiations (the persistent grid is sized once per class).
-template <typename T, int N, int S, int MAXT, bool MX>
-int col_occ(void) {
-  constexpr int nt = col_threads<T, N, MX, S, MAXT>();
-  int bz = 0, by = 0;
-  const hipError_t ez = hipOccupancyMaxActiveBlocksPerMultiprocessor(&bz, k_col<T, N, S, MAXT, MX, true>, nt, 0);
-  const hipError_t ey = hipOccupancyMaxActiveBlocksPerMultiprocessor(&by, k_col<T, N, S, MAXT, MX, false>, nt, 0);
-  if (ez != hipSuccess || ey != hipSuccess) return 1;
-  const int b = bz < by ? bz : by;
-  return b > 0 ? b : 1;
+// Tile width and resident workgroups per CU of a column-pass class.
+template <typename T, int N, int S, int MAXT, bool MX, bool Z>
+ColClass col_occ(void) {
+  ColClass c;
+  c.width = col_tile<T, N, MX, S, MAXT, Z>();
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c.blocks, k_col<T, N, S, MAXT, MX, Z>,
+                                                                    col_threads<T, N, MX, S, MAXT, Z>(), 0);
+  if (e != hipSuccess || c.blocks < 1) c.blocks = 1;
+  // the 1024-thread tiles at 256: one workgroup per CU also where the registers
+  // would let two reside (more rows of more fields in flight at once cost HBM
+  // efficiency: 12-field forward y pass 239 us with one, 253 with two)
+  if (N == 256 && col_threads<T, N, MX, S, MAXT, Z>() == 4 * kThreads) c.blocks = 1;
+  return c;
 }
 template <typename T, int N, bool MX>
-int col_occupancy(int dir, int maxt) {
-  if (dir < 0) return col_occ<T, N, -1, 1, MX>();
-  if (maxt <= 1) return col_occ<T, N, 1, 1, MX>();
-  return col_occ<T, N, 1, kMaxTerms, MX>();
+ColClass col_class(int dir, int maxt, bool z) {
+  if (dir < 0) return z ? col_occ<T, N, -1, 1, MX, true>() : col_occ<T, N, -1, 1, MX, false>();
+  if (maxt <= 1) return z ? col_occ<T, N, 1, 1, MX, true>() : col_occ<T, N, 1, 1, MX, false>();
+  return z ? col_occ<T, N, 1, kMaxTerms, MX, true>() : col_occ<T, N, 1, kMaxTerms, MX, false>();
 }
 template <typename T, int N, bool MX>
 void rhs(const RhsArgs<T>& a, dim3 g, hipStream_t s) {
@@ -88,7 +91,6 @@ template <typename T, int N, bool MX>
 Kern<T> make() {
   Kern<T> k;
   k.n = N;
-  k.col_width = col_tile<T, N, MX>();
   k.rhs_width = rhs_tile<T, N, MX>();
   k.twiddles = make_twiddles<T, PlanOf<N, MX>>;
   k.col_inv = col_inv<T, N, MX>;
@@ -96,7 +98,7 @@ Kern<T> make() {
   k.rhs = rhs<T, N, MX>;
   k.row = row<T, N, MX>;
   k.row_occupancy = row_occupancy<T, N, MX>;
-  k.col_occupancy = col_occupancy<T, N, MX>;
+  k.col_class = col_class<T, N, MX>;
   return k;
 }
 

@@ -58,47 +58,74 @@ template <typename T, int N> constexpr int col_width() {
 // FP64 at N = 512 takes 512 threads on its 8-column tiles, one butterfly
 // each (146 registers instead of 256 with 256 threads, three waves per SIMD
 // instead of one: 6.89 -> 4.35 ms per step).
+// From 384 the same 16-column tiles with 1024 threads (384 FP32 924 -> 890 us,
+// FP64 1985 -> 1656 us).  The mixed path at 256 and FP32 at 192 and 96 take 8
+// columns and 256 threads (more, smaller workgroups: 371 -> 349, 126 -> 102 and
+// 17.3 -> 16.3 us).
 template <typename T, int N, bool MX> constexpr bool rhs_wide() { return sizeof(T) == 4 && N >= 256; }
 template <typename T, int N, bool MX> constexpr int rhs_threads() {
   if (sizeof(T) == 8 && N == 512) return 2 * kThreads;
+  if (!MX && N == 384) return 4 * kThreads;
   if (sizeof(T) == 4 && ((!MX && N == 512) || N == 1024)) return 4 * kThreads;
+  if (MX && N == 256) return kThreads;
   return rhs_wide<T, N, MX>() ? 2 * kThreads : kThreads;
 }
 template <typename T, int N, bool MX> constexpr int rhs_tile() {
+  if (!MX && N == 384) return 16;
   if (sizeof(T) == 4 && !MX && N == 512) return 16;
-  return rhs_wide<T, N, MX>() ? (N == 256 ? 16 : 8) : col_width<T, N>();
+  if (sizeof(T) == 4 && !MX && (N == 192 || (N == 96 && MHD_SCHED == 0))) return 8;
+  return rhs_wide<T, N, MX>() ? (N == 256 && !MX ? 16 : 8) : col_width<T, N>();
 }
 // Minimum resident waves per SIMD asked of the compiler (register cap).
 template <typename T, int N, bool MX> constexpr int rhs_min_waves() {
-  return rhs_wide<T, N, MX>() || (sizeof(T) == 8 && N == 512) ? 1 : 3;
+  return rhs_wide<T, N, MX>() || rhs_threads<T, N, MX>() > kThreads ? 1 : 3;
 }
 
-// Threads and tile width of the column passes (S = +1 inverse, -1 forward;
-// MAXT input terms per element).  Long FP32 columns take 16-column tiles, so
-// that every row segment is a whole 128-byte line (8 FP32 columns would read
-// half lines, whose other halves another workgroup reads later, often after
-// eviction), and enough threads that each holds one or two first-pass
-// butterflies.  Measured per pass class: one butterfly per thread (fewer
-// registers, more resident waves) pays for the inverse passes at N = 256 and
-// 512 and for the forward passes at N = 512; the forward passes at N = 256
-// run best with two.  At N = 1024 the passes take 8-column tiles with 1024
-// threads, one first-pass butterfly each (98-126 registers, four waves per
-// SIMD; with 512 threads they held 162-222 and ran two: 8-15% slower per
-// pass, FP32 and mixed).  FP64 at N = 512 (8-column tiles) takes 512 threads,
-// one butterfly each (144-202 registers instead of 242-256 and one wave per
-// SIMD with 256 threads; the three-term pass 3.02 -> 2.38 ms per step), other
-// FP64 sizes 256.  The MFMA variant follows the FP32 rule from N = 256 up
-// (its one-term inverse passes at 256 hold 112 registers with 512 threads,
-// 180 with 256: 8-12% faster) and keeps 256 threads below.
-template <typename T, int N, bool MX, int S, int MAXT> constexpr int col_threads() {
-  if (sizeof(T) == 8 && N == 512) return 2 * kThreads;
-  if (sizeof(T) != 4 || (MX && N < 256)) return kThreads;
-  if (N == 256) return (MAXT > 1 || S > 0) ? 2 * kThreads : kThreads;
-  if (N == 512 || N == 1024) return 4 * kThreads;
-  return N > 512 ? 2 * kThreads : kThreads;
+// Threads and tile width (columns) of the column passes: S = +1 inverse, -1
+// forward; MAXT input terms per element; Z axis z, else y.  Two things decide
+// them, measured per pass class (microseconds per launch in the step, before ->
+// after):
+//  - a tile's row segment is a run of C columns, and a persistent workgroup has
+//    one tile's loads in flight: wide tiles (256-byte segments, 1024 threads) keep
+//    more bytes in flight per CU where the arrays come from HBM (256 FP32 12-field
+//    y passes 269 -> 255 and 254 -> 239; FP64 445 -> 419), narrow ones make more
+//    items for the small z launches;
+//  - one first-pass butterfly per thread (fewest registers, most waves) is the
+//    fastest for the inverse passes throughout and for most forward ones; the
+//    three-term pass, which holds three inputs per element, only fits that way
+//    (384 FP32 652 -> 492; 256 FP64 291 -> 266; 512 FP64 3020 -> 2380).
+// Sizes up to 128: 16 columns while the tile stays within 32 KiB; 128 threads at
+// 64 (256 left half of them idle: step 81 -> 79).
+struct ColShape {
+  int c, nt;
+};
+template <typename T, int N, bool MX, int S, int MAXT, bool Z> constexpr ColShape col_shape() {
+  constexpr bool f32 = sizeof(T) == 4, one = MAXT == 1;
+  if (MHD_SCHED == 0) {
+    if (N == 64 && !MX) return {16, 128};
+    if (N == 192 && !MX) {
+      if (f32) return !one ? ColShape{16, 512} : (S > 0 ? ColShape{32, 512} : ColShape{16, 256});
+      return !one ? ColShape{8, 256} : (S > 0 ? ColShape{32, 1024} : ColShape{16, 512});
+    }
+    if (N == 256) {
+      if (!Z || (f32 && !one)) return {32, 1024};
+      return {16, f32 && !MX && S < 0 ? 256 : 512};
+    }
+    if (N == 384) {
+      if (MX) return {16, 512};
+      return f32 || one ? ColShape{16, 1024} : ColShape{8, 512};
+    }
+    if (N == 512) return f32 ? ColShape{16, 1024} : ColShape{8, 512};
+    if (N == 768) return {8, f32 ? 512 : 256};
+    if (N == 1024) return {8, 1024};
+  }
+  return {col_width<T, N>(), kThreads};
 }
-template <typename T, int N, bool MX> constexpr int col_tile() {
-  return (sizeof(T) == 4 && N >= 256 && N <= 512) ? 16 : col_width<T, N>();
+template <typename T, int N, bool MX, int S, int MAXT, bool Z> constexpr int col_threads() {
+  return col_shape<T, N, MX, S, MAXT, Z>().nt;
+}
+template <typename T, int N, bool MX, int S, int MAXT, bool Z> constexpr int col_tile() {
+  return col_shape<T, N, MX, S, MAXT, Z>().c;
 }
 
 template <typename T>
@@ -146,10 +173,10 @@ __device__ __forceinline__ TileField tile_field(int nfields) {
 // geometry, the strides and the wavenumbers of the multipliers are constants
 // rather than uniform branches per element.
 template <typename T, int N, int S, int MAXT, bool MX, bool Z>
-__global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT>())) k_col(const ColArgs<T> a) {
+__global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(const ColArgs<T> a) {
   using PL = PlanOf<N, MX>;
-  constexpr int C = col_tile<T, N, MX>();
-  constexpr int NT = col_threads<T, N, MX, S, MAXT>();
+  constexpr int C = col_tile<T, N, MX, S, MAXT, Z>();
+  constexpr int NT = col_threads<T, N, MX, S, MAXT, Z>();
   constexpr int NH = Band<N>::NH, NHP = Band<N>::NHP, NBB = Band<N>::NB;
   using FP = FirstPass<PL, C, NT>;
   __shared__ cx<T> tile[N * C];

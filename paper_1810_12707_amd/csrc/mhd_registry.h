@@ -6,16 +6,21 @@
 
 namespace mhd {
 
+// Launch geometry of a column-pass class (direction, term count, axis).
+struct ColClass {
+  int width = 0;   // columns per work item
+  int blocks = 0;  // resident workgroups (per CU from the kernels; per GPU in a context)
+};
+
 template <typename T>
 struct Kern {
   int n = 0;
-  int col_width = 0;  // columns per work item of the column passes
   int rhs_width = 0;  // columns per workgroup of the forward-z RHS pass
   void (*twiddles)(T*) = nullptr;  // fills the plan's twiddle table (at most n complex values)
   // column passes; maxt = largest number of terms of any output spec (1 or 3)
   void (*col_inv)(int maxt, const ColArgs<T>&, dim3, hipStream_t) = nullptr;
   void (*col_fwd)(const ColArgs<T>&, dim3, hipStream_t) = nullptr;
-  int (*col_occupancy)(int dir, int maxt) = nullptr;
+  ColClass (*col_class)(int dir, int maxt, bool z) = nullptr;
   void (*rhs)(const RhsArgs<T>&, dim3, hipStream_t) = nullptr;
   void (*row)(int mode, const RowArgs<T>&, dim3, hipStream_t) = nullptr;
   // resident workgroups per CU of a row-pass mode (persistent grid sizing)
