@@ -311,8 +311,10 @@ enum {
  * context's stream (-1 selects every class; at most 4096 launches are
  * recorded, later ones are counted as dropped); class_mask = 0 stops
  * recording.  Each event pair adds a little time between launches, so a
- * throughput measurement should select only the classes it needs.  Creates
- * its events on first use (no device memory). */
+ * throughput measurement should select only the classes it needs.  While
+ * recording, small grids run the passes one by one too (otherwise several of
+ * them run in one launch; the results are the same bits).  Creates its events on
+ * first use (no device memory). */
 int mhd_profile(mhd_ctx* ctx, int32_t class_mask);
 
 /* Synchronises the stream and writes, per launch class (MHD_PASS_*), the

@@ -38,12 +38,17 @@ template <typename T> using cx = typename V2<T>::t;
 template <typename T> __device__ __forceinline__ cx<T> mk(T a, T b) { cx<T> r; r.x = a; r.y = b; return r; }
 template <typename X> __device__ __forceinline__ X cadd(X a, X b) { X r; r.x = a.x + b.x; r.y = a.y + b.y; return r; }
 template <typename X> __device__ __forceinline__ X csub(X a, X b) { X r; r.x = a.x - b.x; r.y = a.y - b.y; return r; }
+// Products and sums of products name their FMAs: left to the compiler, which of
+// the two products is rounded by itself would differ from kernel to kernel, and
+// the fused and the pass-by-pass kernels would not agree bit for bit.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename X> __device__ __forceinline__ X cmul(X a, X b) {
-  X r; r.x = a.x * b.x - a.y * b.y; r.y = a.x * b.y + a.y * b.x; return r;
+  X r; r.x = fma_(-a.y, b.y, a.x * b.x); r.y = fma_(a.y, b.x, a.x * b.y); return r;
 }
 // a * conj(b)
 template <typename X> __device__ __forceinline__ X cmulc(X a, X b) {
-  X r; r.x = a.x * b.x + a.y * b.y; r.y = a.y * b.x - a.x * b.y; return r;
+  X r; r.x = fma_(a.y, b.y, a.x * b.x); r.y = fma_(-a.x, b.y, a.y * b.x); return r;
 }
 template <typename X> __device__ __forceinline__ X cconj(X a) { X r; r.x = a.x; r.y = -a.y; return r; }
 template <typename X, typename S> __device__ __forceinline__ X cscale(X a, S s) { X r; r.x = a.x * s; r.y = a.y * s; return r; }
@@ -54,8 +59,6 @@ template <typename X> __device__ __forceinline__ X ctimes_mi(X a) { X r; r.x = a
 template <int S, typename X> __device__ __forceinline__ X ctimes_si(X a) { return S < 0 ? ctimes_mi(a) : ctimes_i(a); }
 
 // s a + b for a real s
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename X, typename T> __device__ __forceinline__ X cfma(T s, X a, X b) {
   X r; r.x = fma_(s, a.x, b.x); r.y = fma_(s, a.y, b.y); return r;
 }
@@ -88,11 +91,11 @@ template <int S, typename X> __device__ __forceinline__ void dft3(X* v) {
   const T h = T(0.86602540378443864676372317075294);  // sin(pi/3)
   X t = cadd(v[1], v[2]);
   X d = csub(v[1], v[2]);
-  X m = csub(v[0], cscale(t, T(0.5)));
+  X m = cfma(T(-0.5), t, v[0]);
   v[0] = cadd(v[0], t);
-  X sd = ctimes_si<S>(cscale(d, h));  // S * i * sin(pi/3) * (v1 - v2)
-  v[1] = cadd(m, sd);
-  v[2] = csub(m, sd);
+  X sd = ctimes_si<S>(d);  // S * i * (v1 - v2)
+  v[1] = cfma(h, sd, m);
+  v[2] = cfma(-h, sd, m);
 }
 
 template <int S, typename X> __device__ __forceinline__ void dft4(X* v) {

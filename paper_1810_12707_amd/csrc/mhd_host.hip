@@ -19,7 +19,7 @@
 #include <vector>
 
 #include "../../include/mhd.h"
-#include "mhd_internal.h"
+#include "mhd_kernels.h"
 #include "mhd_registry.h"
 
 namespace mhd {
@@ -96,51 +96,20 @@ k_reduce(const double* __restrict__ p1, int64_t n1, int nq1, unsigned max_mask, 
   }
 }
 
-// Spectral sums over the compact B^ (half spectrum: kx > 0 modes count twice):
-// sum Re(J^ . conj B^)/|k|^2, sum |i k.B^|^2, sum |J^|^2 with J^ = i k x B^.
-// Eq. MHD1 in spectral form, R_rho = -i k . m^, with the density's AB2
-// update U_rho += dt (a_cur R + a_prev R_prev), R_prev <- R, or the store of
-// R into rout.  One thread per compact entry (padding skipped) of member
-// blockIdx.y.  Launched before the forward-z pass that forms the other seven
-// right-hand sides, since that pass overwrites m^ with its next time level.
+// The density right-hand side and update (rho_entry), one thread per compact
+// entry (padding skipped) of member blockIdx.y.  Launched before the forward-z
+// pass that forms the other seven right-hand sides, since that pass overwrites m^
+// with its next time level.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) k_rho_rhs(const RhsArgs<T> a) {
-  using V2 = typename std::conditional<sizeof(T) == 4, float2, double2>::type;
+__global__ void __launch_bounds__(kThreads) k_rho_rhs(const RhoArgs<T> a) {
   const Geo& g = a.g;
-  const int mem = blockIdx.y;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t plane = (int64_t)g.nb * g.nhp;
   const int lz = (int)(idx / plane);
   const int rem = (int)(idx - (int64_t)lz * plane);
   const int ly = rem / g.nhp, kx = rem - ly * g.nhp;
   if (idx >= g.sc || kx >= g.nh) return;
-  const int kz = lz <= g.K ? lz : lz - g.nb;
-  const int ky = ly <= g.K ? ly : ly - g.nb;
-  const int64_t ms = a.bt.mstride;
-  V2* const state = reinterpret_cast<V2*>(member_ptr(a.state, mem, ms));
-  const V2 mx = state[g.sc + idx], my = state[2 * g.sc + idx], mz = state[3 * g.sc + idx];
-  const T dx = T(kx) * mx.x + T(ky) * my.x + T(kz) * mz.x;
-  const T dy = T(kx) * mx.y + T(ky) * my.y + T(kz) * mz.y;
-  V2 R;
-  R.x = a.kinematic ? T(0) : dy;  // -i (dx + i dy); zero with the density frozen
-  R.y = a.kinematic ? T(0) : -dx;
-  if (a.rout) {
-    reinterpret_cast<V2*>(member_ptr(a.rout, mem, ms))[idx] = R;
-    return;
-  }
-  V2* const rprev = reinterpret_cast<V2*>(member_ptr(a.rprev, mem, ms));
-  const T dt = T(a.dt[mem]), ac = T(a.a_cur[mem]), ap = T(a.a_prev[mem]);
-  T ir = R.x * ac, ii = R.y * ac;
-  if (a.a_prev[mem] != 0.0) {
-    const V2 p = rprev[idx];
-    ir += p.x * ap;
-    ii += p.y * ap;
-  }
-  V2 u = state[idx];
-  u.x += dt * ir;
-  u.y += dt * ii;
-  state[idx] = u;
-  rprev[idx] = R;
+  rho_entry<T>(a, blockIdx.y, idx, kx, ly <= g.K ? ly : ly - g.nb, lz <= g.K ? lz : lz - g.nb);
 }
 
 // ABC body force of Section V-B in spectral form.  With f = F0 (sin z + cos y,
@@ -423,6 +392,8 @@ __global__ void __launch_bounds__(kThreads) k_moments(const T* __restrict__ d, i
   part[2 * r + 1] = s3 + c3;
 }
 
+// Spectral sums over the compact B^ (half spectrum: kx > 0 modes count twice):
+// sum Re(J^ . conj B^)/|k|^2, sum |i k.B^|^2, sum |J^|^2 with J^ = i k x B^.
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 k_spec_diag(const T* __restrict__ bx, const T* __restrict__ by, const T* __restrict__ bz, Geo g,
@@ -585,6 +556,8 @@ struct Layout {
   size_t tw, state, rprev, uhat, tstate, trhs, force, iz, iy, part, spart, status, res, hash, shpart, shres, total;
 };
 
+size_t n_fused_iy(int n) { return n <= kSlabMax ? 4 : 0; }
+
 Layout make_layout(const Geo& g, size_t tsize) {
   Layout L;
   size_t off = 0;
@@ -597,7 +570,8 @@ Layout make_layout(const Geo& g, size_t tsize) {
   L.tstate = take(8 * (size_t)g.sc * cplx);
   L.trhs = take(8 * (size_t)g.sc * cplx);
   L.force = take(4 * (size_t)g.sc * cplx);
-  L.iz = take(12 * (size_t)g.iz * cplx);
+  // twelve I_z slots, or the four I_y slots the fused passes keep u and q in
+  L.iz = take(std::max(12 * (size_t)g.iz, n_fused_iy(g.n) * (size_t)g.iy) * cplx);
   L.iy = take(16 * (size_t)g.iy * cplx);
   const size_t rows = (size_t)g.n * g.n / 2;
   const size_t spec_blocks = (size_t)((g.sc + kThreads - 1) / kThreads);
@@ -863,6 +837,28 @@ struct Engine {
 
   double inv_n3() const { return 1.0 / (double)g.n3; }
 
+  // Inverse z and y passes into the I_y slots 0, 1, ...
+  void inverse_zy(int nout, const T* const* ins, int nin, const OutSpec* specs) {
+    if (k.zyinv) {
+      ColArgs<T> a = col_args(PK_ZINV, nout);
+      for (int i = 0; i < nin; ++i) a.in[i] = ins[i];
+      for (int f = 0; f < nout; ++f) {
+        a.out[f] = iy(f);
+        a.spec[f] = specs[f];
+      }
+      k.zyinv(a, ms.n, c->stream);
+      return;
+    }
+    T* zo[kMaxOut];
+    T* yo[kMaxOut];
+    for (int f = 0; f < nout; ++f) {
+      zo[f] = iz(f);
+      yo[f] = iy(f);
+    }
+    col(PK_ZINV, nout, ins, nin, zo, specs);
+    y_copy(PK_YINV, nout, zo, yo);
+  }
+
   // Real fields [nf][n^3] (dtype) -> compact spectra D F[f] at dst.
   void forward_real(const void* real, int dtype, int nf, T* dst) {
     RowArgs<T> r = row_args();
@@ -871,6 +867,12 @@ struct Engine {
     r.nf = nf;
     set_out(r, 0);
     k.row(RM_XFWD_REAL, r, row_grid(RM_XFWD_REAL), c->stream);
+    if (k.yzfwd) {
+      ColArgs<T> a = col_args(PK_ZFWD, nf);
+      for (int f = 0; f < nf; ++f) { a.in[f] = iy(f); a.out[f] = spec_field(dst, f); }
+      k.yzfwd(a, ms.n, c->stream);
+      return;
+    }
     T* yi[kMaxOut];
     T* yo[kMaxOut];
     for (int f = 0; f < nf; ++f) { yi[f] = iy(f); yo[f] = iz(f); }
@@ -885,17 +887,12 @@ struct Engine {
   // Compact spectra at src (nf fields) -> real fields [nf][n^3] (dtype).
   void inverse_real(const T* src, int nf, void* real, int dtype) {
     const T* zi[kMaxIn];
-    T* zo[kMaxOut];
     OutSpec sp[kMaxOut];
     for (int f = 0; f < nf; ++f) {
       zi[f] = src + 2 * (size_t)f * g.sc;
-      zo[f] = iz(f);
       sp[f] = copy_spec(f, inv_n3());
     }
-    col(PK_ZINV, nf, zi, nf, zo, sp);
-    T* yo[kMaxOut];
-    for (int f = 0; f < nf; ++f) yo[f] = iy(f);
-    y_copy(PK_YINV, nf, zo, yo);
+    inverse_zy(nf, zi, nf, sp);
     RowArgs<T> r = row_args();
     r.real_out = real;
     r.real_dtype = dtype == MHD_FP64 ? 0 : 1;
@@ -939,15 +936,51 @@ struct Engine {
   // ms.a_prev.  record_status: fold the flux pass's CFL speed and
   // non-finite count into the status slots (steps do; pure right-hand sides
   // and the later stages of a multistage step do not).
-  void phase_b(T* U, T* rout) { phase_b(U, rout, rout == nullptr); }
   void phase_b(T* U, T* rout, bool record_status) {
     const double s = inv_n3();
     // inputs: 0-2 B^, 3 E^, 4-6 u^
     const T* zi[7] = {spec_field(U, 4), spec_field(U, 5), spec_field(U, 6), spec_field(U, 7),
                       spec_field(uhat(), 0), spec_field(uhat(), 1), spec_field(uhat(), 2)};
+    OutSpec sp[12];
+    flux_input_specs(sp);
+    T* zo[12];
+    for (int f = 0; f < 12; ++f) zo[f] = iz(f);
+    timed(MHD_PASS_ZINV_B, [&] { col(PK_ZINV, 12, zi, 7, zo, sp); });
+    T* yo[12];
+    for (int f = 0; f < 12; ++f) yo[f] = iy(4 + f);
+    timed(MHD_PASS_YINV_B, [&] { y_copy(PK_YINV, 12, zo, yo); });
+    const RowArgs<T> r = flux_args(record_status);
+    timed(MHD_PASS_XB, [&] { k.row(RM_XB, r, row_grid(RM_XB), c->stream); });
+    T* fi[12];
+    T* fo[12];
+    for (int f = 0; f < 12; ++f) { fi[f] = iy(f); fo[f] = iz(f); }
+    timed(MHD_PASS_YFWD_B, [&] { y_copy(PK_YFWD, 12, fi, fo); });
+    RhsArgs<T> q = rhs_args(U, rout);
+    for (int f = 0; f < 12; ++f) q.flux[f] = iz(f);
+    const RhoArgs<T> ra = rho_args(U, rout);
+    const unsigned sblocks = (unsigned)((g.sc + kThreads - 1) / kThreads);
+    timed(MHD_PASS_RHO, [&] {
+      launch_force(U);
+      hipLaunchKernelGGL((k_rho_rhs<T>), dim3(sblocks, (unsigned)ms.n), dim3(kThreads), 0, c->stream, ra);
+    });
+    timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * 7 * ms.n)), c->stream); });
+  }
+
+  // The body force's spectra, from rho^ and m^ of this step before either is
+  // updated.
+  void launch_force(const T* U) {
+    if (c->p.force == 0.0) return;
+    const unsigned sblocks = (unsigned)((g.sc + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL((k_force_abc<T>), dim3(sblocks), dim3(kThreads), 0, c->stream, U, force(), g, c->p.force);
+  }
+
+  // Spectra of the twelve flux-pass inputs that phase B synthesises: B, E, S, J
+  // from the sources 0-2 B^, 3 E^, 4-6 u^.
+  void flux_input_specs(OutSpec* out) const {
+    const double s = inv_n3();
     enum { X = 0, Y = 1, Z = 2 };
     const double t3 = s / 3.0, h = 0.5 * s;
-    OutSpec sp[12] = {
+    const OutSpec sp[12] = {
         copy_spec(0, s), copy_spec(1, s), copy_spec(2, s), copy_spec(3, s),
         // traceless strain (Eqs. 3-4): S_ij = (d_i u_j + d_j u_i)/2 - delta_ij div u / 3
         spec({term(4, X, 2 * t3), term(5, Y, -t3), term(6, Z, -t3)}),  // S_xx
@@ -960,26 +993,42 @@ struct Engine {
         spec({term(0, Z, s), term(2, X, -s)}),  // J_y
         spec({term(1, X, s), term(0, Y, -s)}),  // J_z
     };
-    T* zo[12];
-    for (int f = 0; f < 12; ++f) zo[f] = iz(f);
-    timed(MHD_PASS_ZINV_B, [&] { col(PK_ZINV, 12, zi, 7, zo, sp); });
-    T* yo[12];
-    for (int f = 0; f < 12; ++f) yo[f] = iy(4 + f);
-    timed(MHD_PASS_YINV_B, [&] { y_copy(PK_YINV, 12, zo, yo); });
+    for (int f = 0; f < 12; ++f) out[f] = sp[f];
+  }
+
+  // Flux pass over the I_y slots 0-15, its outputs into slots 0-11.
+  RowArgs<T> flux_args(bool record_status) const {
     RowArgs<T> r = row_args();
     set_in(r, 0);
     set_out(r, 0);
     if (c->p.flags & MHD_FLAG_VISC_LAPLACIAN)
       for (int m = 0; m < ms.n; ++m) r.nu[m] = 0.0;  // no stress-form terms: the force is added spectrally
     r.status = record_status ? status() : nullptr;
-    timed(MHD_PASS_XB, [&] { k.row(RM_XB, r, row_grid(RM_XB), c->stream); });
-    T* fi[12];
-    T* fo[12];
-    for (int f = 0; f < 12; ++f) { fi[f] = iy(f); fo[f] = iz(f); }
-    timed(MHD_PASS_YFWD_B, [&] { y_copy(PK_YFWD, 12, fi, fo); });
+    return r;
+  }
+
+  RhoArgs<T> rho_args(T* U, T* rout) const {
+    RhoArgs<T> a;
+    std::memset(&a, 0, sizeof(a));
+    a.state = U;
+    a.rprev = rprev();
+    a.rout = rout;
+    a.kinematic = (c->p.flags & MHD_FLAG_KINEMATIC) ? 1 : 0;
+    a.g = g;
+    a.bt = batch();
+    for (int m = 0; m < ms.n; ++m) {
+      a.dt[m] = ms.dt[m];
+      a.a_cur[m] = ms.a_cur[m];
+      a.a_prev[m] = ms.a_prev[m];
+    }
+    return a;
+  }
+
+  // Arguments of the last pass of a right-hand side (flux pointers left to the caller).
+  RhsArgs<T> rhs_args(T* U, T* rout) const {
+    enum { X = 0, Y = 1, Z = 2 };
     RhsArgs<T> q;
     std::memset(&q, 0, sizeof(q));
-    for (int f = 0; f < 12; ++f) q.flux[f] = iz(f);
     // flux slots: 0 Pi_xx, 1 Pi_yy, 2 Pi_zz, 3 Pi_xy, 4 Pi_xz, 5 Pi_yz, 6-8 F^E, 9-11 e = u x B
     // R_f = F_z[A_f] + i kz F_z[Z_f]
     q.A[1] = spec({term(0, X, -1), term(3, Y, -1)});  // MHD2: -i k_j Pi_xj
@@ -1011,15 +1060,65 @@ struct Engine {
     }
     q.g = g;
     q.bt = batch();
-    const unsigned sblocks = (unsigned)((g.sc + kThreads - 1) / kThreads);
-    timed(MHD_PASS_RHO, [&] {
-      // the body force reads rho^ and m^ of this step before either is updated
-      if (q.force)
-        hipLaunchKernelGGL((k_force_abc<T>), dim3(sblocks), dim3(kThreads), 0, c->stream, U, force(), g,
-                           c->p.force);
-      hipLaunchKernelGGL((k_rho_rhs<T>), dim3(sblocks, (unsigned)ms.n), dim3(kThreads), 0, c->stream, q);
-    });
-    timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * 7 * ms.n)), c->stream); });
+    return q;
+  }
+
+  // One right-hand side of state U and its update (or the store into rout).
+  // record_status as for phase_b.  Small grids run the fused passes; while
+  // mhd_profile records, every launch class runs by itself.
+  void evaluate(T* U, T* rout) { evaluate(U, rout, rout == nullptr); }
+  void evaluate(T* U, T* rout, bool record_status) {
+    if (!k.zyinv || c->prof_on) {
+      phase_a(U);
+      phase_b(U, rout, record_status);
+      return;
+    }
+    // rho, m, B, E and J (the strains, slots 8-12, follow from u)
+    OutSpec sp[12];
+    flux_input_specs(sp);
+    ColArgs<T> a = col_args(PK_ZINV, 11);
+    for (int f = 0; f < 4; ++f) {
+      a.in[f] = spec_field(U, 4 + f);  // B^, E^
+      a.in[4 + f] = spec_field(U, f);  // rho^, m^
+    }
+    for (int f = 0; f < 4; ++f) {
+      a.out[f] = iy(f);
+      a.spec[f] = copy_spec(4 + f, inv_n3());
+      a.out[4 + f] = iy(4 + f);
+      a.spec[4 + f] = sp[f];
+    }
+    for (int f = 0; f < 3; ++f) {
+      a.out[8 + f] = iy(13 + f);
+      a.spec[8 + f] = sp[9 + f];
+    }
+    k.zyinv(a, ms.n, c->stream);
+    // u (and q) into the I_z slots, which the fused passes leave free, as I_y fields
+    RowArgs<T> ra = row_args();
+    set_in(ra, 0);
+    ra.out0 = iz(0);
+    ra.out_stride = g.iy;
+    ra.nf = na();
+    k.row(RM_XA, ra, row_grid(RM_XA), c->stream);
+    launch_force(U);
+    a = col_args(PK_ZINV, 5);
+    for (int f = 0; f < 3; ++f) a.in[4 + f] = iz(0) + 2 * (size_t)f * g.iy;
+    for (int f = 0; f < 5; ++f) {
+      a.out[f] = iy(8 + f);
+      a.spec[f] = sp[4 + f];
+    }
+    k.strain_rho(a, rho_args(U, rout), ms.n, c->stream);
+    if (na() == 4) {  // the viscous-force variant needs u^ and q^ themselves
+      a = col_args(PK_ZFWD, 4);
+      for (int f = 0; f < 4; ++f) {
+        a.in[f] = iz(0) + 2 * (size_t)f * g.iy;
+        a.out[f] = spec_field(uhat(), f);
+      }
+      k.yzfwd(a, ms.n, c->stream);
+    }
+    k.row(RM_XB, flux_args(record_status), row_grid(RM_XB), c->stream);
+    RhsArgs<T> q = rhs_args(U, rout);
+    for (int f = 0; f < 12; ++f) q.flux[f] = iy(f);
+    k.yzrhs(q, ms.n, c->stream);
   }
 
   double step_bytes() const {
@@ -1046,30 +1145,25 @@ struct Engine {
   void step_once(bool first) {
     const double dt = c->p.dt;
     if (c->p.scheme == MHD_RK4) {
-      phase_a(state());
-      phase_b(state(), trhs(), true);
+      evaluate(state(), trhs(), true);
       combine(CB_RK_FIRST, 0.5 * dt, 0.0);
       const double cs[3] = {0.5 * dt, dt, dt / 6.0};
       for (int st = 0; st < 3; ++st) {
-        phase_a(tstate());
-        phase_b(tstate(), trhs(), false);
+        evaluate(tstate(), trhs(), false);
         combine(st < 2 ? CB_RK_MID : CB_RK_LAST, cs[st], st < 2 ? 2.0 : 1.0);
       }
       return;
     }
     if (c->p.scheme == MHD_PC) {
-      phase_a(state());
-      phase_b(state(), trhs(), true);
+      evaluate(state(), trhs(), true);
       combine(CB_PC_PRED, dt, 0.0, first ? 1.0 : 1.5, first ? 0.0 : -0.5);
-      phase_a(tstate());
-      phase_b(tstate(), trhs(), false);
+      evaluate(tstate(), trhs(), false);
       combine(CB_PC_CORR, 0.5 * dt, 0.0);
       return;
     }
     ms.a_cur[0] = first ? 1.0 : 1.5;
     ms.a_prev[0] = first ? 0.0 : -0.5;
-    phase_a(state());
-    phase_b(state(), nullptr);
+    evaluate(state(), nullptr);
   }
 
   void reset_status() {
@@ -1089,12 +1183,7 @@ struct Engine {
     OutSpec sp[NF];
     for (int f = 0; f < 8; ++f) sp[f] = copy_spec(f, s);
     sp[8] = spec({term(4, X, s), term(5, Y, s), term(6, Z, s)});  // div B
-    T* zo[NF];
-    for (int f = 0; f < NF; ++f) zo[f] = iz(f);
-    col(PK_ZINV, NF, zi, 8, zo, sp);
-    T* yo[NF];
-    for (int f = 0; f < NF; ++f) yo[f] = iy(f);
-    y_copy(PK_YINV, NF, zo, yo);
+    inverse_zy(NF, zi, 8, sp);
     RowArgs<T> r = row_args();
     set_in(r, 0);
     r.partials = part();
@@ -1463,8 +1552,7 @@ void group_launch(mhd_ens* E, EnsGroup& G, const Kern<T>& k, bool rhs_only) {
     ms.a_prev[s] = mc->first_step ? 0.0 : -0.5;
   }
   Engine<T> e(G.lead, k, ms);
-  e.phase_a(e.state());
-  e.phase_b(e.state(), rhs_only ? e.trhs() : nullptr);
+  e.evaluate(e.state(), rhs_only ? e.trhs() : nullptr);
 }
 
 // Every group as a parallel branch forked from and joined into `origin` (the
@@ -1721,8 +1809,7 @@ int mhd_rhs(mhd_ctx* c, const void* d_in, void* d_out, int32_t dtype) {
   if (!c || !d_in || !d_out || !dtype_ok(dtype)) return MHD_E_ARG;
   return with_engine(c, [&](auto& e) {
     e.forward_real(d_in, dtype, 8, e.tstate());
-    e.phase_a(e.tstate());
-    e.phase_b(e.tstate(), e.trhs());
+    e.evaluate(e.tstate(), e.trhs());
     e.inverse_real(e.trhs(), 8, d_out, dtype);
     return check_launch(c, "mhd_rhs");
   });
@@ -1883,11 +1970,8 @@ int mhd_spectra(mhd_ctx* c, double* h_eu, double* h_eb, double* h_mom) {
                        shpart, (int64_t)0, 0, shres, shres);
     // d = du_x/dx = F^-1[i k_x u^_x] on the grid, then its second and third moments
     const T* zi[1] = {e.uhat()};
-    T* zo[1] = {e.iz(0)};
     OutSpec sp[1] = {spec({term(0, 0, e.inv_n3())})};
-    e.col(PK_ZINV, 1, zi, 1, zo, sp);
-    T* yo[1] = {e.iy(0)};
-    e.y_copy(PK_YINV, 1, zo, yo);
+    e.inverse_zy(1, zi, 1, sp);
     RowArgs<T> r = e.row_args();
     T* real = e.iy(4);
     r.real_out = real;

@@ -2,6 +2,7 @@
 // (FP64 only up to N = 512, where the row pass's LDS footprint still fits).
 #include "mhd_kernels.h"
 #include "mhd_registry.h"
+#include "mhd_slab.h"
 
 #ifndef MHD_N
 #error "compile with -DMHD_N=<grid size>"
@@ -52,6 +53,26 @@ void rhs(const RhsArgs<T>& a, dim3 g, hipStream_t s) {
   hipLaunchKernelGGL((k_zfwd_rhs<T, N, MX>), g, dim3(rhs_threads<T, N, MX>()), 0, s, a);
 }
 template <typename T, int N, bool MX>
+void zyinv(const ColArgs<T>& a, int nmem, hipStream_t s) {
+  hipLaunchKernelGGL((k_zyinv<T, N, MX>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
+                     dim3(slab_threads<T, N, MX>()), 0, s, a);
+}
+template <typename T, int N, bool MX>
+void yzfwd(const ColArgs<T>& a, int nmem, hipStream_t s) {
+  hipLaunchKernelGGL((k_yzfwd<T, N, MX>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
+                     dim3(slab_threads<T, N, MX>()), 0, s, a);
+}
+template <typename T, int N, bool MX>
+void strain_rho(const ColArgs<T>& a, const RhoArgs<T>& q, int nmem, hipStream_t s) {
+  hipLaunchKernelGGL((k_strain_rho<T, N, MX>), dim3((unsigned)(nmem * (a.nout + 1) * Band<N>::NH)),
+                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, q);
+}
+template <typename T, int N, bool MX>
+void yzrhs(const RhsArgs<T>& a, int nmem, hipStream_t s) {
+  hipLaunchKernelGGL((k_yzrhs<T, N, MX>), dim3((unsigned)(nmem * 7 * Band<N>::NH)),
+                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a);
+}
+template <typename T, int N, bool MX>
 void row(int mode, const RowArgs<T>& a, dim3 g, hipStream_t s) {
   switch (mode) {
     case RM_XA: hipLaunchKernelGGL((k_row<T, N, RM_XA, MX>), g, dim3(row_threads<T, N, RM_XA, MX>()), 0, s, a); break;
@@ -96,6 +117,12 @@ Kern<T> make() {
   k.col_inv = col_inv<T, N, MX>;
   k.col_fwd = col_fwd<T, N, MX>;
   k.rhs = rhs<T, N, MX>;
+  if constexpr (N <= kSlabMax && MHD_SCHED == 0) {
+    k.zyinv = zyinv<T, N, MX>;
+    k.yzfwd = yzfwd<T, N, MX>;
+    k.strain_rho = strain_rho<T, N, MX>;
+    k.yzrhs = yzrhs<T, N, MX>;
+  }
   k.row = row<T, N, MX>;
   k.row_occupancy = row_occupancy<T, N, MX>;
   k.col_class = col_class<T, N, MX>;

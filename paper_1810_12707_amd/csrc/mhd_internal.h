@@ -34,6 +34,7 @@
 
 namespace mhd {
 
+constexpr int kSlabMax = 32;     // largest grid whose z and y passes run fused
 constexpr int kLineBytes = 128;  // memory line the intermediates' rows and planes are padded to
 constexpr int kThreads = 256;  // threads per workgroup of every pass kernel
 constexpr int kMaxTerms = 3;   // terms of one spectral linear combination
@@ -112,8 +113,7 @@ struct ColArgs {
 // Forward-z pass that forms the right-hand side (Eqs. MHD2-MHD4 in spectral
 // form) and applies the AB2 update.  Output f = 1..7 is
 //   R_f = F_z[A_f] + i kz F_z[Z_f] - eta |k|^2 B^_f (f = 4, 5, 6),
-// with A_f, Z_f combinations of the y-transformed fluxes.  The density pass
-// (Eq. MHD1, R_rho = -i k.m^) takes the same arguments.
+// with A_f, Z_f combinations of the y-transformed fluxes.
 template <typename T>
 struct RhsArgs {
   const T* flux[kMaxIn];  // I_z flux slots
@@ -136,6 +136,19 @@ struct RhsArgs {
   Batch bt;
   // per member: time step, AB2 coefficients of R^n and R^{n-1}, diffusivity
   double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem], eta[kMaxMem];
+};
+
+// Density right-hand side and update (Eq. MHD1); fields as in RhsArgs.
+template <typename T>
+struct RhoArgs {
+  T* state;
+  T* rprev;
+  T* rout;
+  int32_t kinematic;
+  int32_t pad;
+  Geo g;
+  Batch bt;
+  double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem];
 };
 
 enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4 };

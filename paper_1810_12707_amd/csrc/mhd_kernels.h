@@ -305,18 +305,14 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(c
             const cx<T> xv = px[t][i][r];
             if constexpr (MAXT > 1 || MX) {
               const T ck = dk[t] * T(ax[t] == 1 ? kyy : (ax[t] == 2 ? kz : kx));
-              acc.x += re[t] * xv.x;
-              acc.x -= ck * xv.y;
-              acc.y += re[t] * xv.y;
-              acc.y += ck * xv.x;
+              acc.x = fma_(-ck, xv.y, fma_(re[t], xv.x, acc.x));
+              acc.y = fma_(ck, xv.x, fma_(re[t], xv.y, acc.y));
             } else if (t < nt) {
               if (ax[t] < 0) {
-                acc.x += re[t] * xv.x;
-                acc.y += re[t] * xv.y;
+                acc = cfma(re[t], xv, acc);
               } else {
                 const T ck = dk[t] * T(ax[t] == 0 ? kx : (ax[t] == 1 ? kyy : kz));
-                acc.x -= ck * xv.y;
-                acc.y += ck * xv.x;
+                acc = cfma(ck, ctimes_i(xv), acc);
               }
             }
           }
@@ -356,6 +352,80 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(c
   }
 }
 
+// ------------------------------------------------------------------ right-hand-side epilogue
+// Field f (1..7) of one member in the last pass of a right-hand side: the
+// resistive term, the Section V variants, and the AB2 update
+// U += dt (a_cur R^n + a_prev R^{n-1}), R^{n-1} <- R^n, or the store of R into
+// rout.  off: entry of the compact spectrum.
+template <typename T> struct RhsMember {
+  const RhsArgs<T>& a;
+  int f;
+  T *state, *rprev, *rout;  // field f
+  const T *uhat, *force;    // the entries that belong to field f
+  T dt, ac, ap, eta;
+  bool use_prev, need_state, need_prev, induction;
+  __device__ __forceinline__ RhsMember(const RhsArgs<T>& args, int mem, int fld) : a(args), f(fld) {
+    const int64_t ms = a.bt.mstride, sc = a.g.sc;
+    const int vslot = f <= 3 ? f - 1 : 3;  // u^_{f-1} for the momentum, q^ for the energy
+    state = member_ptr(a.state, mem, ms) + 2 * f * sc;
+    rprev = member_ptr(a.rprev, mem, ms) + 2 * f * sc;
+    rout = a.rout ? member_ptr(a.rout, mem, ms) + 2 * f * sc : nullptr;
+    uhat = member_ptr(a.uhat, mem, ms) + 2 * vslot * sc;
+    force = a.force ? member_ptr(a.force, mem, ms) + 2 * vslot * sc : nullptr;
+    dt = T(a.dt[mem]);
+    ac = T(a.a_cur[mem]);
+    ap = T(a.a_prev[mem]);
+    eta = T(a.eta[mem]);
+    use_prev = a.a_prev[mem] != 0.0;
+    induction = f >= 4 && f <= 6;
+    need_state = !rout || induction;
+    need_prev = !rout && use_prev;
+  }
+  __device__ __forceinline__ cx<T> old_state(int64_t off) const { return need_state ? ld(state, off) : mk<T>(0, 0); }
+  __device__ __forceinline__ cx<T> old_rhs(int64_t off) const { return need_prev ? ld(rprev, off) : mk<T>(0, 0); }
+  __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u, cx<T> rp, int kx, int ky, int kz) const {
+    const T k2 = T(kx * kx + ky * ky + kz * kz);
+    if (induction) {
+      // MHD4 resistive term: - eta |k|^2 B^
+      R = cfma(-(eta * k2), u, R);
+    } else {
+      // viscous force mu lap u, and mu lap(|u|^2/2) in the energy
+      if (a.mu != 0.0) R = cfma(-(T(a.mu) * k2), ld(uhat, off), R);
+      if (a.force) R = cadd(R, ld(force, off));
+      if (a.kinematic) R = mk<T>(0, 0);  // frozen rho u and E
+    }
+    if (rout) {
+      st(rout, off, R);
+    } else {
+      cx<T> inc = cscale(R, ac);
+      if (use_prev) inc = cfma(ap, rp, inc);
+      st(state, off, cfma(dt, inc, u));
+      st(rprev, off, R);
+    }
+  }
+};
+
+// One entry of Eq. MHD1 in spectral form, R_rho = -i k . m^, with the density's
+// AB2 update U_rho += dt (a_cur R + a_prev R_prev), R_prev <- R, or the store of
+// R into rout.
+template <typename T>
+__device__ __forceinline__ void rho_entry(const RhoArgs<T>& a, int mem, int64_t idx, int kx, int ky, int kz) {
+  const int64_t ms = a.bt.mstride, sc = a.g.sc;
+  T* const state = member_ptr(a.state, mem, ms);
+  const cx<T> mx = ld(state, sc + idx), my = ld(state, 2 * sc + idx), mz = ld(state, 3 * sc + idx);
+  const cx<T> d = cfma(T(kz), mz, cfma(T(ky), my, cscale(mx, T(kx))));
+  const cx<T> R = a.kinematic ? mk<T>(0, 0) : ctimes_mi(d);  // zero with the density frozen
+  if (a.rout) {
+    st(member_ptr(a.rout, mem, ms), idx, R);
+    return;
+  }
+  T* const rprev = member_ptr(a.rprev, mem, ms);
+  cx<T> inc = cscale(R, T(a.a_cur[mem]));
+  if (a.a_prev[mem] != 0.0) inc = cfma(T(a.a_prev[mem]), ld(rprev, idx), inc);
+  st(state, idx, cfma(T(a.dt[mem]), inc, ld(state, idx)));
+  st(rprev, idx, R);
+}
+
 // ------------------------------------------------------------------ k_zfwd_rhs
 // Flat grid over (member, column tile of (ky, kx), output field f = 1..7),
 // field fastest.
@@ -377,15 +447,10 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
   constexpr int ZT = (NCOLS + C - 1) / C;  // column tiles per member
   const int mem = tf.tile / ZT;
   const int c0 = (tf.tile - mem * ZT) * C;
-  const int64_t sc = a.g.sc;
   constexpr int64_t LS = NCOLS;             // plane stride of a compact spectrum (kz)
   constexpr int64_t LSZ = Pitch<T, N>::Z;  // plane stride of I_z (z)
-  const T dt = T(a.dt[mem]), ac = T(a.a_cur[mem]), ap = T(a.a_prev[mem]);
-  const bool use_prev = a.a_prev[mem] != 0.0;
   const int64_t ms = a.bt.mstride;
-  T* const state = member_ptr(a.state, mem, ms);
-  T* const rprev = member_ptr(a.rprev, mem, ms);
-  T* const rout = a.rout ? member_ptr(a.rout, mem, ms) : nullptr;
+  const RhsMember<T> M(a, mem, f);
 
   // Output (i, r) of this thread's last-pass slots: compact index, or -1 for
   // a slot that is idle, a padding column or a dealiased kz.
@@ -399,7 +464,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
     const int l = pos_band<N>(q);
     if (l < 0) return -1;
     kz = band_k<N>(l);
-    return f * sc + (int64_t)l * LS + col;
+    return (int64_t)l * LS + col;
   };
   // The state (for the update, and B^ for the resistive term) and the
   // previous RHS: FP32 from N = 512 loads them before the transforms, so that
@@ -410,8 +475,6 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
   // 0.458 -> 0.372 ms at 256, 3.35 -> 2.59 ms at 512) and the narrow shapes
   // load them last.
   constexpr bool PRE = rhs_wide<T, N, MX>() && !MX && N >= 512;
-  const bool need_state = !rout || (f >= 4 && f <= 6);
-  const bool need_prev = !rout && use_prev;
   cx<T> u_pre[LP::CNT][LP::R], r_pre[LP::CNT][LP::R];
   auto load_old = [&](int i, int r) {
     u_pre[i][r] = mk<T>(0, 0);
@@ -419,29 +482,16 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
     int kx, ky, kz;
     const int64_t idx = out_index(i, r, kx, ky, kz);
     if (idx < 0) return;
-    if (need_state) u_pre[i][r] = ld(state, idx);
-    if (need_prev) r_pre[i][r] = ld(rprev, idx);
+    u_pre[i][r] = M.old_state(idx);
+    r_pre[i][r] = M.old_rhs(idx);
   };
-  if constexpr (PRE) {
+  auto load_all_old = [&] {
 #pragma unroll
     for (int i = 0; i < LP::CNT; ++i)
 #pragma unroll
       for (int r = 0; r < LP::R; ++r) load_old(i, r);
-  }
-
-  // R_f -> store, or the AB2 update U += dt (a_cur R^n + a_prev R^{n-1}), R^{n-1} <- R^n
-  auto finish = [&](int64_t idx, cx<T> R, cx<T> u, cx<T> rp) {
-    if (rout) {
-      st(rout, idx, R);
-    } else {
-      cx<T> inc = cscale(R, ac);
-      if (use_prev) inc = cadd(inc, cscale(rp, ap));
-      u.x += dt * inc.x;
-      u.y += dt * inc.y;
-      st(state, idx, u);
-      st(rprev, idx, R);
-    }
   };
+  if constexpr (PRE) load_all_old();
 
   load_twiddles<T, PL, NT>(stw, a.tw, tid);
   cx<T> acc[LP::CNT][LP::R];
@@ -482,18 +532,13 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
           // only): absent terms have zero factors and a zero second input
           const T re = ax[t] < 0 ? cf[t] : T(0);
           const T ck = (ax[t] < 0 ? T(0) : cf[t]) * T(ax[t] == 1 ? ky : kx);
-          v.x += re * xs[t].x;
-          v.x -= ck * xs[t].y;
-          v.y += re * xs[t].y;
-          v.y += ck * xs[t].x;
+          v = cfma(ck, ctimes_i(xs[t]), cfma(re, xs[t], v));
         } else if (t < nt) {
           if (ax[t] < 0) {
-            v.x += cf[t] * xs[t].x;
-            v.y += cf[t] * xs[t].y;
+            v = cfma(cf[t], xs[t], v);
           } else {
             const T ck = cf[t] * T(ax[t] == 0 ? kx : ky);
-            v.x -= ck * xs[t].y;
-            v.y += ck * xs[t].x;
+            v = cfma(ck, ctimes_i(xs[t]), v);
           }
         }
       }
@@ -505,17 +550,14 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
       } else {  // + i kz v
         const int l = pos_band<N>(q);
         const T kz = T(l < 0 ? 0 : band_k<N>(l));
-        acc[i][r].x -= kz * v.y;
-        acc[i][r].y += kz * v.x;
+        acc[i][r] = cfma(kz, ctimes_i(v), acc[i][r]);
       }
     };
     fft_reg<T, PL, C, NT, C, 1, -1, 0, 0, true>(tile, stw, tid, C, load, store);
   }
-  // epilogue over this thread's last-pass positions: resistive term, the
-  // Section V variants (block-uniform branches), update
-  const T eta = T(a.eta[mem]);
-  const bool induction = f >= 4 && f <= 6;
-  const int vslot = f <= 3 ? f - 1 : 3;  // u^_{f-1} for the momentum, q^ for the energy
+  // epilogue over this thread's last-pass positions; all its loads go out
+  // together, ahead of the first that is used
+  if constexpr (!PRE) load_all_old();
 #pragma unroll
   for (int i = 0; i < LP::CNT; ++i) {
 #pragma unroll
@@ -523,26 +565,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
       int kx, ky, kz;
       const int64_t idx = out_index(i, r, kx, ky, kz);
       if (idx < 0) continue;
-      if constexpr (!PRE) load_old(i, r);
-      cx<T> R = acc[i][r];
-      const T k2 = T(kx * kx + ky * ky + kz * kz);
-      if (induction) {
-        // MHD4 resistive term: - eta |k|^2 B^
-        const cx<T> b = u_pre[i][r];
-        R.x -= eta * k2 * b.x;
-        R.y -= eta * k2 * b.y;
-      } else {
-        const int64_t off = idx - f * sc;  // position inside one compact field
-        if (a.mu != 0.0) {
-          // viscous force mu lap u, and mu lap(|u|^2/2) in the energy
-          const cx<T> v = ld(member_ptr(a.uhat, mem, ms), vslot * sc + off);
-          R.x -= T(a.mu) * k2 * v.x;
-          R.y -= T(a.mu) * k2 * v.y;
-        }
-        if (a.force) R = cadd(R, ld(member_ptr(a.force, mem, ms), vslot * sc + off));
-        if (a.kinematic) R = mk<T>(0, 0);  // frozen rho u and E
-      }
-      finish(idx, R, u_pre[i][r], r_pre[i][r]);
+      M.apply(idx, acc[i][r], u_pre[i][r], r_pre[i][r], kx, ky, kz);
     }
   }
 }

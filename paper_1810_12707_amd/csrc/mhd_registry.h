@@ -22,6 +22,12 @@ struct Kern {
   void (*col_fwd)(const ColArgs<T>&, dim3, hipStream_t) = nullptr;
   ColClass (*col_class)(int dir, int maxt, bool z) = nullptr;
   void (*rhs)(const RhsArgs<T>&, dim3, hipStream_t) = nullptr;
+  // fused z and y passes of the small grids (null where the grid is not one); the
+  // grids count one workgroup per (member, field, kx)
+  void (*zyinv)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
+  void (*yzfwd)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
+  void (*strain_rho)(const ColArgs<T>&, const RhoArgs<T>&, int nmem, hipStream_t) = nullptr;
+  void (*yzrhs)(const RhsArgs<T>&, int nmem, hipStream_t) = nullptr;
   void (*row)(int mode, const RowArgs<T>&, dim3, hipStream_t) = nullptr;
   // resident workgroups per CU of a row-pass mode (persistent grid sizing)
   int (*row_occupancy)(int mode) = nullptr;
