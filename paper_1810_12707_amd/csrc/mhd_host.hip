@@ -112,6 +112,15 @@ __global__ void __launch_bounds__(kThreads) k_rho_rhs(const RhoArgs<T> a) {
   rho_entry<T>(a, blockIdx.y, idx, kx, ly <= g.K ? ly : ly - g.nb, lz <= g.K ? lz : lz - g.nb);
 }
 
+// The frozen fields of a kinematic run (frozen_entry), one thread per compact
+// entry of frozen field blockIdx.y of member blockIdx.z.
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_frozen(const RhoArgs<T> a) {
+  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (idx >= a.g.sc || (int)(idx % a.g.nhp) >= a.g.nh) return;
+  frozen_entry<T>(a, blockIdx.z, blockIdx.y, idx);
+}
+
 // ABC body force of Section V-B in spectral form.  With f = F0 (sin z + cos y,
 // sin x + cos z, sin y + cos x), the product of a band-limited field g with
 // one term is a shift of its spectrum: F[g sin z](k) = (g^(k - e_z) -
@@ -601,7 +610,7 @@ struct mhd_ctx {
   int64_t step;
   double t;
   int num_cus = 0;
-  int row_blocks[5] = {0, 0, 0, 0, 0};  // resident workgroups of each row-pass mode
+  int row_blocks[kRowModes] = {};  // resident workgroups of each row-pass mode
   ColClass col_class[3][2];             // column passes: forward, inverse (1 term), inverse (3 terms); y, z
   std::string last_err;
   // benchmark timing (mhd_profile)
@@ -709,6 +718,17 @@ struct Engine {
   double class_bytes(int cls) const {
     const double a4 = (c->p.flags & MHD_FLAG_VISC_LAPLACIAN) ? 1 : 0;  // q = |u|^2/2 beside u
     const double fo = c->p.force != 0.0 ? 4 : 0;                       // body-force spectra
+    if (kinematic()) {
+      switch (cls) {
+        case MHD_PASS_ZINV_B: return cbytes(8, 8, 0);
+        case MHD_PASS_YINV_B: return cbytes(0, 8, 8);
+        case MHD_PASS_XB: return cbytes(0, 0, 11);
+        case MHD_PASS_YFWD_B: return cbytes(0, 3, 3);
+        case MHD_PASS_RHO: return cbytes(kFrozenFields, 0, 0);
+        case MHD_PASS_ZRHS: return cbytes(12, 3, 0);
+        default: return 0.0;
+      }
+    }
     switch (cls) {
       case MHD_PASS_ZINV_A: return cbytes(4, 4, 0);
       case MHD_PASS_YINV_A: return cbytes(0, 4, 4);
@@ -963,7 +983,50 @@ struct Engine {
       launch_force(U);
       hipLaunchKernelGGL((k_rho_rhs<T>), dim3(sblocks, (unsigned)ms.n), dim3(kThreads), 0, c->stream, ra);
     });
-    timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * 7 * ms.n)), c->stream); });
+    timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * q.nf * ms.n)), c->stream); });
+  }
+
+  bool kinematic() const { return (c->p.flags & MHD_FLAG_KINEMATIC) != 0; }
+
+  // Right-hand side of a kinematic run (frozen rho, m and E): rho, m, B, E on the
+  // grid, e = u x B, and the induction equation.  Neither u^, the strains, the
+  // current nor the other fluxes enter it.
+  void evaluate_kinematic(T* U, T* rout, bool record_status) {
+    const T* zi[8];
+    OutSpec sp[8];
+    for (int f = 0; f < 8; ++f) {
+      zi[f] = spec_field(U, f);
+      sp[f] = copy_spec(f, inv_n3());
+    }
+    const bool fused = k.zyinv && !c->prof_on;
+    if (fused) {
+      inverse_zy(8, zi, 8, sp);
+    } else {
+      T* zo[8];
+      T* yo[8];
+      for (int f = 0; f < 8; ++f) { zo[f] = iz(f); yo[f] = iy(f); }
+      timed(MHD_PASS_ZINV_B, [&] { col(PK_ZINV, 8, zi, 8, zo, sp); });
+      timed(MHD_PASS_YINV_B, [&] { y_copy(PK_YINV, 8, zo, yo); });
+    }
+    RowArgs<T> r = flux_args(record_status);
+    set_out(r, 8);
+    timed(MHD_PASS_XB, [&] { k.row(RM_XK, r, row_grid(RM_XK), c->stream); });
+    RhsArgs<T> q = rhs_args(U, rout);
+    if (fused) {
+      for (int f = 0; f < 3; ++f) q.flux[9 + f] = iy(8 + f);
+      k.yzrhs(q, kFrozenFields, ms.n, c->stream);
+      return;
+    }
+    T* ei[3] = {iy(8), iy(9), iy(10)};
+    T* eo[3] = {iz(0), iz(1), iz(2)};
+    timed(MHD_PASS_YFWD_B, [&] { y_copy(PK_YFWD, 3, ei, eo); });
+    for (int f = 0; f < 3; ++f) q.flux[9 + f] = eo[f];
+    const RhoArgs<T> ra = rho_args(U, rout);
+    timed(MHD_PASS_RHO, [&] {
+      hipLaunchKernelGGL((k_frozen<T>), dim3((unsigned)((g.sc + kThreads - 1) / kThreads), kFrozenFields, (unsigned)ms.n),
+                         dim3(kThreads), 0, c->stream, ra);
+    });
+    timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * q.nf * ms.n)), c->stream); });
   }
 
   // The body force's spectra, from rho^ and m^ of this step before either is
@@ -1013,7 +1076,6 @@ struct Engine {
     a.state = U;
     a.rprev = rprev();
     a.rout = rout;
-    a.kinematic = (c->p.flags & MHD_FLAG_KINEMATIC) ? 1 : 0;
     a.g = g;
     a.bt = batch();
     for (int m = 0; m < ms.n; ++m) {
@@ -1050,7 +1112,8 @@ struct Engine {
     q.tw = tw();
     q.uhat = uhat();
     q.mu = (c->p.flags & MHD_FLAG_VISC_LAPLACIAN) ? c->p.nu : 0.0;
-    q.kinematic = (c->p.flags & MHD_FLAG_KINEMATIC) ? 1 : 0;
+    q.f0 = kinematic() ? 4 : 1;
+    q.nf = kinematic() ? 3 : 7;
     q.force = c->p.force != 0.0 ? force() : nullptr;
     for (int m = 0; m < ms.n; ++m) {
       q.dt[m] = ms.dt[m];
@@ -1068,6 +1131,10 @@ struct Engine {
   // mhd_profile records, every launch class runs by itself.
   void evaluate(T* U, T* rout) { evaluate(U, rout, rout == nullptr); }
   void evaluate(T* U, T* rout, bool record_status) {
+    if (kinematic()) {
+      evaluate_kinematic(U, rout, record_status);
+      return;
+    }
     if (!k.zyinv || c->prof_on) {
       phase_a(U);
       phase_b(U, rout, record_status);
@@ -1118,7 +1185,7 @@ struct Engine {
     k.row(RM_XB, flux_args(record_status), row_grid(RM_XB), c->stream);
     RhsArgs<T> q = rhs_args(U, rout);
     for (int f = 0; f < 12; ++f) q.flux[f] = iy(f);
-    k.yzrhs(q, ms.n, c->stream);
+    k.yzrhs(q, 0, ms.n, c->stream);
   }
 
   double step_bytes() const {
@@ -1302,7 +1369,7 @@ static int ctx_geometry(mhd_ctx* c) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->num_cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess || c->num_cus <= 0) return MHD_E_HIP;
   const bool f32 = is_fp32(p->precision);
-  for (int m = 0; m < 5; ++m) {
+  for (int m = 0; m < kRowModes; ++m) {
     const int occ = f32 ? static_cast<const Kern<float>*>(kv)->row_occupancy(m)
                         : static_cast<const Kern<double>*>(kv)->row_occupancy(m);
     c->row_blocks[m] = occ * c->num_cus;

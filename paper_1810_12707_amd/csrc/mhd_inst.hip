@@ -68,43 +68,38 @@ void strain_rho(const ColArgs<T>& a, const RhoArgs<T>& q, int nmem, hipStream_t 
                      dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, q);
 }
 template <typename T, int N, bool MX>
-void yzrhs(const RhsArgs<T>& a, int nmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_yzrhs<T, N, MX>), dim3((unsigned)(nmem * 7 * Band<N>::NH)),
-                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a);
+void yzrhs(const RhsArgs<T>& a, int nfrozen, int nmem, hipStream_t s) {
+  hipLaunchKernelGGL((k_yzrhs<T, N, MX>), dim3((unsigned)(nmem * (a.nf + nfrozen) * Band<N>::NH)),
+                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, nfrozen);
 }
-template <typename T, int N, bool MX>
-void row(int mode, const RowArgs<T>& a, dim3 g, hipStream_t s) {
+// fn<MODE>() for a run-time row mode
+template <typename F>
+void with_row_mode(int mode, F&& fn) {
   switch (mode) {
-    case RM_XA: hipLaunchKernelGGL((k_row<T, N, RM_XA, MX>), g, dim3(row_threads<T, N, RM_XA, MX>()), 0, s, a); break;
-    case RM_XB: hipLaunchKernelGGL((k_row<T, N, RM_XB, MX>), g, dim3(row_threads<T, N, RM_XB, MX>()), 0, s, a); break;
-    case RM_XFWD_REAL: hipLaunchKernelGGL((k_row<T, N, RM_XFWD_REAL, MX>), g, dim3(row_threads<T, N, RM_XFWD_REAL, MX>()), 0, s, a); break;
-    case RM_XINV_REAL: hipLaunchKernelGGL((k_row<T, N, RM_XINV_REAL, MX>), g, dim3(row_threads<T, N, RM_XINV_REAL, MX>()), 0, s, a); break;
-    case RM_XDIAG: hipLaunchKernelGGL((k_row<T, N, RM_XDIAG, MX>), g, dim3(row_threads<T, N, RM_XDIAG, MX>()), 0, s, a); break;
+    case RM_XA: fn(std::integral_constant<int, RM_XA>()); break;
+    case RM_XB: fn(std::integral_constant<int, RM_XB>()); break;
+    case RM_XFWD_REAL: fn(std::integral_constant<int, RM_XFWD_REAL>()); break;
+    case RM_XINV_REAL: fn(std::integral_constant<int, RM_XINV_REAL>()); break;
+    case RM_XDIAG: fn(std::integral_constant<int, RM_XDIAG>()); break;
+    case RM_XK: fn(std::integral_constant<int, RM_XK>()); break;
     default: break;
   }
 }
-
+template <typename T, int N, bool MX>
+void row(int mode, const RowArgs<T>& a, dim3 g, hipStream_t s) {
+  with_row_mode(mode, [&](auto m) {
+    constexpr int M = decltype(m)::value;
+    hipLaunchKernelGGL((k_row<T, N, M, MX>), g, dim3(row_threads<T, N, M, MX>()), 0, s, a);
+  });
+}
 template <typename T, int N, bool MX>
 int row_occupancy(int mode) {
   int blocks = 0;
   hipError_t e = hipSuccess;
-  switch (mode) {
-    case RM_XA: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, RM_XA, MX>,
-                                                     row_threads<T, N, RM_XA, MX>(), 0); break;
-    case RM_XB: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, RM_XB, MX>,
-                                                     row_threads<T, N, RM_XB, MX>(), 0); break;
-    case RM_XFWD_REAL:
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, RM_XFWD_REAL, MX>,
-                                                     row_threads<T, N, RM_XFWD_REAL, MX>(), 0);
-      break;
-    case RM_XINV_REAL:
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, RM_XINV_REAL, MX>,
-                                                     row_threads<T, N, RM_XINV_REAL, MX>(), 0);
-      break;
-    case RM_XDIAG: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, RM_XDIAG, MX>,
-                                                     row_threads<T, N, RM_XDIAG, MX>(), 0); break;
-    default: break;
-  }
+  with_row_mode(mode, [&](auto m) {
+    constexpr int M = decltype(m)::value;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, M, MX>, row_threads<T, N, M, MX>(), 0);
+  });
   return (e == hipSuccess && blocks > 0) ? blocks : 1;
 }
 

@@ -126,32 +126,31 @@ struct RhsArgs {
   // Section V variants (single runs only, so scalars): mu != 0 adds the
   // viscous force -mu |k|^2 u^ to R_m and -mu |k|^2 q^ to R_E, q = |u|^2/2,
   // from uhat [4][sc] (u^x, u^y, u^z, q^); force: [4][sc] body-force spectra
-  // added to R_m and R_E, or null; kinematic: R_rho, R_m, R_E are zero
+  // added to R_m and R_E, or null
   const T* uhat;
   const T* force;
   double mu;
-  int32_t kinematic;
-  int32_t pad2;
+  int32_t f0, nf;  // fields f0 .. f0 + nf - 1: 1..7, or 4..6 (B) of a kinematic run
   Geo g;
   Batch bt;
   // per member: time step, AB2 coefficients of R^n and R^{n-1}, diffusivity
   double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem], eta[kMaxMem];
 };
 
-// Density right-hand side and update (Eq. MHD1); fields as in RhsArgs.
+// Density right-hand side and update (Eq. MHD1), and the frozen fields of a
+// kinematic run; members as in RhsArgs.
 template <typename T>
 struct RhoArgs {
   T* state;
   T* rprev;
   T* rout;
-  int32_t kinematic;
-  int32_t pad;
   Geo g;
   Batch bt;
   double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem];
 };
 
-enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4 };
+enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5 };
+constexpr int kRowModes = 6;
 
 template <typename T>
 struct RowArgs {
@@ -164,7 +163,7 @@ struct RowArgs {
   int32_t real_dtype;       // 0 = double, 1 = float
   int32_t nf;               // fields of an I/O pass
   double* partials;         // per-block records (RM_XDIAG, single member)
-  double* status;           // RM_XB: status slots [kStatusSlots][2] (max signal speed, non-finite
+  double* status;           // RM_XB, RM_XK: status slots [kStatusSlots][2] (max signal speed, non-finite
                             // count), slot = workgroup id; null: no status (pure RHS evaluations)
   const T* tw;
   Geo g;

@@ -392,7 +392,6 @@ template <typename T> struct RhsMember {
       // viscous force mu lap u, and mu lap(|u|^2/2) in the energy
       if (a.mu != 0.0) R = cfma(-(T(a.mu) * k2), ld(uhat, off), R);
       if (a.force) R = cadd(R, ld(force, off));
-      if (a.kinematic) R = mk<T>(0, 0);  // frozen rho u and E
     }
     if (rout) {
       st(rout, off, R);
@@ -414,7 +413,7 @@ __device__ __forceinline__ void rho_entry(const RhoArgs<T>& a, int mem, int64_t 
   T* const state = member_ptr(a.state, mem, ms);
   const cx<T> mx = ld(state, sc + idx), my = ld(state, 2 * sc + idx), mz = ld(state, 3 * sc + idx);
   const cx<T> d = cfma(T(kz), mz, cfma(T(ky), my, cscale(mx, T(kx))));
-  const cx<T> R = a.kinematic ? mk<T>(0, 0) : ctimes_mi(d);  // zero with the density frozen
+  const cx<T> R = ctimes_mi(d);
   if (a.rout) {
     st(member_ptr(a.rout, mem, ms), idx, R);
     return;
@@ -426,9 +425,32 @@ __device__ __forceinline__ void rho_entry(const RhoArgs<T>& a, int mem, int64_t 
   st(rprev, idx, R);
 }
 
+// One entry of a frozen field of a kinematic run (rho, m, E: R = 0).  The update
+// U += dt (a_cur 0 + a_prev R_prev), R_prev <- 0 changes nothing once the history is
+// zero (it is not where a run continues from another's checkpoint), so a steady
+// step only reads the history.
+constexpr int kFrozenFields = 5;
+__host__ __device__ constexpr int frozen_field(int i) { return i < 4 ? i : 7; }
+template <typename T, class Args>
+__device__ __forceinline__ void frozen_entry(const Args& a, int mem, int i, int64_t idx) {
+  const int64_t ms = a.bt.mstride, at = frozen_field(i) * a.g.sc + idx;
+  const cx<T> zero = mk<T>(0, 0);
+  if (a.rout) {
+    st(member_ptr(a.rout, mem, ms), at, zero);
+    return;
+  }
+  T* const rprev = member_ptr(a.rprev, mem, ms);
+  if (a.a_prev[mem] != 0.0) {
+    const cx<T> p = ld(rprev, at);
+    if (p.x == T(0) && p.y == T(0)) return;
+    T* const state = member_ptr(a.state, mem, ms);
+    st(state, at, cfma(T(a.dt[mem]), cfma(T(a.a_prev[mem]), p, zero), ld(state, at)));
+  }
+  st(rprev, at, zero);
+}
+
 // ------------------------------------------------------------------ k_zfwd_rhs
-// Flat grid over (member, column tile of (ky, kx), output field f = 1..7),
-// field fastest.
+// Flat grid over (member, column tile of (ky, kx), output field), field fastest.
 template <typename T, int N, bool MX>
 __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N, MX>())) k_zfwd_rhs(const RhsArgs<T> a) {
   using PL = PlanOf<N, MX>;
@@ -440,10 +462,10 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
   __shared__ cx<T> tile[N * C];
   __shared__ cx<T> stw[N];
   const int tid = threadIdx.x;
-  // fields 1..7; R_rho is formed by its own pass before this one, because
-  // this pass overwrites m^ (which R_rho = -i k . m^ reads) with its next level
-  const TileField tf = tile_field(7);
-  const int f = tf.field + 1;
+  // fields 1..7 (or B alone); R_rho is formed by its own pass before this one,
+  // because this pass overwrites m^ (which R_rho = -i k . m^ reads) with its next level
+  const TileField tf = tile_field(a.nf);
+  const int f = tf.field + a.f0;
   constexpr int ZT = (NCOLS + C - 1) / C;  // column tiles per member
   const int mem = tf.tile / ZT;
   const int c0 = (tf.tile - mem * ZT) * C;
@@ -577,6 +599,7 @@ template <> struct RowShape<RM_XA> { static constexpr int NIN = 4, NOUT = 3, NB 
 template <> struct RowShape<RM_XB> { static constexpr int NIN = 16, NOUT = 12, NB = 16; };
 template <> struct RowShape<RM_XFWD_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
 template <> struct RowShape<RM_XINV_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
+template <> struct RowShape<RM_XK> { static constexpr int NIN = 8, NOUT = 3, NB = 8; };
 template <> struct RowShape<RM_XDIAG> { static constexpr int NIN = kDiagFields, NOUT = 0, NB = kDiagFields; };
 
 template <typename T>
@@ -687,7 +710,12 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // every lane of a first pass hold a butterfly (128: 256 threads in FP32, 56.8 ->
 // 55.1 us) or half as many (64, and 128 in FP64 where the registers of two
 // butterflies fit: 20.2 -> 18.5 and 109 -> 89 us; FP32 at 128 would spill).
+// The kinematic pass (eight fields) takes a thread per first-pass butterfly.
 template <typename T, int N, int MODE, bool MX> constexpr int row_threads() {
+  if (MODE == RM_XK) {
+    constexpr int w = 8 * (N / PlanOf<N, MX>::r[0]);
+    return w <= 64 ? 64 : (w >= 512 ? 512 : (w + 63) / 64 * 64);
+  }
   if (!MX && MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
   if (!MX && MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
   if (sizeof(T) == 4 && !MX && MODE == RM_XA && N == 256) return kThreads / 2;
@@ -701,7 +729,7 @@ template <typename T, int N, int MODE, bool MX> constexpr int row_threads() {
 // and then runs one wave per SIMD (the MFMA variant at N = 512 was 1.3x
 // slower so than capped).
 template <typename T, int N, int MODE, bool MX> constexpr int row_min_blocks() {
-  if (sizeof(T) != 4 || row_threads<T, N, MODE, MX>() < kThreads) return 1;
+  if (sizeof(T) != 4 || row_threads<T, N, MODE, MX>() < kThreads || MODE == RM_XK) return 1;
   if (!MX && MODE == RM_XB && (N == 512 || N == 384 || N == 256)) return 2;
   return 2 * kThreads / row_threads<T, N, MODE, MX>();
 }
@@ -742,7 +770,9 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
   // first-pass butterflies per field leave lanes of a wave idle: 96 FP32 flux
   // pass 30.8 -> 35.7 us), by the mixed flux pass (slower) or with fewer fields
   // than waves.
-  constexpr bool WAVE = (MX ? (MODE == RM_XA && !mid_mfma<PL>()) : (MODE == RM_XA || MODE == RM_XB)) &&
+  constexpr bool FLUX = MODE == RM_XB || MODE == RM_XK;  // forms fluxes and the status
+  constexpr bool WAVE = MODE == RM_XK ? !MX && is_pow2(N) && N >= 64 :
+                       (MX ? (MODE == RM_XA && !mid_mfma<PL>()) : (MODE == RM_XA || MODE == RM_XB)) &&
                        (N >= 384 || (!MX && (N == 256 || N == 128 || N == 64 || (N == 192 && NT == 64)))) &&
                        NB >= NT / 64;
   // MFMA groups overlapped in the mixed last pass (measured: the velocity
@@ -834,7 +864,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
   for (; item < nitems; item += gridDim.x) {
     const int mem = (int)(item / rows_per_mem);
     const int64_t row0 = 2 * (item - mem * rows_per_mem);  // flattened row z*N + y of the first row
-    if constexpr (MODE == RM_XB) {
+    if constexpr (FLUX) {
       if (mem != cur_m) {  // uniform across the workgroup
         if (cur_m >= 0 && a.status) {
           flush_status<NT>(double(cfl), bad, member_ptr(a.status, cur_m, a.bt.mstride), red);
@@ -1092,7 +1122,40 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
       continue;
     }
 
-    if constexpr (MODE == RM_XA || MODE == RM_XB || MODE == RM_XFWD_REAL) {
+    if constexpr (MODE == RM_XK) {
+      // Kinematic run: the induction flux e = u x B and the status.
+      // Inputs: 0 rho, 1-3 m, 4-6 B, 7 E.  Outputs: 0-2 e.
+      const T gm1 = T(a.gamma[mem] - 1.0), gam = T(a.gamma[mem]);
+      for (int x = tid; x < N; x += NT) {
+        cx<T> v[8], o[3];
+#pragma unroll
+        for (int f = 0; f < 8; ++f) v[f] = buf[at(f, x)];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          auto g = [&](int f) -> T { return h == 0 ? v[f].x : v[f].y; };
+          const T rho = g(0), mx = g(1), my = g(2), mz = g(3), Bx = g(4), By = g(5), Bz = g(6), E = g(7);
+          const T ir = recip_(rho);
+          const T ux = mx * ir, uy = my * ir, uz = mz * ir;
+          const T B2 = Bx * Bx + By * By + Bz * Bz;
+          const T P = gm1 * (E - T(0.5) * (mx * ux + my * uy + mz * uz) - T(0.5) * B2);
+          const T e[3] = {uy * Bz - uz * By, uz * Bx - ux * Bz, ux * By - uy * Bx};
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            if (h == 0) o[k].x = e[k];
+            else o[k].y = e[k];
+          }
+          const T c = fmax(fabs(ux), fmax(fabs(uy), fabs(uz))) + sqrt_((gam * P + B2) * ir);
+          if (!(c <= cfl)) cfl = c;  // NaN propagates
+          const bool fin = finite_(rho) && finite_(mx) && finite_(my) && finite_(mz) && finite_(Bx) &&
+                           finite_(By) && finite_(Bz) && finite_(E);
+          bad += fin ? 0 : 1;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) buf[at(k, x)] = o[k];
+      }
+    }
+
+    if constexpr (MODE == RM_XA || FLUX || MODE == RM_XFWD_REAL) {
       __syncthreads();
       lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K, UNR>(buf, stw, tid, nout);  // only k <= K and N - k are read
       // unpack: X0[k] = (Z[k] + conj Z[N-k]) / 2, X1[k] = -i (Z[k] - conj Z[N-k]) / 2, k = 0..K,
@@ -1150,7 +1213,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
     }
   }
 
-  if constexpr (MODE == RM_XB) {
+  if constexpr (FLUX) {
     if (cur_m >= 0 && a.status) flush_status<NT>(double(cfl), bad, member_ptr(a.status, cur_m, a.bt.mstride), red);
   }
   if constexpr (MODE == RM_XDIAG) {

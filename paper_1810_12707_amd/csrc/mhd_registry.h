@@ -27,7 +27,7 @@ struct Kern {
   void (*zyinv)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
   void (*yzfwd)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
   void (*strain_rho)(const ColArgs<T>&, const RhoArgs<T>&, int nmem, hipStream_t) = nullptr;
-  void (*yzrhs)(const RhsArgs<T>&, int nmem, hipStream_t) = nullptr;
+  void (*yzrhs)(const RhsArgs<T>&, int nfrozen, int nmem, hipStream_t) = nullptr;
   void (*row)(int mode, const RowArgs<T>&, dim3, hipStream_t) = nullptr;
   // resident workgroups per CU of a row-pass mode (persistent grid sizing)
   int (*row_occupancy)(int mode) = nullptr;

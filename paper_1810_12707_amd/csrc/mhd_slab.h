@@ -234,17 +234,22 @@ __global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
 // Flux planes -> right-hand sides and update of m, B and E (fields 1..7): forward y
 // of the up to three fluxes side by side (teams 0, 1: the terms of A_f, team 2:
 // Z_f), forward z of their combinations, and the epilogue of k_zfwd_rhs over all
-// threads.
+// threads.  The nfrozen fields after them are those a kinematic run freezes.
 template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>())) k_yzrhs(const RhsArgs<T> a) {
+__global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
+    k_yzrhs(const RhsArgs<T> a, int nfrozen) {
   using SL = Slab<T, N, MX>;
   constexpr int NT = SL::NT, NA = kTeams * NT;
   constexpr int NE = SL::NB * SL::NB, CNT = (NE + NA - 1) / NA;  // entries of this kx, per thread
   __shared__ cx<T> buf[kTeams][SL::SZ];
   __shared__ cx<T> stw[N];
   const int tid = threadIdx.x, team = __builtin_amdgcn_readfirstlane(tid / NT), ttid = tid - team * NT;
-  const SlabItem it = slab_item<SL::NH>(7);
-  const int f = it.f + 1;
+  const SlabItem it = slab_item<SL::NH>(a.nf + nfrozen);
+  if (it.f >= a.nf) {
+    for (int e = tid; e < NE; e += NA) frozen_entry<T>(a, it.m, it.f - a.nf, (int64_t)e * SL::NHP + it.kx);
+    return;
+  }
+  const int f = it.f + a.f0;
   const OutSpec& A = a.A[f];
   const OutSpec& Z = a.Z[f];
   // the state and the previous right-hand side, in flight during the transforms
