@@ -101,7 +101,7 @@ k_reduce(const double* __restrict__ p1, int64_t n1, int nq1, unsigned max_mask, 
 // pass that forms the other seven right-hand sides, since that pass overwrites m^
 // with its next time level.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) k_rho_rhs(const RhoArgs<T> a) {
+__global__ void __launch_bounds__(kThreads) k_rho_rhs(const UpdateArgs<T> a) {
   const Geo& g = a.g;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t plane = (int64_t)g.nb * g.nhp;
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(kThreads) k_rho_rhs(const RhoArgs<T> a) {
 // The frozen fields of a kinematic run (frozen_entry), one thread per compact
 // entry of frozen field blockIdx.y of member blockIdx.z.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) k_frozen(const RhoArgs<T> a) {
+__global__ void __launch_bounds__(kThreads) k_frozen(const UpdateArgs<T> a) {
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= a.g.sc || (int)(idx % a.g.nhp) >= a.g.nh) return;
   frozen_entry<T>(a, blockIdx.z, blockIdx.y, idx);
@@ -196,40 +196,6 @@ __global__ void __launch_bounds__(kThreads) k_force_abc(const T* __restrict__ st
     work.y += a * (s2.y + c2.y);
   }
   F[3 * g.sc + idx] = work;
-}
-
-// Stage arithmetic of the Runge-Kutta and predictor-corrector schemes over the
-// eight compact fields (one thread per entry, padding skipped):
-//   CB_RK_FIRST:  acc = R;          us = u + c R
-//   CB_RK_MID:    acc += w R;       us = u + c R
-//   CB_RK_LAST:   u += c (acc + R)
-//   CB_PC_PRED:   us = u + dt (a_cur R + a_prev acc); acc = R   (acc = history)
-//   CB_PC_CORR:   u += c (acc + R)                              (acc = R^n)
-enum { CB_RK_FIRST = 0, CB_RK_MID, CB_RK_LAST, CB_PC_PRED, CB_PC_CORR };
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_combine(T* __restrict__ u, const T* __restrict__ R,
-                                                     T* __restrict__ acc, T* __restrict__ us, Geo g, int op,
-                                                     double c, double w, double a_cur, double a_prev) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // entry of the 8 fields
-  if (e >= 8 * g.sc) return;
-  const int64_t idx = e % g.sc;
-  if (idx % g.nhp >= g.nh) return;  // kx padding: never read or written
-  const int64_t j = 2 * e;
-  for (int h = 0; h < 2; ++h) {
-    const T r = R[j + h];
-    switch (op) {
-      case CB_RK_FIRST: acc[j + h] = r; us[j + h] = u[j + h] + T(c) * r; break;
-      case CB_RK_MID: acc[j + h] += T(w) * r; us[j + h] = u[j + h] + T(c) * r; break;
-      case CB_PC_PRED: {
-        // the Euler start (a_prev = 0) never reads the history, which may not exist yet
-        const T hist = a_prev != 0.0 ? T(a_prev) * acc[j + h] : T(0);
-        us[j + h] = u[j + h] + T(c) * (T(a_cur) * r + hist);
-        acc[j + h] = r;
-        break;
-      }
-      default: u[j + h] += T(c) * (acc[j + h] + r); break;  // CB_RK_LAST, CB_PC_CORR
-    }
-  }
 }
 
 // ------------------------------------------------------------------ tracers
@@ -951,13 +917,9 @@ struct Engine {
     timed(MHD_PASS_ZFWD_A, [&] { col(PK_ZFWD, nu_, uo, nu_, ho, cp); });
   }
 
-  // Phase B: fluxes and the spectral RHS of state U.  rout == nullptr: AB2
-  // update of U and the history with the members' coefficients ms.a_cur,
-  // ms.a_prev.  record_status: fold the flux pass's CFL speed and
-  // non-finite count into the status slots (steps do; pure right-hand sides
-  // and the later stages of a multistage step do not).
-  void phase_b(T* U, T* rout, bool record_status) {
-    const double s = inv_n3();
+  // Phase B: fluxes and the spectral RHS, and its update.
+  void phase_b(const UpdateArgs<T>& up, bool record_status) {
+    T* const U = up.state;
     // inputs: 0-2 B^, 3 E^, 4-6 u^
     const T* zi[7] = {spec_field(U, 4), spec_field(U, 5), spec_field(U, 6), spec_field(U, 7),
                       spec_field(uhat(), 0), spec_field(uhat(), 1), spec_field(uhat(), 2)};
@@ -975,13 +937,12 @@ struct Engine {
     T* fo[12];
     for (int f = 0; f < 12; ++f) { fi[f] = iy(f); fo[f] = iz(f); }
     timed(MHD_PASS_YFWD_B, [&] { y_copy(PK_YFWD, 12, fi, fo); });
-    RhsArgs<T> q = rhs_args(U, rout);
+    RhsArgs<T> q = rhs_args(up);
     for (int f = 0; f < 12; ++f) q.flux[f] = iz(f);
-    const RhoArgs<T> ra = rho_args(U, rout);
     const unsigned sblocks = (unsigned)((g.sc + kThreads - 1) / kThreads);
     timed(MHD_PASS_RHO, [&] {
       launch_force(U);
-      hipLaunchKernelGGL((k_rho_rhs<T>), dim3(sblocks, (unsigned)ms.n), dim3(kThreads), 0, c->stream, ra);
+      hipLaunchKernelGGL((k_rho_rhs<T>), dim3(sblocks, (unsigned)ms.n), dim3(kThreads), 0, c->stream, up);
     });
     timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * q.nf * ms.n)), c->stream); });
   }
@@ -991,7 +952,8 @@ struct Engine {
   // Right-hand side of a kinematic run (frozen rho, m and E): rho, m, B, E on the
   // grid, e = u x B, and the induction equation.  Neither u^, the strains, the
   // current nor the other fluxes enter it.
-  void evaluate_kinematic(T* U, T* rout, bool record_status) {
+  void evaluate_kinematic(const UpdateArgs<T>& up, bool record_status) {
+    T* const U = up.state;
     const T* zi[8];
     OutSpec sp[8];
     for (int f = 0; f < 8; ++f) {
@@ -1011,7 +973,7 @@ struct Engine {
     RowArgs<T> r = flux_args(record_status);
     set_out(r, 8);
     timed(MHD_PASS_XB, [&] { k.row(RM_XK, r, row_grid(RM_XK), c->stream); });
-    RhsArgs<T> q = rhs_args(U, rout);
+    RhsArgs<T> q = rhs_args(up);
     if (fused) {
       for (int f = 0; f < 3; ++f) q.flux[9 + f] = iy(8 + f);
       k.yzrhs(q, kFrozenFields, ms.n, c->stream);
@@ -1021,10 +983,9 @@ struct Engine {
     T* eo[3] = {iz(0), iz(1), iz(2)};
     timed(MHD_PASS_YFWD_B, [&] { y_copy(PK_YFWD, 3, ei, eo); });
     for (int f = 0; f < 3; ++f) q.flux[9 + f] = eo[f];
-    const RhoArgs<T> ra = rho_args(U, rout);
     timed(MHD_PASS_RHO, [&] {
       hipLaunchKernelGGL((k_frozen<T>), dim3((unsigned)((g.sc + kThreads - 1) / kThreads), kFrozenFields, (unsigned)ms.n),
-                         dim3(kThreads), 0, c->stream, ra);
+                         dim3(kThreads), 0, c->stream, up);
     });
     timed(MHD_PASS_ZRHS, [&] { k.rhs(q, dim3((unsigned)(rtiles() * q.nf * ms.n)), c->stream); });
   }
@@ -1070,12 +1031,19 @@ struct Engine {
     return r;
   }
 
-  RhoArgs<T> rho_args(T* U, T* rout) const {
-    RhoArgs<T> a;
+  // Update of a step with op (c, w as in UpdateOp) for a right-hand side of state
+  // U; op UP_STORE: R into rout.
+  UpdateArgs<T> update_args(int op, T* U, T* rout = nullptr, double cc = 0.0, double w = 0.0) const {
+    UpdateArgs<T> a;
     std::memset(&a, 0, sizeof(a));
     a.state = U;
-    a.rprev = rprev();
-    a.rout = rout;
+    a.u = state();
+    a.acc = rprev();
+    a.us = tstate();
+    a.rout = rout ? rout : trhs();
+    a.op = op;
+    a.c = cc;
+    a.w = w;
     a.g = g;
     a.bt = batch();
     for (int m = 0; m < ms.n; ++m) {
@@ -1087,7 +1055,7 @@ struct Engine {
   }
 
   // Arguments of the last pass of a right-hand side (flux pointers left to the caller).
-  RhsArgs<T> rhs_args(T* U, T* rout) const {
+  RhsArgs<T> rhs_args(const UpdateArgs<T>& up) const {
     enum { X = 0, Y = 1, Z = 2 };
     RhsArgs<T> q;
     std::memset(&q, 0, sizeof(q));
@@ -1106,38 +1074,31 @@ struct Engine {
     q.A[6] = spec({term(10, X, 1), term(9, Y, -1)});
     q.A[7] = spec({term(6, X, -1), term(7, Y, -1)});  // MHD3: -i k . F^E
     q.Z[7] = spec({term(8, -1, -1)});
-    q.state = U;
-    q.rprev = rprev();
-    q.rout = rout;
+    q.up = up;
     q.tw = tw();
     q.uhat = uhat();
     q.mu = (c->p.flags & MHD_FLAG_VISC_LAPLACIAN) ? c->p.nu : 0.0;
     q.f0 = kinematic() ? 4 : 1;
     q.nf = kinematic() ? 3 : 7;
     q.force = c->p.force != 0.0 ? force() : nullptr;
-    for (int m = 0; m < ms.n; ++m) {
-      q.dt[m] = ms.dt[m];
-      q.a_cur[m] = ms.a_cur[m];
-      q.a_prev[m] = ms.a_prev[m];
-      q.eta[m] = ms.eta[m];
-    }
-    q.g = g;
-    q.bt = batch();
+    for (int m = 0; m < ms.n; ++m) q.eta[m] = ms.eta[m];
     return q;
   }
 
-  // One right-hand side of state U and its update (or the store into rout).
-  // record_status as for phase_b.  Small grids run the fused passes; while
-  // mhd_profile records, every launch class runs by itself.
-  void evaluate(T* U, T* rout) { evaluate(U, rout, rout == nullptr); }
-  void evaluate(T* U, T* rout, bool record_status) {
+  // One right-hand side (of state up.state) and its update.  record_status: fold
+  // the flux pass's CFL speed and non-finite count into the status slots (the
+  // first evaluation of a step does; pure right-hand sides and later stages do
+  // not).  Small grids run the fused passes; while mhd_profile records, every
+  // launch class runs by itself.
+  void evaluate(const UpdateArgs<T>& up, bool record_status) {
+    T* const U = up.state;
     if (kinematic()) {
-      evaluate_kinematic(U, rout, record_status);
+      evaluate_kinematic(up, record_status);
       return;
     }
     if (!k.zyinv || c->prof_on) {
       phase_a(U);
-      phase_b(U, rout, record_status);
+      phase_b(up, record_status);
       return;
     }
     // rho, m, B, E and J (the strains, slots 8-12, follow from u)
@@ -1173,7 +1134,7 @@ struct Engine {
       a.out[f] = iy(8 + f);
       a.spec[f] = sp[4 + f];
     }
-    k.strain_rho(a, rho_args(U, rout), ms.n, c->stream);
+    k.strain_rho(a, up, ms.n, c->stream);
     if (na() == 4) {  // the viscous-force variant needs u^ and q^ themselves
       a = col_args(PK_ZFWD, 4);
       for (int f = 0; f < 4; ++f) {
@@ -1183,7 +1144,7 @@ struct Engine {
       k.yzfwd(a, ms.n, c->stream);
     }
     k.row(RM_XB, flux_args(record_status), row_grid(RM_XB), c->stream);
-    RhsArgs<T> q = rhs_args(U, rout);
+    RhsArgs<T> q = rhs_args(up);
     for (int f = 0; f < 12; ++f) q.flux[f] = iy(f);
     k.yzrhs(q, 0, ms.n, c->stream);
   }
@@ -1192,45 +1153,32 @@ struct Engine {
     double b = 0.0;
     for (int cls = 0; cls < MHD_PASS_COUNT; ++cls) b += class_bytes(cls);
     const double evals = c->p.scheme == MHD_RK4 ? 4 : (c->p.scheme == MHD_PC ? 2 : 1);
-    // a multistage step: its right-hand sides plus the stage arithmetic over the 8-field sets
-    const double stage = c->p.scheme == MHD_RK4 ? 4 * cbytes(24, 0, 0) + cbytes(8, 0, 0)
-                                                 : (c->p.scheme == MHD_PC ? 2 * cbytes(24, 0, 0) : 0.0);
+    // The launch classes count an AB2 update (8 fields: state and history read and
+    // written, 32 S_c).  RK4's four updates move 24 + 32 + 32 + 24 and the three
+    // stage states' B (9) instead of 128; PC's two 32 + 24 + 3 instead of 64.
+    const double stage = c->p.scheme == MHD_RK4 ? cbytes(-7, 0, 0) : (c->p.scheme == MHD_PC ? cbytes(-5, 0, 0) : 0.0);
     return b * evals + stage;
   }
 
-  void combine(int op, double cc, double w, double a_cur = 0.0, double a_prev = 0.0) {
-    const unsigned blocks = (unsigned)((8 * g.sc + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL((k_combine<T>), dim3(blocks), dim3(kThreads), 0, c->stream, state(), trhs(), rprev(),
-                       tstate(), g, op, cc, w, a_cur, a_prev);
-  }
-
-  // One step of the context's scheme (single runs).  AB2: one right-hand
-  // side with the update fused into its last pass.  RK4 and PC: right-hand
-  // sides into trhs, stage states in tstate, and rprev as the RK4 stage sum
-  // or the PC history.  The flux pass of the first evaluation (the state at
-  // t_n) records the CFL / non-finite status.
+  // One step of the context's scheme (single runs), every update fused into the
+  // last pass of its right-hand side.  RK4 keeps its stage sum in rprev, RK4 and PC
+  // their stage states in tstate.  The flux pass of the first evaluation (the
+  // state at t_n) records the CFL / non-finite status.
   void step_once(bool first) {
     const double dt = c->p.dt;
-    if (c->p.scheme == MHD_RK4) {
-      evaluate(state(), trhs(), true);
-      combine(CB_RK_FIRST, 0.5 * dt, 0.0);
-      const double cs[3] = {0.5 * dt, dt, dt / 6.0};
-      for (int st = 0; st < 3; ++st) {
-        evaluate(tstate(), trhs(), false);
-        combine(st < 2 ? CB_RK_MID : CB_RK_LAST, cs[st], st < 2 ? 2.0 : 1.0);
-      }
-      return;
-    }
-    if (c->p.scheme == MHD_PC) {
-      evaluate(state(), trhs(), true);
-      combine(CB_PC_PRED, dt, 0.0, first ? 1.0 : 1.5, first ? 0.0 : -0.5);
-      evaluate(tstate(), trhs(), false);
-      combine(CB_PC_CORR, 0.5 * dt, 0.0);
-      return;
-    }
     ms.a_cur[0] = first ? 1.0 : 1.5;
     ms.a_prev[0] = first ? 0.0 : -0.5;
-    evaluate(state(), nullptr);
+    if (c->p.scheme == MHD_RK4) {
+      evaluate(update_args(UP_RK_FIRST, state(), nullptr, 0.5 * dt), true);
+      evaluate(update_args(UP_RK_MID, tstate(), nullptr, 0.5 * dt, 2.0), false);
+      evaluate(update_args(UP_RK_MID, tstate(), nullptr, dt, 2.0), false);
+      evaluate(update_args(UP_LAST, tstate(), nullptr, dt / 6.0), false);
+    } else if (c->p.scheme == MHD_PC) {
+      evaluate(update_args(UP_PC_PRED, state()), true);
+      evaluate(update_args(UP_LAST, tstate(), nullptr, 0.5 * dt), false);
+    } else {
+      evaluate(update_args(UP_AB2, state()), true);
+    }
   }
 
   void reset_status() {
@@ -1619,7 +1567,7 @@ void group_launch(mhd_ens* E, EnsGroup& G, const Kern<T>& k, bool rhs_only) {
     ms.a_prev[s] = mc->first_step ? 0.0 : -0.5;
   }
   Engine<T> e(G.lead, k, ms);
-  e.evaluate(e.state(), rhs_only ? e.trhs() : nullptr);
+  e.evaluate(e.update_args(rhs_only ? UP_STORE : UP_AB2, e.state()), !rhs_only);
 }
 
 // Every group as a parallel branch forked from and joined into `origin` (the
@@ -1876,7 +1824,7 @@ int mhd_rhs(mhd_ctx* c, const void* d_in, void* d_out, int32_t dtype) {
   if (!c || !d_in || !d_out || !dtype_ok(dtype)) return MHD_E_ARG;
   return with_engine(c, [&](auto& e) {
     e.forward_real(d_in, dtype, 8, e.tstate());
-    e.evaluate(e.tstate(), e.trhs());
+    e.evaluate(e.update_args(UP_STORE, e.tstate(), e.trhs()), false);
     e.inverse_real(e.trhs(), 8, d_out, dtype);
     return check_launch(c, "mhd_rhs");
   });

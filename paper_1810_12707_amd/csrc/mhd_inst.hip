@@ -63,7 +63,7 @@ void yzfwd(const ColArgs<T>& a, int nmem, hipStream_t s) {
                      dim3(slab_threads<T, N, MX>()), 0, s, a);
 }
 template <typename T, int N, bool MX>
-void strain_rho(const ColArgs<T>& a, const RhoArgs<T>& q, int nmem, hipStream_t s) {
+void strain_rho(const ColArgs<T>& a, const UpdateArgs<T>& q, int nmem, hipStream_t s) {
   hipLaunchKernelGGL((k_strain_rho<T, N, MX>), dim3((unsigned)(nmem * (a.nout + 1) * Band<N>::NH)),
                      dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, q);
 }

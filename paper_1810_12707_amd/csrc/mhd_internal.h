@@ -110,6 +110,33 @@ struct ColArgs {
   Batch bt;
 };
 
+// What becomes of a right-hand side R = R(U) in the pass that forms it (U: the
+// state it is evaluated at; u: the state a step advances; acc: the AB2 / PC
+// history or the RK4 stage sum; us: a stage state):
+//   UP_STORE     rout = R
+//   UP_AB2       u += dt (a_cur R + a_prev acc); acc = R          (U = u)
+//   UP_RK_FIRST  acc = R;          us = u + c R                   (U = u)
+//   UP_RK_MID    acc += w R;       us = u + c R                   (U = us)
+//   UP_PC_PRED   us = u + dt (a_cur R + a_prev acc); acc = R      (U = u)
+//   UP_LAST      u += c (acc + R)            (RK4's last stage, PC's corrector; U = us)
+// A history with a_prev = 0 (the Euler start) is not read.
+enum UpdateOp { UP_STORE = 0, UP_AB2, UP_RK_FIRST, UP_RK_MID, UP_PC_PRED, UP_LAST };
+
+template <typename T>
+struct UpdateArgs {
+  T* state;  // U, compact [8][sc]
+  T* u;
+  T* acc;
+  T* us;
+  T* rout;
+  int32_t op;
+  int32_t pad;
+  double c, w;
+  double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem];  // per member
+  Geo g;
+  Batch bt;
+};
+
 // Forward-z pass that forms the right-hand side (Eqs. MHD2-MHD4 in spectral
 // form) and applies the AB2 update.  Output f = 1..7 is
 //   R_f = F_z[A_f] + i kz F_z[Z_f] - eta |k|^2 B^_f (f = 4, 5, 6),
@@ -119,9 +146,7 @@ struct RhsArgs {
   const T* flux[kMaxIn];  // I_z flux slots
   OutSpec A[8];
   OutSpec Z[8];
-  T* state;               // compact [8][sc]
-  T* rprev;               // compact [8][sc] (R^{n-1}, overwritten with R^n)
-  T* rout;                // if non-null: store R here, leave state/rprev untouched
+  UpdateArgs<T> up;
   const T* tw;
   // Section V variants (single runs only, so scalars): mu != 0 adds the
   // viscous force -mu |k|^2 u^ to R_m and -mu |k|^2 q^ to R_E, q = |u|^2/2,
@@ -131,22 +156,7 @@ struct RhsArgs {
   const T* force;
   double mu;
   int32_t f0, nf;  // fields f0 .. f0 + nf - 1: 1..7, or 4..6 (B) of a kinematic run
-  Geo g;
-  Batch bt;
-  // per member: time step, AB2 coefficients of R^n and R^{n-1}, diffusivity
-  double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem], eta[kMaxMem];
-};
-
-// Density right-hand side and update (Eq. MHD1), and the frozen fields of a
-// kinematic run; members as in RhsArgs.
-template <typename T>
-struct RhoArgs {
-  T* state;
-  T* rprev;
-  T* rout;
-  Geo g;
-  Batch bt;
-  double dt[kMaxMem], a_cur[kMaxMem], a_prev[kMaxMem];
+  double eta[kMaxMem];  // diffusivity, per member
 };
 
 enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5 };

@@ -77,7 +77,9 @@ template <typename T, int N, bool MX> constexpr int rhs_tile() {
   return rhs_wide<T, N, MX>() ? (N == 256 && !MX ? 16 : 8) : col_width<T, N>();
 }
 // Minimum resident waves per SIMD asked of the compiler (register cap).
+// FP32 at 128: seven waves, so that the 1785 workgroups are resident at once.
 template <typename T, int N, bool MX> constexpr int rhs_min_waves() {
+  if (sizeof(T) == 4 && !MX && N == 128 && MHD_SCHED == 0) return 7;
   return rhs_wide<T, N, MX>() || rhs_threads<T, N, MX>() > kThreads ? 1 : 3;
 }
 
@@ -353,100 +355,107 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(c
 }
 
 // ------------------------------------------------------------------ right-hand-side epilogue
-// Field f (1..7) of one member in the last pass of a right-hand side: the
-// resistive term, the Section V variants, and the AB2 update
-// U += dt (a_cur R^n + a_prev R^{n-1}), R^{n-1} <- R^n, or the store of R into
-// rout.  off: entry of the compact spectrum.
-template <typename T> struct RhsMember {
-  const RhsArgs<T>& a;
-  int f;
-  T *state, *rprev, *rout;  // field f
-  const T *uhat, *force;    // the entries that belong to field f
-  T dt, ac, ap, eta;
-  bool use_prev, need_state, need_prev, induction;
-  __device__ __forceinline__ RhsMember(const RhsArgs<T>& args, int mem, int fld) : a(args), f(fld) {
-    const int64_t ms = a.bt.mstride, sc = a.g.sc;
-    const int vslot = f <= 3 ? f - 1 : 3;  // u^_{f-1} for the momentum, q^ for the energy
-    state = member_ptr(a.state, mem, ms) + 2 * f * sc;
-    rprev = member_ptr(a.rprev, mem, ms) + 2 * f * sc;
-    rout = a.rout ? member_ptr(a.rout, mem, ms) + 2 * f * sc : nullptr;
-    uhat = member_ptr(a.uhat, mem, ms) + 2 * vslot * sc;
-    force = a.force ? member_ptr(a.force, mem, ms) + 2 * vslot * sc : nullptr;
+// The update of field f (0..7) of one member: see UpdateOp.  off: entry of the
+// compact spectrum.
+template <typename T> struct Update {
+  int op;
+  T *state, *u, *acc, *us, *rout;  // field f
+  T dt, ac, ap, c, w;
+  bool use_prev;
+  __device__ __forceinline__ Update(const UpdateArgs<T>& a, int mem, int f) {
+    const int64_t ms = a.bt.mstride, at = 2 * f * a.g.sc;
+    op = a.op;
+    state = member_ptr(a.state, mem, ms) + at;
+    u = member_ptr(a.u, mem, ms) + at;
+    acc = member_ptr(a.acc, mem, ms) + at;
+    us = member_ptr(a.us, mem, ms) + at;
+    rout = member_ptr(a.rout, mem, ms) + at;
     dt = T(a.dt[mem]);
     ac = T(a.a_cur[mem]);
     ap = T(a.a_prev[mem]);
-    eta = T(a.eta[mem]);
+    c = T(a.c);
+    w = T(a.w);
     use_prev = a.a_prev[mem] != 0.0;
-    induction = f >= 4 && f <= 6;
-    need_state = !rout || induction;
-    need_prev = !rout && use_prev;
   }
-  __device__ __forceinline__ cx<T> old_state(int64_t off) const { return need_state ? ld(state, off) : mk<T>(0, 0); }
-  __device__ __forceinline__ cx<T> old_rhs(int64_t off) const { return need_prev ? ld(rprev, off) : mk<T>(0, 0); }
-  __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u, cx<T> rp, int kx, int ky, int kz) const {
+  __device__ __forceinline__ bool reads_acc() const {
+    return op == UP_RK_MID || op == UP_LAST || ((op == UP_AB2 || op == UP_PC_PRED) && use_prev);
+  }
+  __device__ __forceinline__ bool at_u() const { return op != UP_RK_MID && op != UP_LAST && op != UP_STORE; }  // U = u
+  __device__ __forceinline__ cx<T> old_u(int64_t off) const { return op != UP_STORE ? ld(u, off) : mk<T>(0, 0); }
+  __device__ __forceinline__ cx<T> old_acc(int64_t off) const { return reads_acc() ? ld(acc, off) : mk<T>(0, 0); }
+  // u0, a0: old_u and old_acc of the entry
+  __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u0, cx<T> a0) const {
+    if (op == UP_STORE) {
+      st(rout, off, R);
+    } else if (op == UP_AB2 || op == UP_PC_PRED) {
+      cx<T> inc = cscale(R, ac);
+      if (use_prev) inc = cfma(ap, a0, inc);
+      st(op == UP_AB2 ? u : us, off, cfma(dt, inc, u0));
+      st(acc, off, R);
+    } else if (op == UP_LAST) {
+      st(u, off, cfma(c, cadd(a0, R), u0));
+    } else {
+      st(acc, off, op == UP_RK_FIRST ? R : cfma(w, R, a0));
+      st(us, off, cfma(c, R, u0));
+    }
+  }
+};
+
+// Field f (1..7) in the last pass of a right-hand side: the resistive term, the
+// Section V variants and the update.
+template <typename T> struct RhsMember {
+  const RhsArgs<T>& a;
+  Update<T> up;
+  const T *uhat, *force;  // the entries that belong to field f
+  T eta;
+  bool induction;
+  __device__ __forceinline__ RhsMember(const RhsArgs<T>& args, int mem, int f) : a(args), up(args.up, mem, f) {
+    const int64_t ms = a.up.bt.mstride, sc = a.up.g.sc;
+    const int vslot = f <= 3 ? f - 1 : 3;  // u^_{f-1} for the momentum, q^ for the energy
+    uhat = member_ptr(a.uhat, mem, ms) + 2 * vslot * sc;
+    force = a.force ? member_ptr(a.force, mem, ms) + 2 * vslot * sc : nullptr;
+    eta = T(a.eta[mem]);
+    induction = f >= 4 && f <= 6;
+  }
+  __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u0, cx<T> a0, int kx, int ky, int kz) const {
     const T k2 = T(kx * kx + ky * ky + kz * kz);
     if (induction) {
       // MHD4 resistive term: - eta |k|^2 B^
-      R = cfma(-(eta * k2), u, R);
+      R = cfma(-(eta * k2), up.at_u() ? u0 : ld(up.state, off), R);
     } else {
       // viscous force mu lap u, and mu lap(|u|^2/2) in the energy
       if (a.mu != 0.0) R = cfma(-(T(a.mu) * k2), ld(uhat, off), R);
       if (a.force) R = cadd(R, ld(force, off));
     }
-    if (rout) {
-      st(rout, off, R);
-    } else {
-      cx<T> inc = cscale(R, ac);
-      if (use_prev) inc = cfma(ap, rp, inc);
-      st(state, off, cfma(dt, inc, u));
-      st(rprev, off, R);
-    }
+    up.apply(off, R, u0, a0);
   }
 };
 
-// One entry of Eq. MHD1 in spectral form, R_rho = -i k . m^, with the density's
-// AB2 update U_rho += dt (a_cur R + a_prev R_prev), R_prev <- R, or the store of
-// R into rout.
+// One entry of Eq. MHD1 in spectral form, R_rho = -i k . m^, and its update.
 template <typename T>
-__device__ __forceinline__ void rho_entry(const RhoArgs<T>& a, int mem, int64_t idx, int kx, int ky, int kz) {
-  const int64_t ms = a.bt.mstride, sc = a.g.sc;
-  T* const state = member_ptr(a.state, mem, ms);
+__device__ __forceinline__ void rho_entry(const UpdateArgs<T>& a, int mem, int64_t idx, int kx, int ky, int kz) {
+  const int64_t sc = a.g.sc;
+  const T* const state = member_ptr(a.state, mem, a.bt.mstride);
   const cx<T> mx = ld(state, sc + idx), my = ld(state, 2 * sc + idx), mz = ld(state, 3 * sc + idx);
+  const Update<T> up(a, mem, 0);
+  const cx<T> u0 = up.old_u(idx), a0 = up.old_acc(idx);
   const cx<T> d = cfma(T(kz), mz, cfma(T(ky), my, cscale(mx, T(kx))));
-  const cx<T> R = ctimes_mi(d);
-  if (a.rout) {
-    st(member_ptr(a.rout, mem, ms), idx, R);
-    return;
-  }
-  T* const rprev = member_ptr(a.rprev, mem, ms);
-  cx<T> inc = cscale(R, T(a.a_cur[mem]));
-  if (a.a_prev[mem] != 0.0) inc = cfma(T(a.a_prev[mem]), ld(rprev, idx), inc);
-  st(state, idx, cfma(T(a.dt[mem]), inc, ld(state, idx)));
-  st(rprev, idx, R);
+  up.apply(idx, ctimes_mi(d), u0, a0);
 }
 
-// One entry of a frozen field of a kinematic run (rho, m, E: R = 0).  The update
-// U += dt (a_cur 0 + a_prev R_prev), R_prev <- 0 changes nothing once the history is
-// zero (it is not where a run continues from another's checkpoint), so a steady
-// step only reads the history.
+// One entry of a frozen field of a kinematic run (rho, m, E): the update with R = 0.
+// It changes nothing once the history is zero (which it is not where a run
+// continues from another's checkpoint), so a steady AB2 step only reads the
+// history; the stage sums and last stages of the other schemes add nothing.
 constexpr int kFrozenFields = 5;
 __host__ __device__ constexpr int frozen_field(int i) { return i < 4 ? i : 7; }
-template <typename T, class Args>
-__device__ __forceinline__ void frozen_entry(const Args& a, int mem, int i, int64_t idx) {
-  const int64_t ms = a.bt.mstride, at = frozen_field(i) * a.g.sc + idx;
-  const cx<T> zero = mk<T>(0, 0);
-  if (a.rout) {
-    st(member_ptr(a.rout, mem, ms), at, zero);
-    return;
-  }
-  T* const rprev = member_ptr(a.rprev, mem, ms);
-  if (a.a_prev[mem] != 0.0) {
-    const cx<T> p = ld(rprev, at);
-    if (p.x == T(0) && p.y == T(0)) return;
-    T* const state = member_ptr(a.state, mem, ms);
-    st(state, at, cfma(T(a.dt[mem]), cfma(T(a.a_prev[mem]), p, zero), ld(state, at)));
-  }
-  st(rprev, at, zero);
+template <typename T>
+__device__ __forceinline__ void frozen_entry(const UpdateArgs<T>& a, int mem, int i, int64_t idx) {
+  const Update<T> up(a, mem, frozen_field(i));
+  if (up.op == UP_RK_MID || up.op == UP_LAST) return;
+  const cx<T> zero = mk<T>(0, 0), a0 = up.old_acc(idx);
+  if (up.op == UP_AB2 && up.use_prev && a0.x == T(0) && a0.y == T(0)) return;
+  up.apply(idx, zero, up.old_u(idx), a0);
 }
 
 // ------------------------------------------------------------------ k_zfwd_rhs
@@ -471,7 +480,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
   const int c0 = (tf.tile - mem * ZT) * C;
   constexpr int64_t LS = NCOLS;             // plane stride of a compact spectrum (kz)
   constexpr int64_t LSZ = Pitch<T, N>::Z;  // plane stride of I_z (z)
-  const int64_t ms = a.bt.mstride;
+  const int64_t ms = a.up.bt.mstride;
   const RhsMember<T> M(a, mem, f);
 
   // Output (i, r) of this thread's last-pass slots: compact index, or -1 for
@@ -504,8 +513,8 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
     int kx, ky, kz;
     const int64_t idx = out_index(i, r, kx, ky, kz);
     if (idx < 0) return;
-    u_pre[i][r] = M.old_state(idx);
-    r_pre[i][r] = M.old_rhs(idx);
+    u_pre[i][r] = M.up.old_u(idx);
+    r_pre[i][r] = M.up.old_acc(idx);
   };
   auto load_all_old = [&] {
 #pragma unroll

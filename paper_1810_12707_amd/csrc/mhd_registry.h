@@ -26,7 +26,7 @@ struct Kern {
   // grids count one workgroup per (member, field, kx)
   void (*zyinv)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
   void (*yzfwd)(const ColArgs<T>&, int nmem, hipStream_t) = nullptr;
-  void (*strain_rho)(const ColArgs<T>&, const RhoArgs<T>&, int nmem, hipStream_t) = nullptr;
+  void (*strain_rho)(const ColArgs<T>&, const UpdateArgs<T>&, int nmem, hipStream_t) = nullptr;
   void (*yzrhs)(const RhsArgs<T>&, int nfrozen, int nmem, hipStream_t) = nullptr;
   void (*row)(int mode, const RowArgs<T>&, dim3, hipStream_t) = nullptr;
   // resident workgroups per CU of a row-pass mode (persistent grid sizing)

@@ -189,7 +189,7 @@ __global__ void __launch_bounds__((slab_threads<T, N, MX>())) k_yzfwd(const ColA
 // overwrites it.
 template <typename T, int N, bool MX>
 __global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
-    k_strain_rho(const ColArgs<T> a, const RhoArgs<T> q) {
+    k_strain_rho(const ColArgs<T> a, const UpdateArgs<T> q) {
   using SL = Slab<T, N, MX>;
   constexpr int NT = SL::NT, NA = kTeams * NT;
   __shared__ cx<T> buf[kTeams][SL::SZ];
@@ -246,27 +246,27 @@ __global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
   const int tid = threadIdx.x, team = __builtin_amdgcn_readfirstlane(tid / NT), ttid = tid - team * NT;
   const SlabItem it = slab_item<SL::NH>(a.nf + nfrozen);
   if (it.f >= a.nf) {
-    for (int e = tid; e < NE; e += NA) frozen_entry<T>(a, it.m, it.f - a.nf, (int64_t)e * SL::NHP + it.kx);
+    for (int e = tid; e < NE; e += NA) frozen_entry<T>(a.up, it.m, it.f - a.nf, (int64_t)e * SL::NHP + it.kx);
     return;
   }
   const int f = it.f + a.f0;
   const OutSpec& A = a.A[f];
   const OutSpec& Z = a.Z[f];
-  // the state and the previous right-hand side, in flight during the transforms
+  // the state and the history, in flight during the transforms
   const RhsMember<T> M(a, it.m, f);
   cx<T> u[CNT], rp[CNT];
 #pragma unroll
   for (int i = 0; i < CNT; ++i) {
     const int e = tid + i * NA;
     const int64_t off = (int64_t)e * SL::NHP + it.kx;
-    u[i] = e < NE ? M.old_state(off) : mk<T>(0, 0);
-    rp[i] = e < NE ? M.old_rhs(off) : mk<T>(0, 0);
+    u[i] = e < NE ? M.up.old_u(off) : mk<T>(0, 0);
+    rp[i] = e < NE ? M.up.old_acc(off) : mk<T>(0, 0);
   }
   load_twiddles<T, typename SL::PL, NA>(stw, a.tw, tid);
   // a team without a term of its own repeats A's first (its result is not read)
   const int src = team == 2 ? (Z.nterms > 0 ? Z.t[0].src : A.t[0].src) : A.t[team < A.nterms ? team : 0].src;
   cx<T>* const own = buf[team];
-  SL::yfwd(own, stw, ttid, member_ptr(a.flux[src], it.m, a.bt.mstride), it.kx, T(0.5),
+  SL::yfwd(own, stw, ttid, member_ptr(a.flux[src], it.m, a.up.bt.mstride), it.kx, T(0.5),
            [&](int z, int y, cx<T> val) { own[z * SL::P + y] = val; });
   __syncthreads();
   SL::template fft<-1, SL::NB, SL::P, 1, true>(
