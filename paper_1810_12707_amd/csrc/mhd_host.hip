@@ -40,38 +40,39 @@ Registry& registry() {
 
 // ------------------------------------------------------------------ reductions
 
-// One launch for both record sets of the diagnostics.  Block q reduces
-// column q of p1[n1][nq1] into out1[q] for q < nq1, else column q - nq1 of
-// p2[n2][nq2] into out2[q - nq1].  Thread t takes records t, t + 256, ... with
-// a Neumaier sum (or a NaN-propagating max when bit q of max_mask is set; the
-// mask applies to the first set), and the 256 (sum, compensation) pairs are
-// combined pairwise in a fixed tree.  Deterministic for given record counts.
-__device__ __forceinline__ void two_sum_into(double& s, double& c, double x) {
-  const double t = s + x;
-  if (fabs(s) >= fabs(x)) c += (s - t) + x;
-  else c += (x - t) + s;
-  s = t;
-}
+// Error-free sum as in neumaier_add, and the reduction of record sets: set i is
+// part[nrec][nq], block q of the set's nq blocks reduces column q into out[q].
+// Thread t takes records t, t + 256, ... with a Neumaier sum (or a
+// NaN-propagating max when bit q of max_mask is set), and the 256 (sum,
+// compensation) pairs are combined pairwise in a fixed tree.  Deterministic for
+// given record counts.
+struct ReduceSet {
+  const double* part;
+  double* out;
+  int64_t nrec;
+  int32_t nq;
+  uint32_t max_mask;
+};
+constexpr int kReduceSets = 3;
+struct ReduceArgs {
+  ReduceSet set[kReduceSets];
+};
 
-__global__ void __launch_bounds__(kThreads)
-k_reduce(const double* __restrict__ p1, int64_t n1, int nq1, unsigned max_mask, const double* __restrict__ p2,
-         int64_t n2, int nq2, double* __restrict__ out1, double* __restrict__ out2) {
+__global__ void __launch_bounds__(kThreads) k_reduce(const ReduceArgs a) {
   __shared__ double s_s[kThreads];
   __shared__ double s_c[kThreads];
-  const bool first = (int)blockIdx.x < nq1;
-  const int q = first ? (int)blockIdx.x : (int)blockIdx.x - nq1;
-  const double* part = first ? p1 : p2;
-  const int64_t nrec = first ? n1 : n2;
-  const int nq = first ? nq1 : nq2;
+  int i = 0, q = blockIdx.x;
+  while (i + 1 < kReduceSets && q >= a.set[i].nq) q -= a.set[i++].nq;
+  const ReduceSet& S = a.set[i];
   const int tid = threadIdx.x;
-  const bool is_max = first && ((max_mask >> q) & 1u);
+  const bool is_max = (S.max_mask >> (q & 31)) & 1u;
   double s = 0.0, c = 0.0;
-  for (int64_t r = tid; r < nrec; r += kThreads) {
-    const double x = part[r * nq + q];
+  for (int64_t r = tid; r < S.nrec; r += kThreads) {
+    const double x = S.part[r * S.nq + q];
     if (is_max) {
       if (!(x <= s)) s = x;
     } else {
-      two_sum_into(s, c, x);
+      neumaier_add(s, c, x);
     }
   }
   s_s[tid] = s;
@@ -82,18 +83,15 @@ k_reduce(const double* __restrict__ p1, int64_t n1, int nq1, unsigned max_mask, 
       if (is_max) {
         if (!(s_s[tid + w] <= s_s[tid])) s_s[tid] = s_s[tid + w];
       } else {
-        double a = s_s[tid], ca = s_c[tid] + s_c[tid + w];
-        two_sum_into(a, ca, s_s[tid + w]);
-        s_s[tid] = a;
-        s_c[tid] = ca;
+        double x = s_s[tid], cx_ = s_c[tid] + s_c[tid + w];
+        neumaier_add(x, cx_, s_s[tid + w]);
+        s_s[tid] = x;
+        s_c[tid] = cx_;
       }
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    const double r = is_max ? s_s[0] : s_s[0] + s_c[0];
-    (first ? out1 : out2)[q] = r;
-  }
+  if (tid == 0) S.out[q] = is_max ? s_s[0] : s_s[0] + s_c[0];
 }
 
 // The density right-hand side and update (rho_entry), one thread per compact
@@ -333,14 +331,16 @@ __global__ void __launch_bounds__(kThreads) k_tracer_push(const Point4<T>* __res
 // Per block: raw shell sums sum |u^|^2 and sum |B^|^2 and sum |k.u^|^2 in LDS
 // (FP64 LDS atomics: the order of additions inside a block is not fixed, so
 // a block's sums are reproducible to FP64 rounding), written to
-// part[b][2 nsh + 1] and reduced over blocks by k_reduce.
-constexpr int kSpecBlocks = 256;
+// part[b][2 nsh + 1] and reduced over blocks by k_reduce.  The divergence sum
+// (one bin for every entry: all lanes of a wave on one address) is kept per thread.
+constexpr int kSpecBlocks = 1024;
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_spectra(const T* __restrict__ uh, const T* __restrict__ bh, Geo g,
                                                      int nsh, double* __restrict__ part) {
-  extern __shared__ double bins[];  // 2 nsh + 1
+  extern __shared__ double bins[];  // 2 nsh, then 2 kThreads of reduction scratch
   const int nb = 2 * nsh + 1;
-  for (int i = threadIdx.x; i < nb; i += kThreads) bins[i] = 0.0;
+  for (int i = threadIdx.x; i < 2 * nsh; i += kThreads) bins[i] = 0.0;
+  double th = 0.0, thc = 0.0;
   __syncthreads();
   const int64_t plane = (int64_t)g.nb * g.nhp;
   for (int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x; idx < g.sc;
@@ -369,42 +369,50 @@ __global__ void __launch_bounds__(kThreads) k_spectra(const T* __restrict__ uh, 
       atomicAdd(&bins[s], w * a);
       atomicAdd(&bins[nsh + s], w * b);
     }
-    atomicAdd(&bins[2 * nsh], w * (dr * dr + di * di));
+    neumaier_add(th, thc, w * (dr * dr + di * di));
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nb; i += kThreads) part[(int64_t)blockIdx.x * nb + i] = bins[i];
+  const double t = block_sum_comp(th, thc, bins + 2 * nsh, threadIdx.x);  // begins with a barrier
+  for (int i = threadIdx.x; i < 2 * nsh; i += kThreads) part[(int64_t)blockIdx.x * nb + i] = bins[i];
+  if (threadIdx.x == 0) part[(int64_t)blockIdx.x * nb + 2 * nsh] = t;
 }
 
-// Per-thread Neumaier sums of d^2 and d^3 over a real field d[n3] (grid-stride);
-// thread t of block b writes its compensated pair sums to part[(b T + t)][2].
+// Neumaier sums of d^2 and d^3 over a real field d[n3] (grid-stride per thread,
+// compensated tree over the block); block b writes part[b][2].
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_moments(const T* __restrict__ d, int64_t n3, double* __restrict__ part) {
+  __shared__ double red[2 * kThreads];
   double s2 = 0.0, c2 = 0.0, s3 = 0.0, c3 = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n3; i += (int64_t)gridDim.x * kThreads) {
     const double v = double(d[i]);
-    two_sum_into(s2, c2, v * v);
-    two_sum_into(s3, c3, v * v * v);
+    neumaier_add(s2, c2, v * v);
+    neumaier_add(s3, c3, v * v * v);
   }
-  const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  part[2 * r] = s2 + c2;
-  part[2 * r + 1] = s3 + c3;
+  const double m2 = block_sum_comp(s2, c2, red, threadIdx.x);
+  const double m3 = block_sum_comp(s3, c3, red, threadIdx.x);
+  if (threadIdx.x == 0) {
+    part[2 * (int64_t)blockIdx.x] = m2;
+    part[2 * (int64_t)blockIdx.x + 1] = m3;
+  }
 }
 
 // Spectral sums over the compact B^ (half spectrum: kx > 0 modes count twice):
 // sum Re(J^ . conj B^)/|k|^2, sum |i k.B^|^2, sum |J^|^2 with J^ = i k x B^.
+// Grid-stride with a Neumaier sum per thread, so that at most kDiagBlocks records
+// are left to reduce.
+constexpr int kDiagBlocks = 1024;
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 k_spec_diag(const T* __restrict__ bx, const T* __restrict__ by, const T* __restrict__ bz, Geo g,
             double* __restrict__ part) {
-  __shared__ double s[kThreads];
+  __shared__ double red[2 * kThreads];
   const int tid = threadIdx.x;
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + tid;
-  double q[kSpecQ] = {0.0, 0.0, 0.0};
+  double q[kSpecQ] = {0.0, 0.0, 0.0}, qc[kSpecQ] = {0.0, 0.0, 0.0};
   const int64_t plane = (int64_t)g.nb * g.nhp;
-  const int lz = (int)(idx / plane);
-  const int rem = (int)(idx - (int64_t)lz * plane);
-  const int ly = rem / g.nhp, kx = rem - ly * g.nhp;
-  if (idx < g.sc && kx < g.nh) {  // padding columns hold no data and are not read
+  for (int64_t idx = (int64_t)blockIdx.x * kThreads + tid; idx < g.sc; idx += (int64_t)gridDim.x * kThreads) {
+    const int lz = (int)(idx / plane);
+    const int rem = (int)(idx - (int64_t)lz * plane);
+    const int ly = rem / g.nhp, kx = rem - ly * g.nhp;
+    if (kx >= g.nh) continue;  // padding columns hold no data and are not read
     const int kz = lz <= g.K ? lz : lz - g.nb;
     const int ky = ly <= g.K ? ly : ly - g.nb;
     const double w = kx == 0 ? 1.0 : 2.0;
@@ -418,20 +426,15 @@ k_spec_diag(const T* __restrict__ bx, const T* __restrict__ by, const T* __restr
     const double k2 = double(kx) * kx + double(ky) * ky + double(kz) * kz;
     // Re(i c . conj B) = -(Im c . Re B) + (Re c . Im B)
     const double jb = -(cxi * Xr + cyi * Yr + czi * Zr) + (cxr * Xi + cyr * Yi + czr * Zi);
-    q[SQ_HM] = k2 > 0 ? w * jb / k2 : 0.0;
+    neumaier_add(q[SQ_HM], qc[SQ_HM], k2 > 0 ? w * jb / k2 : 0.0);
     const double dr = kx * Xr + ky * Yr + kz * Zr, di = kx * Xi + ky * Yi + kz * Zi;
-    q[SQ_DIVB2] = w * (dr * dr + di * di);
-    q[SQ_J2] = w * (cxr * cxr + cxi * cxi + cyr * cyr + cyi * cyi + czr * czr + czi * czi);
+    neumaier_add(q[SQ_DIVB2], qc[SQ_DIVB2], w * (dr * dr + di * di));
+    neumaier_add(q[SQ_J2], qc[SQ_J2],
+                 w * (cxr * cxr + cxi * cxi + cyr * cyr + cyi * cyi + czr * czr + czi * czi));
   }
   for (int i = 0; i < kSpecQ; ++i) {
-    __syncthreads();
-    s[tid] = q[i];
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-      if (tid < w) s[tid] += s[tid + w];
-      __syncthreads();
-    }
-    if (tid == 0) part[(int64_t)blockIdx.x * kSpecQ + i] = s[0];
+    const double r = block_sum_comp(q[i], qc[i], red, tid);
+    if (tid == 0) part[(int64_t)blockIdx.x * kSpecQ + i] = r;
   }
 }
 
@@ -572,14 +575,13 @@ Layout make_layout(const Geo& g, size_t tsize) {
   L.iz = take(std::max(12 * (size_t)g.iz, n_fused_iy(g.n) * (size_t)g.iy) * cplx);
   L.iy = take(16 * (size_t)g.iy * cplx);
   const size_t rows = (size_t)g.n * g.n / 2;
-  const size_t spec_blocks = (size_t)((g.sc + kThreads - 1) / kThreads);
   L.part = take(rows * kDiagQ * sizeof(double));
-  L.spart = take(spec_blocks * kSpecQ * sizeof(double));
+  L.spart = take((size_t)kDiagBlocks * kSpecQ * sizeof(double));
   L.status = take((size_t)kStatusSlots * 2 * sizeof(double));
   L.res = take(kResWords * sizeof(double));
   L.hash = take(sizeof(uint64_t));
   const size_t nbins = 2 * (size_t)spectrum_shells(g.K) + 1;
-  L.shpart = take(std::max(nbins * kSpecBlocks, (size_t)2 * kSpecBlocks * kThreads) * sizeof(double));
+  L.shpart = take(nbins * kSpecBlocks * sizeof(double));
   L.shres = take((nbins + 2) * sizeof(double));
   L.total = off;
   return L;
@@ -913,6 +915,42 @@ struct Engine {
   // Outputs of phase A: u^ (3), and q^ = D F[|u|^2/2] with the viscous-force variant.
   int na() const { return (c->p.flags & MHD_FLAG_VISC_LAPLACIAN) ? 4 : 3; }
 
+  // u^ (and q^) = D F[m / rho] of U for a diagnostic: phase A, fused on small grids.
+  void velocity_spectra(T* U) {
+    if (!k.zyinv) {
+      phase_a(U);
+      return;
+    }
+    const T* zi[4];
+    OutSpec sp[4];
+    for (int f = 0; f < 4; ++f) {
+      zi[f] = spec_field(U, f);
+      sp[f] = copy_spec(f, inv_n3());
+    }
+    inverse_zy(4, zi, 4, sp);
+    fused_velocity();
+    fused_velocity_spectra();
+  }
+
+  // Fused passes: rho and m in the I_y slots 0-3 -> u (and q) in the I_z slots, which
+  // these passes leave free, as I_y fields; and from there to u^ (and q^).
+  void fused_velocity() {
+    RowArgs<T> r = row_args();
+    set_in(r, 0);
+    r.out0 = iz(0);
+    r.out_stride = g.iy;
+    r.nf = na();
+    k.row(RM_XA, r, row_grid(RM_XA), c->stream);
+  }
+  void fused_velocity_spectra() {
+    ColArgs<T> a = col_args(PK_ZFWD, na());
+    for (int f = 0; f < na(); ++f) {
+      a.in[f] = iz(0) + 2 * (size_t)f * g.iy;
+      a.out[f] = spec_field(uhat(), f);
+    }
+    k.yzfwd(a, ms.n, c->stream);
+  }
+
   // Phase A: u^ = D F[m / rho] from the state U.
   void phase_a(T* U) {
     const T* zi[4];
@@ -1143,13 +1181,7 @@ struct Engine {
       a.spec[8 + f] = sp[9 + f];
     }
     k.zyinv(a, ms.n, c->stream);
-    // u (and q) into the I_z slots, which the fused passes leave free, as I_y fields
-    RowArgs<T> ra = row_args();
-    set_in(ra, 0);
-    ra.out0 = iz(0);
-    ra.out_stride = g.iy;
-    ra.nf = na();
-    k.row(RM_XA, ra, row_grid(RM_XA), c->stream);
+    fused_velocity();
     launch_force(U);
     a = col_args(PK_ZINV, 5);
     for (int f = 0; f < 3; ++f) a.in[4 + f] = iz(0) + 2 * (size_t)f * g.iy;
@@ -1158,14 +1190,7 @@ struct Engine {
       a.spec[f] = sp[4 + f];
     }
     k.strain_rho(a, up, ms.n, c->stream);
-    if (na() == 4) {  // the viscous-force variant needs u^ and q^ themselves
-      a = col_args(PK_ZFWD, 4);
-      for (int f = 0; f < 4; ++f) {
-        a.in[f] = iz(0) + 2 * (size_t)f * g.iy;
-        a.out[f] = spec_field(uhat(), f);
-      }
-      k.yzfwd(a, ms.n, c->stream);
-    }
+    if (na() == 4) fused_velocity_spectra();  // the viscous-force variant needs u^ and q^ themselves
     k.row(RM_XB, flux_args(record_status), row_grid(RM_XB), c->stream);
     RhsArgs<T> q = rhs_args(up);
     for (int f = 0; f < 12; ++f) q.flux[f] = iy(f);
@@ -1227,15 +1252,21 @@ struct Engine {
     r.partials = part();
     const dim3 grid = row_grid(RM_XDIAG);  // one partial record per workgroup (<= n^2/2)
     k.row(RM_XDIAG, r, grid, c->stream);
-    const int sblocks = (int)((g.sc + kThreads - 1) / kThreads);
+    const int sblocks = (int)std::min<int64_t>((g.sc + kThreads - 1) / kThreads, kDiagBlocks);
     hipLaunchKernelGGL((k_spec_diag<T>), dim3(sblocks), dim3(kThreads), 0, c->stream, spec_field(U, 4),
                        spec_field(U, 5), spec_field(U, 6), g, spart());
-    const unsigned maxmask = (1u << DQ_DIVB_MAX) | (1u << DQ_CFL_MAX);
-    hipLaunchKernelGGL(k_reduce, dim3(kDiagQ + kSpecQ), dim3(kThreads), 0, c->stream, part(), (int64_t)grid.x,
-                       kDiagQ, maxmask, spart(), (int64_t)sblocks, kSpecQ, res(), res() + 16);
-    // the steps' status slots: FP64 max of the signal speeds, sum of the non-finite counts
-    hipLaunchKernelGGL(k_reduce, dim3(2), dim3(kThreads), 0, c->stream, status(), (int64_t)kStatusSlots, 2, 1u,
-                       status(), (int64_t)0, 0, res() + kResStatus, res() + kResStatus);
+    // the two record sets, and the steps' status slots: FP64 max of the signal
+    // speeds, sum of the non-finite counts
+    reduce({part(), res(), (int64_t)grid.x, kDiagQ, (1u << DQ_DIVB_MAX) | (1u << DQ_CFL_MAX)},
+           {spart(), res() + 16, sblocks, kSpecQ, 0u}, {status(), res() + kResStatus, kStatusSlots, 2, 1u});
+  }
+
+  void reduce(const ReduceSet& a, const ReduceSet& b = ReduceSet(), const ReduceSet& d = ReduceSet()) {
+    ReduceArgs r;
+    r.set[0] = a;
+    r.set[1] = b;
+    r.set[2] = d;
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)(a.nq + b.nq + d.nq)), dim3(kThreads), 0, c->stream, r);
   }
 };
 
@@ -2001,11 +2032,11 @@ int mhd_spectra(mhd_ctx* c, double* h_eu, double* h_eb, double* h_mom) {
   double* shres = reinterpret_cast<double*>(c->ws + c->L.shres);
   int rc = with_engine(c, [&](auto& e) {
     using T = std::remove_pointer_t<decltype(e.state())>;
-    e.phase_a(e.state());  // u^ = D F[m / rho] of the current state
-    hipLaunchKernelGGL((k_spectra<T>), dim3(kSpecBlocks), dim3(kThreads), nb * sizeof(double), c->stream,
+    e.velocity_spectra(e.state());  // u^ = D F[m / rho] of the current state
+    const int sb = (int)std::min<int64_t>((g.sc + kThreads - 1) / kThreads, kSpecBlocks);
+    hipLaunchKernelGGL((k_spectra<T>), dim3(sb), dim3(kThreads), (2 * nsh + 2 * kThreads) * sizeof(double), c->stream,
                        e.uhat(), e.spec_field(e.state(), 4), g, nsh, shpart);
-    hipLaunchKernelGGL(k_reduce, dim3(nb), dim3(kThreads), 0, c->stream, shpart, (int64_t)kSpecBlocks, nb, 0u,
-                       shpart, (int64_t)0, 0, shres, shres);
+    e.reduce({shpart, shres, sb, nb, 0u});
     // d = du_x/dx = F^-1[i k_x u^_x] on the grid, then its second and third moments
     const T* zi[1] = {e.uhat()};
     OutSpec sp[1] = {spec({term(0, 0, e.inv_n3())})};
@@ -2017,9 +2048,9 @@ int mhd_spectra(mhd_ctx* c, double* h_eu, double* h_eb, double* h_mom) {
     r.nf = 1;
     e.set_in(r, 0);
     e.k.row(RM_XINV_REAL, r, e.row_grid(RM_XINV_REAL), c->stream);
-    hipLaunchKernelGGL((k_moments<T>), dim3(kSpecBlocks), dim3(kThreads), 0, c->stream, real, g.n3, shpart);
-    hipLaunchKernelGGL(k_reduce, dim3(2), dim3(kThreads), 0, c->stream, shpart, (int64_t)kSpecBlocks * kThreads, 2,
-                       0u, shpart, (int64_t)0, 0, shres + nb, shres + nb);
+    const int mb = (int)std::min<int64_t>((g.n3 + kThreads - 1) / kThreads, kSpecBlocks);
+    hipLaunchKernelGGL((k_moments<T>), dim3(mb), dim3(kThreads), 0, c->stream, real, g.n3, shpart);
+    e.reduce({shpart, shres + nb, mb, 2, 0u});
     return check_launch(c, "mhd_spectra");
   });
   if (rc != MHD_OK) return rc;
