@@ -62,8 +62,8 @@ enum {
 
 /* Working precision (mhd_params.precision) and real-field element types
  * (dtype arguments take MHD_FP64 or MHD_FP32 only).  MHD_MIXED stores and
- * computes in FP32 but runs every radix-16 FFT stage that goes LDS to LDS as
- * a matrix product on the MFMA units: the DFT matrix and the data are split
+ * computes in FP32 but runs the radix-16 FFT stages of its y and z passes (from
+ * n = 48) as matrix products on the MFMA units: the DFT matrix and the data are split
  * into BF16 high and low parts and three products are accumulated in FP32
  * (the low*low product is dropped); twiddles stay FP32.  Real fields and
  * compact spectra of an MHD_MIXED context are FP32. */

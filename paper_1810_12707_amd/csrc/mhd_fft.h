@@ -8,11 +8,11 @@
 // is needed.  Lanes are assigned to butterflies batch-fastest (column tiles,
 // unit-stride LDS access across adjacent columns) or butterfly-fastest (rows).
 //
-// A plan (PlanT) is the list of radices.  In a mixed-precision plan
-// (MX = true) every radix-16 pass that runs LDS to LDS is a matrix product on
-// the MFMA units: the 16-point DFT of 16 butterflies at once is the real
-// 32 x 32 matrix [[Re W, -Im W], [Im W, Re W]] times the 32 x 16 matrix of their
-// (Re, Im) inputs; W and the inputs are each split into BF16 high and low parts
+// A plan (PlanT) is the list of radices.  In a mixed-precision plan (MX = true,
+// the column passes of the mixed path) the last pass, of radix 16, is a matrix
+// product on the MFMA units: the 16-point DFT of 16 butterflies at once is the
+// real 32 x 32 matrix [[Re W, -Im W], [Im W, Re W]] times the 32 x 16 matrix of
+// their (Re, Im) inputs; W and the inputs are each split into BF16 high and low parts
 // (hi = RNE(x), lo = RNE(x - hi)) and Y = W_hi X_hi + W_hi X_lo + W_lo X_hi is
 // accumulated in FP32 by v_mfma_f32_16x16x32_bf16 (the lo*lo term, about 2^-16
 // relative, is dropped).  Twiddles stay FP32 on the VALU.
@@ -275,18 +275,16 @@ template <int R, int NS, int S, typename X> __device__ __forceinline__ void dft_
 
 template <int NN, bool MXX, int... Rs> struct PlanT {
   static constexpr int N = NN;
-  static constexpr bool MX = MXX;  // radix-16 LDS passes on MFMA (split BF16 x 3)
+  static constexpr bool MX = MXX;  // radix-16 last pass on MFMA (split BF16 x 3)
   static constexpr int r[] = {Rs...};
   static constexpr int np = sizeof...(Rs);
 };
 
-// FP32 / FP64 plans (VALU only) and mixed plans.  A mixed plan ends in a
-// radix-16 stage: the last Stockham pass writes each butterfly onto its own
-// inputs, so the MFMA products run group by group with no registers held
-// across a barrier.  Radix-16 stages before it would (a middle pass must
-// hold every group's products until all groups have read), and a radix-16
-// first pass, which reads from global memory, stays on the VALU; measured
-// fastest: small radices first, one radix-16 MFMA stage last.
+// FP32 / FP64 plans (VALU only) and the plans of the mixed path's column passes.
+// A mixed plan ends in its one radix-16 stage: the last Stockham pass writes each
+// butterfly onto its own inputs, so the MFMA products run group by group with no
+// registers held across a barrier.  A radix-16 first pass, which reads from global
+// memory, stays on the VALU.
 template <int N, bool MX> struct PlanSel;
 #define MHD_PLAN(NN, ...) template <> struct PlanSel<NN, false> { using type = PlanT<NN, false, __VA_ARGS__>; };
 #define MHD_PLAN_MX(NN, ...) template <> struct PlanSel<NN, true> { using type = PlanT<NN, true, __VA_ARGS__>; };
@@ -319,11 +317,6 @@ MHD_PLAN(384, 6, 8, 8)
 MHD_PLAN(512, 8, 8, 8)
 MHD_PLAN(768, 8, 8, 4, 3)
 MHD_PLAN(1024, 8, 8, 4, 4)
-MHD_PLAN_MX(8, 8)
-MHD_PLAN_MX(12, 4, 3)
-MHD_PLAN_MX(16, 4, 4)
-MHD_PLAN_MX(24, 8, 3)
-MHD_PLAN_MX(32, 2, 16)
 MHD_PLAN_MX(48, 3, 16)
 MHD_PLAN_MX(64, 4, 16)
 MHD_PLAN_MX(96, 2, 3, 16)
@@ -342,14 +335,6 @@ template <class PL> constexpr int plan_ns(int p) {
   int ns = 1;
   for (int i = 0; i < p; ++i) ns *= PL::r[i];
   return ns;
-}
-
-// A mixed plan with a radix-16 stage before its last (an LDS-to-LDS MFMA pass).
-template <class PL> constexpr bool mid_mfma() {
-  if (!PL::MX) return false;
-  for (int i = 0; i + 1 < PL::np; ++i)
-    if (PL::r[i] == 16) return true;
-  return false;
 }
 
 template <class PL> constexpr bool plan_ok() {
@@ -586,8 +571,7 @@ __device__ __forceinline__ void load_pass_twiddles(cx<T>* t, const cx<T>* tw, in
 // faster-running index's range the slots differ only in the slower index, by
 // a constant step; that is written out so that LDS addresses become one base
 // plus immediate offsets, which saves the address registers of every slot and
-// radix element (at N = 512 the mixed-precision flux pass spilled without
-// it).  Without LIN the compiler keeps one precomputed address per element,
+// radix element.  Without LIN the compiler keeps one precomputed address per element,
 // and its reads stay single ds_read_b64s.
 template <int NB, int NBF, int NT, int MAP, bool LIN = true>
 __device__ __forceinline__ void slot_map(int tid, int i, int& b, int& j) {
@@ -722,123 +706,38 @@ __device__ __forceinline__ void dft16_operands(int lane, bf16x8& a0h, bf16x8& a0
   }
 }
 
-// Radix-16 Stockham pass on the MFMA units (FP32 data, split BF16 x 3).  Each
-// wave takes 16 butterflies at a time: lane (n = lane mod 16, g = lane / 16)
-// reads elements 4 g .. 4 g + 3 of butterfly n, twiddles them in FP32 and
-// splits their real and imaginary parts into the B operand (k = 2 r + c, as
-// in dft16_operands); after the products lane (n, g) holds outputs
-// q = 4g .. 4g+3 of butterfly n.
-template <class PL, int NB, int NT, int ES, int BS, int S, int P, int MAP, int PADSH>
-__device__ __forceinline__ void fft_pass_mfma(float2* buf, const float2* tw, int tid, int b_act) {
-  static_assert(!wave_map<MAP>(), "MFMA passes use the workgroup lane maps");
-  constexpr int N = PL::N;
-  constexpr int R = 16;
-  constexpr int NS = plan_ns<PL>(P);
-  constexpr int NBF = N / R;
-  constexpr int TOT = NB * NBF;
-  constexpr int NGRP = (TOT + 15) / 16;
-  constexpr int NW = NT / 64;
-  constexpr int GPW = (NGRP + NW - 1) / NW;  // groups per wave
-  const int lane = tid & 63, wv = tid >> 6;
-  const int n = lane & 15, g = lane >> 4;
-  bf16x8 a0h, a0l, a1h, a1l;
-  dft16_operands<S>(lane, a0h, a0l, a1h, a1l);
-  floatx4 yr[GPW], yi[GPW];
-#pragma unroll
-  for (int s = 0; s < GPW; ++s) {
-    const int grp = wv + s * NW;
-    const int w = grp * 16 + n;
-    int b, j;
-    lane_map<NB, NBF, MAP>(w, b, j);
-    const bool ok = grp < NGRP && w < TOT && b < b_act;
-    const int k = j % NS;
-    bf16x8 xh, xl;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 4 * g + e;
-      float2 x = ok ? buf[lds_at<ES, BS, PADSH, PL, P>(b, j + r * NBF)] : make_float2(0.f, 0.f);
-      if constexpr (NS > 1) {
-        if (r > 0) {
-          const float2 tv = tw[tw_offset<PL>(P) + (r - 1) * NS + k];
-          x = (S < 0) ? cmul(x, tv) : cmulc(x, tv);
-        }
-      }
-      const __bf16 hr = (__bf16)x.x, hi = (__bf16)x.y;
-      xh[2 * e] = hr;
-      xl[2 * e] = (__bf16)(x.x - (float)hr);
-      xh[2 * e + 1] = hi;
-      xl[2 * e + 1] = (__bf16)(x.y - (float)hi);
-    }
-    floatx4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
-    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0h, xh, c0, 0, 0, 0);
-    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0h, xl, c0, 0, 0, 0);
-    c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0l, xh, c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1h, xh, c1, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1h, xl, c1, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1l, xh, c1, 0, 0, 0);
-    yr[s] = c0;
-    yi[s] = c1;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < GPW; ++s) {
-    const int grp = wv + s * NW;
-    const int w = grp * 16 + n;
-    int b, j;
-    lane_map<NB, NBF, MAP>(w, b, j);
-    if (grp < NGRP && w < TOT && b < b_act) {
-      const int k = j % NS;
-      const int d = (j / NS) * NS * R + k;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int q = 4 * g + t;
-        buf[lds_at<ES, BS, PADSH, PL, P + 1>(b, d + q * NS)] = make_float2(yr[s][t], yi[s][t]);
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Last radix-16 pass on the MFMA units.  In the last Stockham pass every
-// butterfly writes its outputs onto its own input positions (d = j), so the
-// groups need no common barrier: each group of 16 butterflies is read,
-// multiplied and handed to store(s, t, b, pos, value) (s = group slot of this
-// wave, t = 0..3 the lane's four outputs) before the next group is read.
-// store() may write the LDS positions in place.
-template <class PL, int NB, int NT, int ES, int BS, int S, int P, int MAP, int PADSH, class Store, bool SLOTS = false,
-          int UNR = 1>
+// Last radix-16 pass on the MFMA units (FP32 data, split BF16 x 3).  Each wave
+// takes 16 butterflies at a time: lane (n = lane mod 16, g = lane / 16) reads
+// elements 4 g .. 4 g + 3 of butterfly n, twiddles them in FP32 and splits their
+// real and imaginary parts into the B operand (k = 2 r + c, as in dft16_operands);
+// after the products it holds outputs q = 4g .. 4g+3 of butterfly n.  In the last
+// Stockham pass every butterfly's outputs belong at its own input positions, so
+// the groups need no common barrier: each is read, multiplied and handed to
+// store(s, t, b, pos, value) (s = group slot of this wave, t = 0..3 the lane's
+// four outputs) before the next is read.
+template <class PL, int NB, int NT, int ES, int BS, int S, int P, int MAP, int PADSH, int UNR, class Store>
 __device__ __forceinline__ void fft_pass_mfma_last(const float2* buf, const float2* tw, int tid, int b_act,
                                                    Store&& store) {
+  static_assert(MAP == 0, "MFMA passes run in the column kernels");
   constexpr int N = PL::N;
   constexpr int R = 16;
   constexpr int NS = plan_ns<PL>(P);
-  static_assert(NS * R == N, "the in-place MFMA pass must be the last pass");
+  static_assert(NS * R == N, "the MFMA pass must be the last pass");
   constexpr int NBF = N / R;
   constexpr int TOT = NB * NBF;
   constexpr int NGRP = (TOT + 15) / 16;
   constexpr int NW = NT / 64;
-  // groups per wave: workgroup maps deal the groups round-robin over the
-  // waves; wave maps give each wave the groups of its own sequences
-  constexpr int GPW = wave_map<MAP>() ? (seqs_per_wave<NB, NT>() * NBF + 15) / 16 : (NGRP + NW - 1) / NW;
+  constexpr int GPW = (NGRP + NW - 1) / NW;  // groups per wave, dealt round-robin over the waves
   const int lane = tid & 63, wv = tid >> 6;
   const int n = lane & 15, g = lane >> 4;
   bf16x8 a0h, a0l, a1h, a1l;
   dft16_operands<S>(lane, a0h, a0l, a1h, a1l);
   auto group = [&](int s) {
     int b, j;
-    bool ok;
-    if constexpr (wave_map<MAP>()) {
-      const int u = s * 16 + n;  // butterfly index over the wave's sequences
-      const int fl = u / NBF;
-      j = u - fl * NBF;
-      b = fl * NW + wv;
-      ok = fl < seqs_per_wave<NB, NT>() && b < b_act;
-    } else {
-      const int grp = wv + s * NW;
-      const int w = grp * 16 + n;
-      lane_map<NB, NBF, MAP>(w, b, j);
-      ok = grp < NGRP && w < TOT && b < b_act;
-    }
+    const int grp = wv + s * NW;
+    const int w = grp * 16 + n;
+    lane_map<NB, NBF, MAP>(w, b, j);
+    const bool ok = grp < NGRP && w < TOT && b < b_act;
     bf16x8 xh, xl;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -866,18 +765,10 @@ __device__ __forceinline__ void fft_pass_mfma_last(const float2* buf, const floa
       for (int t = 0; t < 4; ++t) store(s, t, b, j + (4 * g + t) * NS, make_float2(c0[t], c1[t]));
     }
   };
-  // The groups run one after another.  The loop is unrolled completely when
-  // the store keeps its results in registers indexed by the group slot;
-  // otherwise by UNR groups (1, 2 or 4, per kernel by measurement), which
-  // overlaps one group's LDS latency and MFMA chain with the next group's
-  // work at the cost of registers.
-  if constexpr (SLOTS) {
-#pragma unroll
-    for (int s = 0; s < GPW; ++s) group(s);
-  } else if constexpr (UNR >= 4) {
-#pragma unroll 4
-    for (int s = 0; s < GPW; ++s) group(s);
-  } else if constexpr (UNR == 2) {
+  // The groups run one after another, the loop unrolled by UNR (1 or 2, by
+  // measurement): two overlap one group's LDS latency and MFMA chain with the
+  // next group's work at the cost of registers.
+  if constexpr (UNR == 2) {
 #pragma unroll 2
     for (int s = 0; s < GPW; ++s) group(s);
   } else {
@@ -950,39 +841,21 @@ __device__ __forceinline__ void fft_last_valu(cx<T>* buf, const cx<T>* tw, int t
   }
 }
 
-template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int P, int MAP = 0, int PADSH = 0>
-__device__ __forceinline__ void fft_pass(cx<T>* buf, const cx<T>* tw, int tid, int b_act) {
-  if constexpr (PL::MX && PL::r[P] == 16) {
-    static_assert(sizeof(T) == 4, "the mixed path works on FP32 data");
-    fft_pass_mfma<PL, NB, NT, ES, BS, S, P, MAP, PADSH>(reinterpret_cast<float2*>(buf),
-                                                        reinterpret_cast<const float2*>(tw), tid, b_act);
-  } else {
-    fft_pass_valu<T, PL, NB, NT, ES, BS, S, P, MAP, PADSH>(buf, tw, tid, b_act);
-  }
-}
-
-// All passes LDS to LDS; the last pass runs in place (butterfly by butterfly
-// on the VALU, group by group on the MFMA units) and is followed by a barrier.
-// KEEP > 0: only positions <= KEEP and >= N - KEEP of the result are wanted
-// (the others may be left stale).
+// All passes LDS to LDS (VALU plans); the last pass runs in place, butterfly by
+// butterfly, and is followed by a barrier.  KEEP > 0: only positions <= KEEP and
+// >= N - KEEP of the result are wanted (the others may be left stale).
 template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP = 0, int PADSH = 0, int KEEP = 0,
-          int UNR = 1, int P = 0>
+          int P = 0>
 __device__ __forceinline__ void lds_fft(cx<T>* buf, const cx<T>* tw, int tid, int b_act) {
-  static_assert(plan_ok<PL>(), "radix plan does not multiply to N");
+  static_assert(plan_ok<PL>() && !PL::MX, "radix plan does not multiply to N, or is not a VALU plan");
   if constexpr (P < PL::np) {
-    if constexpr (PL::MX && PL::r[P] == 16 && P == PL::np - 1 && P > 0) {
-      float2* fb = reinterpret_cast<float2*>(buf);
-      auto st = [&](int, int, int b, int pos, float2 v) { fb[lds_at<ES, BS, PADSH, PL, P>(b, pos)] = v; };
-      fft_pass_mfma_last<PL, NB, NT, ES, BS, S, P, MAP, PADSH, decltype(st)&, false, UNR>(
-          fb, reinterpret_cast<const float2*>(tw), tid, b_act, st);
-      pass_sync<MAP>();
-    } else if constexpr (P == PL::np - 1 && P > 0) {
+    if constexpr (P == PL::np - 1 && P > 0) {
       fft_last_valu<T, PL, NB, NT, ES, BS, S, MAP, PADSH, KEEP, true>(buf, tw, tid, b_act,
                                                                        [](int, int, int, int, cx<T>) {});
       pass_sync<MAP>();
     } else {
-      fft_pass<T, PL, NB, NT, ES, BS, S, P, MAP, PADSH>(buf, tw, tid, b_act);
-      lds_fft<T, PL, NB, NT, ES, BS, S, MAP, PADSH, KEEP, UNR, P + 1>(buf, tw, tid, b_act);
+      fft_pass_valu<T, PL, NB, NT, ES, BS, S, P, MAP, PADSH>(buf, tw, tid, b_act);
+      lds_fft<T, PL, NB, NT, ES, BS, S, MAP, PADSH, KEEP, P + 1>(buf, tw, tid, b_act);
     }
   }
 }
@@ -991,7 +864,7 @@ __device__ __forceinline__ void lds_fft(cx<T>* buf, const cx<T>* tw, int tid, in
 template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP, int PADSH, int P>
 __device__ __forceinline__ void fft_mid_passes(cx<T>* buf, const cx<T>* tw, int tid, int b_act) {
   if constexpr (P < PL::np - 1) {
-    fft_pass<T, PL, NB, NT, ES, BS, S, P, MAP, PADSH>(buf, tw, tid, b_act);
+    fft_pass_valu<T, PL, NB, NT, ES, BS, S, P, MAP, PADSH>(buf, tw, tid, b_act);
     fft_mid_passes<T, PL, NB, NT, ES, BS, S, MAP, PADSH, P + 1>(buf, tw, tid, b_act);
   }
 }
@@ -1005,19 +878,14 @@ template <class PL, int NB, int NT, int MAP = 1> struct FirstPass {
   static constexpr int CNT = slot_count<NB, NBF, NT, MAP>();
 };
 
-// Per-thread shape of the last pass: outputs are handed to store(i, r, ...)
-// for CNT slots i of R outputs r.  VALU last pass: slot i is the thread's i-th
-// butterfly and r its R outputs.  MFMA radix-16 last pass: slot i is the
-// wave's i-th group of 16 butterflies and r the lane's four outputs.
+// Per-thread shape of a VALU plan's last pass: outputs are handed to
+// store(i, r, ...) for the thread's CNT butterflies i of R outputs r.
 template <class PL, int NB, int NT> struct LastPass {
-  static constexpr int RL = PL::r[PL::np - 1];
-  static constexpr bool MFMA = PL::MX && RL == 16 && PL::np > 1;
-  static constexpr int NBF = PL::N / RL;
+  static_assert(!PL::MX, "VALU plans");
+  static constexpr int R = PL::r[PL::np - 1];
+  static constexpr int NBF = PL::N / R;
   static constexpr int TOT = NB * NBF;
-  static constexpr int NGRP = (TOT + 15) / 16;
-  static constexpr int NW = NT / 64;
-  static constexpr int CNT = MFMA ? (NGRP + NW - 1) / NW : (TOT + NT - 1) / NT;
-  static constexpr int R = MFMA ? 4 : RL;
+  static constexpr int CNT = (TOT + NT - 1) / NT;
 };
 
 // (sequence b, position pos) of output slot (i, r) of this thread in the last
@@ -1025,21 +893,11 @@ template <class PL, int NB, int NT> struct LastPass {
 template <class PL, int NB, int NT, int MAP>
 __device__ __forceinline__ bool last_slot(int tid, int i, int r, int& b, int& pos) {
   using LP = LastPass<PL, NB, NT>;
-  constexpr int NS = PL::N / LP::RL;
   int j;
-  if constexpr (LP::MFMA) {
-    const int lane = tid & 63, wv = tid >> 6, n = lane & 15, g = lane >> 4;
-    const int grp = wv + i * LP::NW;
-    const int w = grp * 16 + n;
-    lane_map<NB, LP::NBF, MAP>(w, b, j);
-    pos = j + (4 * g + r) * NS;
-    return grp < LP::NGRP && w < LP::TOT;
-  } else {
-    const int w = tid + i * NT;
-    lane_map<NB, LP::NBF, MAP>(w, b, j);
-    pos = j + r * NS;
-    return LP::TOT % NT == 0 || w < LP::TOT;
-  }
+  const int w = tid + i * NT;
+  lane_map<NB, LP::NBF, MAP>(w, b, j);
+  pos = j + r * LP::NBF;
+  return LP::TOT % NT == 0 || w < LP::TOT;
 }
 
 // First pass from values already in registers (v[i][r] = element j + r*NBF of
@@ -1074,28 +932,20 @@ __device__ __forceinline__ void fft_first_regs(cx<T>* buf, cx<T> (&v)[FirstPass<
 
 // Middle passes (LDS to LDS) and the last pass, whose outputs go to
 // store(i, r, b, pos, value) with pos = j + r N/R for the thread's i-th
-// butterfly j.  On the VALU the last pass computes straight into registers;
-// an MFMA last pass writes LDS and the same (i, r, pos) are then read back.
+// butterfly j (an MFMA last pass: as fft_pass_mfma_last hands them out).
 // INPLACE: a VALU last pass writes its outputs back to the LDS positions it
-// read instead of calling store (which must then write LDS position pos of
-// sequence b, as it is still called by an MFMA last pass).
-template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP, int PADSH, bool SLOTS = false,
-          bool INPLACE = false, int UNR = 1, class Store>
+// read instead of calling store.
+template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP, int PADSH, bool INPLACE = false,
+          int UNR = 1, class Store>
 __device__ __forceinline__ void fft_rest(cx<T>* buf, const cx<T>* tw, int tid, int b_act, Store&& store) {
   constexpr int NP = PL::np;
   if constexpr (NP > 1) {
     fft_mid_passes<T, PL, NB, NT, ES, BS, S, MAP, PADSH, 1>(buf, tw, tid, b_act);
     constexpr int PLAST = NP - 1;
-    constexpr int R = PL::r[PLAST];
-    if constexpr (PL::MX && R == 16) {
-      auto st2 = [&](int i, int r, int b, int pos, float2 v) {
-        cx<T> vv;
-        vv.x = v.x;
-        vv.y = v.y;
-        store(i, r, b, pos, vv);
-      };
-      fft_pass_mfma_last<PL, NB, NT, ES, BS, S, PLAST, MAP, PADSH, decltype(st2)&, SLOTS, UNR>(
-          reinterpret_cast<const float2*>(buf), reinterpret_cast<const float2*>(tw), tid, b_act, st2);
+    if constexpr (PL::MX && PL::r[PLAST] == 16) {
+      static_assert(sizeof(T) == 4 && !INPLACE, "the mixed path works on FP32 data");
+      fft_pass_mfma_last<PL, NB, NT, ES, BS, S, PLAST, MAP, PADSH, UNR>(
+          reinterpret_cast<const float2*>(buf), reinterpret_cast<const float2*>(tw), tid, b_act, store);
     } else {
       fft_last_valu<T, PL, NB, NT, ES, BS, S, MAP, PADSH, 0, INPLACE>(buf, tw, tid, b_act, store);
     }
@@ -1109,7 +959,7 @@ __device__ __forceinline__ void fft_rest(cx<T>* buf, const cx<T>* tw, int tid, i
 // so their memory requests are in flight together.  For one-pass plans the
 // inputs go straight from load() through the DFT to store().  The LDS buffer
 // may be reused after this returns only past a __syncthreads().
-template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP = 0, int PADSH = 0, bool SLOTS = false, class Load,
+template <typename T, class PL, int NB, int NT, int ES, int BS, int S, int MAP = 0, int PADSH = 0, class Load,
           class Store>
 __device__ __forceinline__ void fft_reg(cx<T>* buf, const cx<T>* tw, int tid, int b_act, Load&& load,
                                         Store&& store) {
@@ -1126,7 +976,7 @@ __device__ __forceinline__ void fft_reg(cx<T>* buf, const cx<T>* tw, int tid, in
     for (int r = 0; r < FP::R; ++r) v[i][r] = ok ? load(b, j + r * FP::NBF) : mk<T>(0, 0);
   }
   fft_first_regs<T, PL, NB, NT, ES, BS, S, MAP, PADSH>(buf, v, tid, b_act, store);
-  fft_rest<T, PL, NB, NT, ES, BS, S, MAP, PADSH, SLOTS>(buf, tw, tid, b_act, store);
+  fft_rest<T, PL, NB, NT, ES, BS, S, MAP, PADSH>(buf, tw, tid, b_act, store);
 }
 
 // Item order of a persistent grid of G workgroups over `total` items: the

@@ -564,7 +564,7 @@ Layout make_layout(const Geo& g, size_t tsize) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   const size_t cplx = 2 * tsize;
-  L.tw = take(2 * (size_t)g.n * cplx);  // the tables of the default and of the alternative schedule's plan
+  L.tw = take(2 * (size_t)g.n * cplx);  // two tables (ctx_setup)
   L.state = take(8 * (size_t)g.sc * cplx);
   L.rprev = take(8 * (size_t)g.sc * cplx);
   L.uhat = take(4 * (size_t)g.sc * cplx);
@@ -691,7 +691,9 @@ struct Engine {
   T* tstate() const { return at(c->L.tstate); }
   T* trhs() const { return at(c->L.trhs); }
   T* force() const { return at(c->L.force); }
+  // twiddles of the column passes, and of the row, z-RHS and fused passes
   T* tw() const { return at(c->L.tw) + ((c->p.flags & MHD_FLAG_SCHEDULE_ALT) ? 2 * (size_t)g.n : 0); }
+  T* tw_valu() const { return c->p.precision == MHD_MIXED ? at(c->L.tw) + 2 * (size_t)g.n : tw(); }
   T* iz(int slot) const { return at(c->L.iz) + 2 * (size_t)slot * g.iz; }
   T* iy(int slot) const { return at(c->L.iy) + 2 * (size_t)slot * g.iy; }
   T* spec_field(T* base, int f) const { return base + 2 * (size_t)f * g.sc; }
@@ -775,6 +777,13 @@ struct Engine {
     return a;
   }
 
+  // the same for a fused launch
+  ColArgs<T> fused_args(int nout) const {
+    ColArgs<T> a = col_args(PK_ZINV, nout);
+    a.tw = tw_valu();
+    return a;
+  }
+
   // Launch a column pass; ins/outs are per-launch slot lists.  Persistent
   // grid: resident workgroups, capped by the item count.
   void col(int kind, int nout, const T* const* ins, int nin, T* const* outs, const OutSpec* specs) {
@@ -819,7 +828,7 @@ struct Engine {
       a.nu[m] = ms.nu[m];
       a.eta[m] = ms.eta[m];
     }
-    a.tw = tw();
+    a.tw = tw_valu();
     a.g = g;
     a.bt = batch();
     return a;
@@ -851,7 +860,7 @@ struct Engine {
   // Inverse z and y passes into the I_y slots 0, 1, ...
   void inverse_zy(int nout, const T* const* ins, int nin, const OutSpec* specs) {
     if (k.zyinv) {
-      ColArgs<T> a = col_args(PK_ZINV, nout);
+      ColArgs<T> a = fused_args(nout);
       for (int i = 0; i < nin; ++i) a.in[i] = ins[i];
       for (int f = 0; f < nout; ++f) {
         a.out[f] = iy(f);
@@ -879,7 +888,7 @@ struct Engine {
     set_out(r, 0);
     k.row(RM_XFWD_REAL, r, row_grid(RM_XFWD_REAL), c->stream);
     if (k.yzfwd) {
-      ColArgs<T> a = col_args(PK_ZFWD, nf);
+      ColArgs<T> a = fused_args(nf);
       for (int f = 0; f < nf; ++f) { a.in[f] = iy(f); a.out[f] = spec_field(dst, f); }
       k.yzfwd(a, ms.n, c->stream);
       return;
@@ -943,7 +952,7 @@ struct Engine {
     k.row(RM_XA, r, row_grid(RM_XA), c->stream);
   }
   void fused_velocity_spectra() {
-    ColArgs<T> a = col_args(PK_ZFWD, na());
+    ColArgs<T> a = fused_args(na());
     for (int f = 0; f < na(); ++f) {
       a.in[f] = iz(0) + 2 * (size_t)f * g.iy;
       a.out[f] = spec_field(uhat(), f);
@@ -1136,7 +1145,7 @@ struct Engine {
     q.A[7] = spec({term(6, X, -1), term(7, Y, -1)});  // MHD3: -i k . F^E
     q.Z[7] = spec({term(8, -1, -1)});
     q.up = up;
-    q.tw = tw();
+    q.tw = tw_valu();
     q.uhat = uhat();
     q.mu = (c->p.flags & MHD_FLAG_VISC_LAPLACIAN) ? c->p.nu : 0.0;
     q.f0 = kinematic() ? 4 : 1;
@@ -1165,7 +1174,7 @@ struct Engine {
     // rho, m, B, E and J (the strains, slots 8-12, follow from u)
     OutSpec sp[12];
     flux_input_specs(sp);
-    ColArgs<T> a = col_args(PK_ZINV, 11);
+    ColArgs<T> a = fused_args(11);
     for (int f = 0; f < 4; ++f) {
       a.in[f] = spec_field(U, 4 + f);  // B^, E^
       a.in[4 + f] = spec_field(U, f);  // rho^, m^
@@ -1183,7 +1192,7 @@ struct Engine {
     k.zyinv(a, ms.n, c->stream);
     fused_velocity();
     launch_force(U);
-    a = col_args(PK_ZINV, 5);
+    a = fused_args(5);
     for (int f = 0; f < 3; ++f) a.in[4 + f] = iz(0) + 2 * (size_t)f * g.iy;
     for (int f = 0; f < 5; ++f) {
       a.out[f] = iy(8 + f);
@@ -1342,7 +1351,8 @@ static int ctx_setup(mhd_ctx* c, const mhd_params* p, void* d_workspace, size_t 
   c->t = 0.0;
   const int rg = ctx_geometry(c);
   if (rg != MHD_OK) return rg;
-  // the plans' twiddle tables, default schedule first (a context may switch)
+  // the plans' twiddle tables: the default schedule's, then the alternative one's
+  // (a context may switch) or, on the mixed path, the VALU plan's
   const Registry& reg = registry();
   const int n = p->n;
   double host[2 * 2 * 1024];
@@ -1350,8 +1360,10 @@ static int ctx_setup(mhd_ctx* c, const mhd_params* p, void* d_workspace, size_t 
   std::memset(host, 0, bytes);
   if (is_fp32(p->precision)) {
     float* h = reinterpret_cast<float*>(host);
-    (p->precision == MHD_MIXED ? reg.mx : reg.f32)[n].twiddles(h);
-    if (p->precision == MHD_FP32 && reg.f32s1[n].row) reg.f32s1[n].twiddles(h + 2 * n);
+    const Kern<float>& k = p->precision == MHD_MIXED ? reg.mx[n] : reg.f32[n];
+    k.twiddles(h);
+    if (p->precision == MHD_MIXED) k.twiddles_valu(h + 2 * n);
+    else if (reg.f32s1[n].row) reg.f32s1[n].twiddles(h + 2 * n);
   } else {
     reg.f64[n].twiddles(host);
   }

@@ -48,29 +48,29 @@ ColClass col_class(int dir, int maxt, bool z) {
   if (maxt <= 1) return z ? col_occ<T, N, 1, 1, MX, true>() : col_occ<T, N, 1, 1, MX, false>();
   return z ? col_occ<T, N, 1, kMaxTerms, MX, true>() : col_occ<T, N, 1, kMaxTerms, MX, false>();
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void rhs(const RhsArgs<T>& a, dim3 g, hipStream_t s) {
-  hipLaunchKernelGGL((k_zfwd_rhs<T, N, MX>), g, dim3(rhs_threads<T, N, MX>()), 0, s, a);
+  hipLaunchKernelGGL((k_zfwd_rhs<T, N>), g, dim3(rhs_threads<T, N>()), 0, s, a);
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void zyinv(const ColArgs<T>& a, int nmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_zyinv<T, N, MX>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
-                     dim3(slab_threads<T, N, MX>()), 0, s, a);
+  hipLaunchKernelGGL((k_zyinv<T, N>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
+                     dim3(slab_threads<T, N>()), 0, s, a);
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void yzfwd(const ColArgs<T>& a, int nmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_yzfwd<T, N, MX>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
-                     dim3(slab_threads<T, N, MX>()), 0, s, a);
+  hipLaunchKernelGGL((k_yzfwd<T, N>), dim3((unsigned)(nmem * a.nout * Band<N>::NH)),
+                     dim3(slab_threads<T, N>()), 0, s, a);
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void strain_rho(const ColArgs<T>& a, const UpdateArgs<T>& q, int nmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_strain_rho<T, N, MX>), dim3((unsigned)(nmem * (a.nout + 1) * Band<N>::NH)),
-                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, q);
+  hipLaunchKernelGGL((k_strain_rho<T, N>), dim3((unsigned)(nmem * (a.nout + 1) * Band<N>::NH)),
+                     dim3(kTeams * slab_threads<T, N>()), 0, s, a, q);
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void yzrhs(const RhsArgs<T>& a, int nfrozen, int nmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_yzrhs<T, N, MX>), dim3((unsigned)(nmem * (a.nf + nfrozen) * Band<N>::NH)),
-                     dim3(kTeams * slab_threads<T, N, MX>()), 0, s, a, nfrozen);
+  hipLaunchKernelGGL((k_yzrhs<T, N>), dim3((unsigned)(nmem * (a.nf + nfrozen) * Band<N>::NH)),
+                     dim3(kTeams * slab_threads<T, N>()), 0, s, a, nfrozen);
 }
 // fn<MODE>() for a run-time row mode
 template <typename F>
@@ -85,41 +85,46 @@ void with_row_mode(int mode, F&& fn) {
     default: break;
   }
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 void row(int mode, const RowArgs<T>& a, dim3 g, hipStream_t s) {
   with_row_mode(mode, [&](auto m) {
     constexpr int M = decltype(m)::value;
-    hipLaunchKernelGGL((k_row<T, N, M, MX>), g, dim3(row_threads<T, N, M, MX>()), 0, s, a);
+    hipLaunchKernelGGL((k_row<T, N, M>), g, dim3(row_threads<T, N, M>()), 0, s, a);
   });
 }
-template <typename T, int N, bool MX>
+template <typename T, int N>
 int row_occupancy(int mode) {
   int blocks = 0;
   hipError_t e = hipSuccess;
   with_row_mode(mode, [&](auto m) {
     constexpr int M = decltype(m)::value;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, M, MX>, row_threads<T, N, M, MX>(), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_row<T, N, M>, row_threads<T, N, M>(), 0);
   });
   return (e == hipSuccess && blocks > 0) ? blocks : 1;
 }
 
+// MX: the mixed path.  Its column passes run the radix-16 plans; the row passes,
+// the z-RHS pass and the small grids run the FP32 kernels, which measured faster
+// there (256: flux pass 512 -> 361 us, z-RHS 318 -> 235; 512: 4496 -> 2695 and
+// 2329 -> 2031) and are more accurate.
 template <typename T, int N, bool MX>
 Kern<T> make() {
   Kern<T> k;
   k.n = N;
-  k.rhs_width = rhs_tile<T, N, MX>();
+  k.rhs_width = rhs_tile<T, N>();
   k.twiddles = make_twiddles<T, PlanOf<N, MX>>;
+  k.twiddles_valu = make_twiddles<T, PlanOf<N>>;
   k.col_inv = col_inv<T, N, MX>;
   k.col_fwd = col_fwd<T, N, MX>;
-  k.rhs = rhs<T, N, MX>;
+  k.rhs = rhs<T, N>;
   if constexpr (N <= kSlabMax && MHD_SCHED == 0) {
-    k.zyinv = zyinv<T, N, MX>;
-    k.yzfwd = yzfwd<T, N, MX>;
-    k.strain_rho = strain_rho<T, N, MX>;
-    k.yzrhs = yzrhs<T, N, MX>;
+    k.zyinv = zyinv<T, N>;
+    k.yzfwd = yzfwd<T, N>;
+    k.strain_rho = strain_rho<T, N>;
+    k.yzrhs = yzrhs<T, N>;
   }
-  k.row = row<T, N, MX>;
-  k.row_occupancy = row_occupancy<T, N, MX>;
+  k.row = row<T, N>;
+  k.row_occupancy = row_occupancy<T, N>;
   k.col_class = col_class<T, N, MX>;
   return k;
 }
@@ -134,7 +139,7 @@ void MHD_CAT(register_s1_, MHD_N)(Registry& r) { r.f32s1[MHD_N] = make<float, MH
 #else
 void MHD_CAT(register_, MHD_N)(Registry& r) {
   r.f32[MHD_N] = make<float, MHD_N, false>();
-  r.mx[MHD_N] = make<float, MHD_N, true>();
+  r.mx[MHD_N] = make<float, MHD_N, (MHD_N > kSlabMax)>();
 #if MHD_N <= 512
   r.f64[MHD_N] = make<double, MHD_N, false>();
 #endif

@@ -48,39 +48,30 @@ template <typename T, int N> constexpr int col_width() {
 
 // Threads and tile width of the forward-z RHS pass.  It is latency-bound
 // (dependent memory phases per workgroup: the first flux group, the second,
-// the state and history), so it wants many resident waves: FP32 at N >= 256
-// runs one first-pass butterfly per thread, which keeps registers low -- 512
-// threads on 16 columns at N = 256, 1024 threads on 16 columns at N = 512
-// (whole 128-byte row segments; 3% faster than 512 threads on 8), 1024
-// threads on 8 columns at N = 1024 (FP32 228 -> 106 registers, mixed 196 ->
-// 116: four waves per SIMD instead of two, 28.0 -> 21.4 and 35.4 -> 24.0 ms
-// per step), and 512 threads on 8 columns for the mixed path below that.
-// FP64 at N = 512 takes 512 threads on its 8-column tiles, one butterfly
-// each (146 registers instead of 256 with 256 threads, three waves per SIMD
-// instead of one: 6.89 -> 4.35 ms per step).
-// From 384 the same 16-column tiles with 1024 threads (384 FP32 924 -> 890 us,
-// FP64 1985 -> 1656 us).  The mixed path at 256 and FP32 at 192 and 96 take 8
-// columns and 256 threads (more, smaller workgroups: 371 -> 349, 126 -> 102 and
-// 17.3 -> 16.3 us).
-template <typename T, int N, bool MX> constexpr bool rhs_wide() { return sizeof(T) == 4 && N >= 256; }
-template <typename T, int N, bool MX> constexpr int rhs_threads() {
+// the state and history), so it wants many resident waves and whole 128-byte row
+// segments: one first-pass butterfly per thread on 16 columns from N = 256 (512
+// threads; 1024 at 384 and 512: 384 FP32 924 -> 890 us, FP64 1985 -> 1656 us), 8
+// columns and 1024 threads at 1024 (FP32 228 -> 106 registers, four waves per SIMD
+// instead of two: 28.0 -> 21.4 ms).  FP64 at 512 takes 512 threads on its 8-column
+// tiles (146 registers instead of 256 with 256 threads: 6.89 -> 4.35 ms).  FP32 at
+// 192 and 96 take 8 columns and 256 threads (more, smaller workgroups: 126 -> 102
+// and 17.3 -> 16.3 us).
+template <typename T, int N> constexpr bool rhs_wide() { return sizeof(T) == 4 && N >= 256; }
+template <typename T, int N> constexpr int rhs_threads() {
   if (sizeof(T) == 8 && N == 512) return 2 * kThreads;
-  if (!MX && N == 384) return 4 * kThreads;
-  if (sizeof(T) == 4 && ((!MX && N == 512) || N == 1024)) return 4 * kThreads;
-  if (MX && N == 256) return kThreads;
-  return rhs_wide<T, N, MX>() ? 2 * kThreads : kThreads;
+  if (N == 384 || (sizeof(T) == 4 && (N == 512 || N == 1024))) return 4 * kThreads;
+  return rhs_wide<T, N>() ? 2 * kThreads : kThreads;
 }
-template <typename T, int N, bool MX> constexpr int rhs_tile() {
-  if (!MX && N == 384) return 16;
-  if (sizeof(T) == 4 && !MX && N == 512) return 16;
-  if (sizeof(T) == 4 && !MX && (N == 192 || (N == 96 && MHD_SCHED == 0))) return 8;
-  return rhs_wide<T, N, MX>() ? (N == 256 && !MX ? 16 : 8) : col_width<T, N>();
+template <typename T, int N> constexpr int rhs_tile() {
+  if (N == 384 || (sizeof(T) == 4 && (N == 256 || N == 512))) return 16;
+  if (sizeof(T) == 4 && (N == 192 || (N == 96 && MHD_SCHED == 0))) return 8;
+  return rhs_wide<T, N>() ? 8 : col_width<T, N>();
 }
 // Minimum resident waves per SIMD asked of the compiler (register cap).
 // FP32 at 128: seven waves, so that the 1785 workgroups are resident at once.
-template <typename T, int N, bool MX> constexpr int rhs_min_waves() {
-  if (sizeof(T) == 4 && !MX && N == 128 && MHD_SCHED == 0) return 7;
-  return rhs_wide<T, N, MX>() || rhs_threads<T, N, MX>() > kThreads ? 1 : 3;
+template <typename T, int N> constexpr int rhs_min_waves() {
+  if (sizeof(T) == 4 && N == 128 && MHD_SCHED == 0) return 7;
+  return rhs_wide<T, N>() || rhs_threads<T, N>() > kThreads ? 1 : 3;
 }
 
 // Threads and tile width (columns) of the column passes: S = +1 inverse, -1
@@ -349,7 +340,7 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(c
     }
     // mixed plans: one-term passes overlap two MFMA groups (the three-term
     // inverse pass would spill)
-    fft_rest<T, PL, C, NT, C, 1, S, 0, 0, false, false, (MAXT == 1 ? 2 : 1)>(tile, stw, tid, C, store);
+    fft_rest<T, PL, C, NT, C, 1, S, 0, 0, false, (MAXT == 1 ? 2 : 1)>(tile, stw, tid, C, store);
     item = next;
   }
 }
@@ -460,11 +451,11 @@ __device__ __forceinline__ void frozen_entry(const UpdateArgs<T>& a, int mem, in
 
 // ------------------------------------------------------------------ k_zfwd_rhs
 // Flat grid over (member, column tile of (ky, kx), output field), field fastest.
-template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N, MX>())) k_zfwd_rhs(const RhsArgs<T> a) {
-  using PL = PlanOf<N, MX>;
-  constexpr int C = rhs_tile<T, N, MX>();
-  constexpr int NT = rhs_threads<T, N, MX>();
+template <typename T, int N>
+__global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())) k_zfwd_rhs(const RhsArgs<T> a) {
+  using PL = PlanOf<N>;
+  constexpr int C = rhs_tile<T, N>();
+  constexpr int NT = rhs_threads<T, N>();
   constexpr int NH = Band<N>::NH, NHP = Band<N>::NHP, NBB = Band<N>::NB;
   constexpr int NCOLS = NBB * NHP;  // flattened (ky, kx) over the padded pitch
   using LP = LastPass<PL, C, NT>;
@@ -497,15 +488,11 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
     kz = band_k<N>(l);
     return (int64_t)l * LS + col;
   };
-  // The state (for the update, and B^ for the resistive term) and the
-  // previous RHS: FP32 from N = 512 loads them before the transforms, so that
-  // these loads are in flight while the flux groups are transformed (5%
-  // faster).  FP32 at N = 256 (a resident workgroup lost to registers, 4%
-  // slower), the mixed path (its MFMA stage needs the registers: 139-140 ->
-  // 108 without the early loads, two workgroups per CU instead of one,
-  // 0.458 -> 0.372 ms at 256, 3.35 -> 2.59 ms at 512) and the narrow shapes
-  // load them last.
-  constexpr bool PRE = rhs_wide<T, N, MX>() && !MX && N >= 512;
+  // The state (for the update, and B^ for the resistive term) and the history:
+  // FP32 from N = 512 loads them before the transforms, so that these loads are
+  // in flight while the flux groups are transformed (5% faster); the others
+  // after them (FP32 at 256: a resident workgroup lost to registers, 4% slower).
+  constexpr bool PRE = rhs_wide<T, N>() && N >= 512;
   cx<T> u_pre[LP::CNT][LP::R], r_pre[LP::CNT][LP::R];
   auto load_old = [&](int i, int r) {
     u_pre[i][r] = mk<T>(0, 0);
@@ -558,13 +545,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
       const cx<T> xs[2] = {x0, x1};
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        if constexpr (MX) {
-          // branch-free, as in the column passes (faster on the mixed path
-          // only): absent terms have zero factors and a zero second input
-          const T re = ax[t] < 0 ? cf[t] : T(0);
-          const T ck = (ax[t] < 0 ? T(0) : cf[t]) * T(ax[t] == 1 ? ky : kx);
-          v = cfma(ck, ctimes_i(xs[t]), cfma(re, xs[t], v));
-        } else if (t < nt) {
+        if (t < nt) {
           if (ax[t] < 0) {
             v = cfma(cf[t], xs[t], v);
           } else {
@@ -584,7 +565,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N, MX>()), (rhs_min_waves<T, N
         acc[i][r] = cfma(kz, ctimes_i(v), acc[i][r]);
       }
     };
-    fft_reg<T, PL, C, NT, C, 1, -1, 0, 0, true>(tile, stw, tid, C, load, store);
+    fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, load, store);
   }
   // epilogue over this thread's last-pass positions; all its loads go out
   // together, ahead of the first that is used
@@ -720,48 +701,44 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // 55.1 us) or half as many (64, and 128 in FP64 where the registers of two
 // butterflies fit: 20.2 -> 18.5 and 109 -> 89 us; FP32 at 128 would spill).
 // The kinematic pass (eight fields) takes a thread per first-pass butterfly.
-template <typename T, int N, int MODE, bool MX> constexpr int row_threads() {
+template <typename T, int N, int MODE> constexpr int row_threads() {
   if (MODE == RM_XK) {
-    constexpr int w = 8 * (N / PlanOf<N, MX>::r[0]);
+    constexpr int w = 8 * (N / PlanOf<N>::r[0]);
     return w <= 64 ? 64 : (w >= 512 ? 512 : (w + 63) / 64 * 64);
   }
-  if (!MX && MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
-  if (!MX && MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
-  if (sizeof(T) == 4 && !MX && MODE == RM_XA && N == 256) return kThreads / 2;
-  if (!MX && MODE == RM_XA && (N == 64 || N == 128 || (sizeof(T) == 8 && N == 192))) return 64;
+  if (MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
+  if (MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
+  if (sizeof(T) == 4 && MODE == RM_XA && N == 256) return kThreads / 2;
+  if (MODE == RM_XA && (N == 64 || N == 128 || (sizeof(T) == 8 && N == 192))) return 64;
   return (sizeof(T) == 4 && N >= 1024) ? 2 * kThreads : kThreads;
 }
 
-// Register caps of the FP32 row passes (MFMA variant included): two waves per
-// SIMD from N = 256 on (the 512-thread flux passes come out at 128 registers or
-// fewer, four waves per SIMD, which is what their LDS allows).  Left free, the flux pass can take more than 256 registers
-// and then runs one wave per SIMD (the MFMA variant at N = 512 was 1.3x
-// slower so than capped).
-template <typename T, int N, int MODE, bool MX> constexpr int row_min_blocks() {
-  if (sizeof(T) != 4 || row_threads<T, N, MODE, MX>() < kThreads || MODE == RM_XK) return 1;
-  if (!MX && MODE == RM_XB && (N == 512 || N == 384 || N == 256)) return 2;
-  return 2 * kThreads / row_threads<T, N, MODE, MX>();
+// Register caps of the FP32 row passes: two waves per SIMD from N = 256 on (the
+// 512-thread flux passes come out at 128 registers or fewer, four waves per SIMD,
+// which is what their LDS allows).  Left free, a flux pass can take more than 256
+// registers and then runs one wave per SIMD.
+template <typename T, int N, int MODE> constexpr int row_min_blocks() {
+  if (sizeof(T) != 4 || row_threads<T, N, MODE>() < kThreads || MODE == RM_XK) return 1;
+  if (MODE == RM_XB && (N == 512 || N == 384 || N == 256)) return 2;
+  return 2 * kThreads / row_threads<T, N, MODE>();
 }
 
-template <typename T, int N, int MODE, bool MX>
-__global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_blocks<T, N, MODE, MX>()))
+template <typename T, int N, int MODE>
+__global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T, N, MODE>()))
     k_row(const RowArgs<T> a) {
-  using PL = PlanOf<N, MX>;
-  constexpr int NT = row_threads<T, N, MODE, MX>();
+  using PL = PlanOf<N>;
+  constexpr int NT = row_threads<T, N, MODE>();
   constexpr int K = Band<N>::K, PY = Pitch<T, N>::Y;
   constexpr int NH = Band<N>::NH;
   constexpr int NB = RowShape<MODE>::NB;
   // LDS row layout, chosen per pass by measurement.  Linear addressing where
   // the precomputed addresses would push a pass past 256 registers into
-  // spills (the flux pass from N = 512 mixed and N = 1024 FP32, the
-  // diagnostics pass at N = 1024).  The stage swizzle (conflict-free LDS
-  // access, but more address arithmetic) where it measured faster: the FP32
-  // flux pass below N = 512 (3%) and the FP32 velocity pass from N = 512 (2%);
-  // it made the mixed passes slower.  Otherwise one padding slot per 8
-  // elements.
-  constexpr bool LIN = (MODE == RM_XB && N >= (MX ? 512 : 1024)) || (MODE == RM_XDIAG && N >= 1024);
-  constexpr bool SWZ = !MX && !LIN && N % 16 == 0 && N >= 128 &&
-                       ((MODE == RM_XB && N < 512) || (MODE == RM_XA && N >= 512));
+  // spills (the flux and diagnostics passes at N = 1024).  The stage swizzle
+  // (conflict-free LDS access, but more address arithmetic) where it measured
+  // faster: the flux pass below N = 512 (3%) and the velocity pass from N = 512
+  // (2%).  Otherwise one padding slot per 8 elements.
+  constexpr bool LIN = (MODE == RM_XB || MODE == RM_XDIAG) && N >= 1024;
+  constexpr bool SWZ = !LIN && N % 16 == 0 && N >= 128 && ((MODE == RM_XB && N < 512) || (MODE == RM_XA && N >= 512));
   constexpr int PADSH = 3;
   constexpr int LAY = SWZ ? kSwizzle : (PADSH | (LIN ? kLinear : 0));
   // row pitch in LDS: swizzled rows are shifted by 16 elements from row to
@@ -773,20 +750,15 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
   // pointwise stage, which reads every field at one point, is bracketed by
   // barriers.  Used (measured) by the velocity and flux passes from N = 384
   // (12% and 5% faster at 512), at 256, 128 and 64 (with the thread counts of
-  // row_threads), by the one-wave FP64 velocity pass at 192 (94 -> 85 us) and by
-  // the mixed velocity pass from 384, whose last-pass MFMA groups then take the
-  // wave's own butterflies (7%); not at 96 and 192 otherwise (their 12 and 32
-  // first-pass butterflies per field leave lanes of a wave idle: 96 FP32 flux
-  // pass 30.8 -> 35.7 us), by the mixed flux pass (slower) or with fewer fields
-  // than waves.
+  // row_threads) and by the one-wave FP64 velocity pass at 192 (94 -> 85 us); not
+  // at 96 and 192 otherwise (their 12 and 32 first-pass butterflies per field
+  // leave lanes of a wave idle: 96 FP32 flux pass 30.8 -> 35.7 us) or with fewer
+  // fields than waves.
   constexpr bool FLUX = MODE == RM_XB || MODE == RM_XK;  // forms fluxes and the status
-  constexpr bool WAVE = MODE == RM_XK ? !MX && is_pow2(N) && N >= 64 :
-                       (MX ? (MODE == RM_XA && !mid_mfma<PL>()) : (MODE == RM_XA || MODE == RM_XB)) &&
-                       (N >= 384 || (!MX && (N == 256 || N == 128 || N == 64 || (N == 192 && NT == 64)))) &&
-                       NB >= NT / 64;
-  // MFMA groups overlapped in the mixed last pass (measured: the velocity
-  // pass 2, the flux pass 4 at N = 256; the others spill or slow down)
-  constexpr int UNR = MODE == RM_XA ? 2 : ((MODE == RM_XB && N <= 256) ? 4 : 1);
+  constexpr bool WAVE = MODE == RM_XK ? is_pow2(N) && N >= 64
+                                      : (MODE == RM_XA || MODE == RM_XB) &&
+                                            (N >= 384 || N == 256 || N == 128 || N == 64 || (N == 192 && NT == 64)) &&
+                                            NB >= NT / 64;
   constexpr int RMAP = WAVE ? 3 : 1;
   using FP = FirstPass<PL, NB, NT, RMAP>;
   auto at = [](int b, int pos) { return lds_at<1, BS, LAY, PL, 0>(b, pos); };
@@ -971,7 +943,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
       }
       fft_first_regs<T, PL, NB, NT, 1, BS, +1, FM1, LAY, ZROWS>(buf, v, tid, nin, lds_store);
       if (item + gridDim.x < nitems) issue(item + gridDim.x);  // next pair's loads overlap the rest
-      fft_rest<T, PL, NB, NT, 1, BS, +1, RMAP, LAY, false, true, UNR>(buf, stw, tid, nin, lds_store);
+      fft_rest<T, PL, NB, NT, 1, BS, +1, RMAP, LAY, true>(buf, stw, tid, nin, lds_store);
     }
     __syncthreads();
 
@@ -1166,7 +1138,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE, MX>()), (row_min_bloc
 
     if constexpr (MODE == RM_XA || FLUX || MODE == RM_XFWD_REAL) {
       __syncthreads();
-      lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K, UNR>(buf, stw, tid, nout);  // only k <= K and N - k are read
+      lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K>(buf, stw, tid, nout);  // only k <= K and N - k are read
       // unpack: X0[k] = (Z[k] + conj Z[N-k]) / 2, X1[k] = -i (Z[k] - conj Z[N-k]) / 2, k = 0..K,
       // stored doubled (2 X0, 2 X1): the forward y pass that reads these rows
       // applies the 1/2 with its copy coefficient (an exact power-of-two

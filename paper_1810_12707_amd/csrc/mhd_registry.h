@@ -16,7 +16,11 @@ template <typename T>
 struct Kern {
   int n = 0;
   int rhs_width = 0;  // columns per workgroup of the forward-z RHS pass
-  void (*twiddles)(T*) = nullptr;  // fills the plan's twiddle table (at most n complex values)
+  // fill the twiddle tables (at most n complex values each) of the column passes'
+  // plan, and of the plan of the row, z-RHS and fused passes (the same but on the
+  // mixed path)
+  void (*twiddles)(T*) = nullptr;
+  void (*twiddles_valu)(T*) = nullptr;
   // column passes; maxt = largest number of terms of any output spec (1 or 3)
   void (*col_inv)(int maxt, const ColArgs<T>&, dim3, hipStream_t) = nullptr;
   void (*col_fwd)(const ColArgs<T>&, dim3, hipStream_t) = nullptr;
@@ -36,7 +40,7 @@ struct Kern {
 struct Registry {
   Kern<float> f32[1025];
   Kern<double> f64[1025];
-  Kern<float> mx[1025];    // FP32 data, radix-16 stages on MFMA (split BF16 x 3)
+  Kern<float> mx[1025];    // FP32 data, column passes' radix-16 stages on MFMA (split BF16 x 3)
   Kern<float> f32s1[1025];  // FP32, alternative schedule (ensemble sizes)
 };
 

@@ -26,15 +26,15 @@ namespace mhd {
 MHD_SCHED_BEGIN
 
 // Threads of one transform team: one first-pass butterfly each, at most 256.
-template <typename T, int N, bool MX> constexpr int slab_threads() {
-  constexpr int w = N * (N / PlanOf<N, MX>::r[0]);
+template <typename T, int N> constexpr int slab_threads() {
+  constexpr int w = N * (N / PlanOf<N>::r[0]);
   return w >= 256 ? 256 : (w + 63) / 64 * 64;
 }
 constexpr int kTeams = 3;  // transforms side by side in k_strain_rho and k_yzrhs
 
-template <typename T, int N, bool MX> struct Slab {
-  using PL = PlanOf<N, MX>;
-  static constexpr int NT = slab_threads<T, N, MX>();
+template <typename T, int N> struct Slab {
+  using PL = PlanOf<N>;
+  static constexpr int NT = slab_threads<T, N>();
   static constexpr int P = N + 1;  // pitch of a z row
   static constexpr int NB = Band<N>::NB, NH = Band<N>::NH, NHP = Band<N>::NHP;
   static constexpr int PY = Pitch<T, N>::Y;
@@ -112,9 +112,9 @@ __device__ __forceinline__ void add_term(cx<T>& acc, const Term& t, cx<T> x, int
 }
 
 // Inverse z and y passes: compact spectra -> I_y planes.
-template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((slab_threads<T, N, MX>())) k_zyinv(const ColArgs<T> a) {
-  using SL = Slab<T, N, MX>;
+template <typename T, int N>
+__global__ void __launch_bounds__((slab_threads<T, N>())) k_zyinv(const ColArgs<T> a) {
+  using SL = Slab<T, N>;
   __shared__ cx<T> buf[SL::SZ];
   __shared__ cx<T> stw[N];
   const int tid = threadIdx.x;
@@ -159,9 +159,9 @@ __global__ void __launch_bounds__((slab_threads<T, N, MX>())) k_zyinv(const ColA
 
 // Forward y and z passes: I_y planes (row-pass outputs, doubled: halved here) ->
 // compact spectra.
-template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((slab_threads<T, N, MX>())) k_yzfwd(const ColArgs<T> a) {
-  using SL = Slab<T, N, MX>;
+template <typename T, int N>
+__global__ void __launch_bounds__((slab_threads<T, N>())) k_yzfwd(const ColArgs<T> a) {
+  using SL = Slab<T, N>;
   __shared__ cx<T> buf[SL::SZ];
   __shared__ cx<T> stw[N];
   const int tid = threadIdx.x;
@@ -187,10 +187,10 @@ __global__ void __launch_bounds__((slab_threads<T, N, MX>())) k_yzfwd(const ColA
 // against a launch and a pass through memory).  Field a.nout is the density
 // right-hand side and update, which needs m^ before the last pass of the step
 // overwrites it.
-template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
+template <typename T, int N>
+__global__ void __launch_bounds__((kTeams * slab_threads<T, N>()))
     k_strain_rho(const ColArgs<T> a, const UpdateArgs<T> q) {
-  using SL = Slab<T, N, MX>;
+  using SL = Slab<T, N>;
   constexpr int NT = SL::NT, NA = kTeams * NT;
   __shared__ cx<T> buf[kTeams][SL::SZ];
   __shared__ cx<T> stw[N];
@@ -235,10 +235,10 @@ __global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
 // of the up to three fluxes side by side (teams 0, 1: the terms of A_f, team 2:
 // Z_f), forward z of their combinations, and the epilogue of k_zfwd_rhs over all
 // threads.  The nfrozen fields after them are those a kinematic run freezes.
-template <typename T, int N, bool MX>
-__global__ void __launch_bounds__((kTeams * slab_threads<T, N, MX>()))
+template <typename T, int N>
+__global__ void __launch_bounds__((kTeams * slab_threads<T, N>()))
     k_yzrhs(const RhsArgs<T> a, int nfrozen) {
-  using SL = Slab<T, N, MX>;
+  using SL = Slab<T, N>;
   constexpr int NT = SL::NT, NA = kTeams * NT;
   constexpr int NE = SL::NB * SL::NB, CNT = (NE + NA - 1) / NA;  // entries of this kx, per thread
   __shared__ cx<T> buf[kTeams][SL::SZ];

@@ -51,9 +51,9 @@ def class_kernels(n: int) -> dict:
     """Launch classes whose kernel instance is used by that class alone in a
     step (FP32 path): class -> substring of the demangled kernel name."""
     return {
-        "xa": f"k_row<float, {n}, 0, false>",
-        "xb": f"k_row<float, {n}, 1, false>",
-        "zrhs": f"k_zfwd_rhs<float, {n}, false>",
+        "xa": f"k_row<float, {n}, 0",
+        "xb": f"k_row<float, {n}, 1",
+        "zrhs": f"k_zfwd_rhs<float, {n}",
         "rho": "k_rho_rhs<float>",
     }
 
@@ -95,13 +95,14 @@ def per_kernel_kib(path: str, counter: str) -> dict:
 
 
 # Launch classes of one step in launch order, with the kernel each uses
-# ({mx}: false on the FP32 path, true on the mixed path).
+# ({mx}: false on the FP32 path, true on the mixed path, in the column passes;
+# the row and z-RHS passes are the same kernels on both).
 STEP_SEQUENCE = [
     ("zinv_a", "k_col<float, {n}, 1, 1, {mx}, true>"), ("yinv_a", "k_col<float, {n}, 1, 1, {mx}, false>"),
-    ("xa", "k_row<float, {n}, 0, {mx}>"), ("yfwd_a", "k_col<float, {n}, -1, 1, {mx}, false>"),
+    ("xa", "k_row<float, {n}, 0"), ("yfwd_a", "k_col<float, {n}, -1, 1, {mx}, false>"),
     ("zfwd_a", "k_col<float, {n}, -1, 1, {mx}, true>"), ("zinv_b", "k_col<float, {n}, 1, 3, {mx}, true>"),
-    ("yinv_b", "k_col<float, {n}, 1, 1, {mx}, false>"), ("xb", "k_row<float, {n}, 1, {mx}>"),
-    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false>"), ("rho", "k_rho_rhs<float>"), ("zrhs", "k_zfwd_rhs<float, {n}, {mx}>"),
+    ("yinv_b", "k_col<float, {n}, 1, 1, {mx}, false>"), ("xb", "k_row<float, {n}, 1"),
+    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false>"), ("rho", "k_rho_rhs<float>"), ("zrhs", "k_zfwd_rhs<float, {n}"),
 ]
 
 
