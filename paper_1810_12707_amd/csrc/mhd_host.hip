@@ -805,6 +805,8 @@ struct Engine {
     if (blocks < 8) blocks = 8;
     if (blocks > items) blocks = items;
     dim3 grid((unsigned)blocks);
+    const int64_t field = kind == PK_YINV ? g.iy : (kind == PK_ZFWD ? g.sc : g.iz);  // complex values per output
+    a.stream = field * nout * ms.n * 2 * (int64_t)sizeof(T) > kStreamBytes;
     if (inv) k.col_inv(maxt, a, grid, c->stream);
     else k.col_fwd(a, grid, c->stream);
   }

@@ -11,13 +11,24 @@
 namespace mhd {
 namespace {
 
-// Column passes: one instantiation per direction, term count and axis (z or y).
+// Column passes: one instantiation per direction, term count, axis (z or y) and, where
+// a launch chooses, way of storing.
+template <typename T, int N, int S, int MAXT, bool MX, bool Z>
+void col_axis(const ColArgs<T>& a, dim3 g, hipStream_t s) {
+  constexpr ColStream cs = col_stream<N, S, Z>();
+  const dim3 nt(col_threads<T, N, MX, S, MAXT, Z>());
+  if constexpr (cs != CS_NEVER) {
+    if (cs == CS_ALWAYS || a.stream) {
+      hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, Z, true>), g, nt, 0, s, a);
+      return;
+    }
+  }
+  if constexpr (cs != CS_ALWAYS) hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, Z, false>), g, nt, 0, s, a);
+}
 template <typename T, int N, int S, int MAXT, bool MX>
 void col_launch(const ColArgs<T>& a, dim3 g, hipStream_t s) {
-  if (a.kind == PK_ZINV || a.kind == PK_ZFWD)
-    hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, true>), g, dim3(col_threads<T, N, MX, S, MAXT, true>()), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_col<T, N, S, MAXT, MX, false>), g, dim3(col_threads<T, N, MX, S, MAXT, false>()), 0, s, a);
+  if (a.kind == PK_ZINV || a.kind == PK_ZFWD) col_axis<T, N, S, MAXT, MX, true>(a, g, s);
+  else col_axis<T, N, S, MAXT, MX, false>(a, g, s);
 }
 template <typename T, int N, bool MX>
 void col_inv(int maxt, const ColArgs<T>& a, dim3 g, hipStream_t s) {
@@ -28,12 +39,14 @@ template <typename T, int N, bool MX>
 void col_fwd(const ColArgs<T>& a, dim3 g, hipStream_t s) {
   col_launch<T, N, -1, 1, MX>(a, g, s);
 }
-// Tile width and resident workgroups per CU of a column-pass class.
+// Tile width and resident workgroups per CU of a column-pass class (both ways of
+// storing come out at the same registers or within a few).
 template <typename T, int N, int S, int MAXT, bool MX, bool Z>
 ColClass col_occ(void) {
   ColClass c;
   c.width = col_tile<T, N, MX, S, MAXT, Z>();
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c.blocks, k_col<T, N, S, MAXT, MX, Z>,
+  constexpr bool st = col_stream<N, S, Z>() == CS_ALWAYS;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c.blocks, k_col<T, N, S, MAXT, MX, Z, st>,
                                                                     col_threads<T, N, MX, S, MAXT, Z>(), 0);
   if (e != hipSuccess || c.blocks < 1) c.blocks = 1;
   // the 1024-thread tiles at 256: one workgroup per CU also where the registers

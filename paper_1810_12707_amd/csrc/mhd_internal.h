@@ -106,9 +106,14 @@ struct ColArgs {
   const T* tw;          // twiddle table of the plan (make_twiddles)
   int32_t kind;         // PassKind
   int32_t nout;
+  int32_t stream;       // the outputs exceed kStreamBytes
+  int32_t pad;
   Geo g;
   Batch bt;
 };
+// Size of the memory-side cache: a column pass that writes more than this in one
+// launch stores past the caches (k_col).
+constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 
 // What becomes of a right-hand side R = R(U) in the pass that forms it (U: the
 // state it is evaluated at; u: the state a step advances; acc: the AB2 / PC

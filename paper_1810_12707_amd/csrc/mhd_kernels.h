@@ -51,11 +51,10 @@ template <typename T, int N> constexpr int col_width() {
 // the state and history), so it wants many resident waves and whole 128-byte row
 // segments: one first-pass butterfly per thread on 16 columns from N = 256 (512
 // threads; 1024 at 384 and 512: 384 FP32 924 -> 890 us, FP64 1985 -> 1656 us), 8
-// columns and 1024 threads at 1024 (FP32 228 -> 106 registers, four waves per SIMD
-// instead of two: 28.0 -> 21.4 ms).  FP64 at 512 takes 512 threads on its 8-column
-// tiles (146 registers instead of 256 with 256 threads: 6.89 -> 4.35 ms).  FP32 at
-// 192 and 96 take 8 columns and 256 threads (more, smaller workgroups: 126 -> 102
-// and 17.3 -> 16.3 us).
+// columns and 1024 threads at 1024 (FP32 228 -> 106 registers: 28.0 -> 21.4 ms).  FP64
+// at 512 takes 512 threads on its 8-column tiles (146 registers instead of 256 with
+// 256 threads: 6.89 -> 4.35 ms).  FP32 at 192 and 96 take 8 columns and 256 threads
+// (more, smaller workgroups: 126 -> 102 and 17.3 -> 16.3 us).
 template <typename T, int N> constexpr bool rhs_wide() { return sizeof(T) == 4 && N >= 256; }
 template <typename T, int N> constexpr int rhs_threads() {
   if (sizeof(T) == 8 && N == 512) return 2 * kThreads;
@@ -67,9 +66,20 @@ template <typename T, int N> constexpr int rhs_tile() {
   if (sizeof(T) == 4 && (N == 192 || (N == 96 && MHD_SCHED == 0))) return 8;
   return rhs_wide<T, N>() ? 8 : col_width<T, N>();
 }
-// Minimum resident waves per SIMD asked of the compiler (register cap).
-// FP32 at 128: seven waves, so that the 1785 workgroups are resident at once.
+// Both flux groups loaded before the first is transformed, one memory phase instead
+// of two, from N = 512.  With the state and history loaded after the transforms the
+// kernel fits 64 registers there, so that two workgroups of 1024 threads share a CU
+// and one loads while the other transforms (512 FP32: 2032 us with one workgroup of
+// 94 registers -> 1650; capped without the early loads 1787; stored past the caches
+// 1592, 4.6 TB/s; FP64 120 registers, 4022 -> 3290; 1024: 21.4 -> 18.2 ms).  Below,
+// the second group's registers cost resident waves (256 FP32: 213 -> 279, 128: 29 ->
+// 35).
+template <int N> constexpr bool rhs_upfront() { return N >= 512; }
+// Minimum resident waves per SIMD asked of the compiler (register cap).  FP32 from
+// 512: 64 registers, as above (68 uncapped at 1024).  FP32 at 128: seven waves, so
+// that the 1785 workgroups are resident at once.
 template <typename T, int N> constexpr int rhs_min_waves() {
+  if (sizeof(T) == 4 && (N == 512 || N == 1024)) return 8;
   if (sizeof(T) == 4 && N == 128 && MHD_SCHED == 0) return 7;
   return rhs_wide<T, N>() || rhs_threads<T, N>() > kThreads ? 1 : 3;
 }
@@ -125,9 +135,21 @@ template <typename T>
 __device__ __forceinline__ cx<T> ld(const T* base, int64_t idx) {
   return reinterpret_cast<const cx<T>*>(base)[idx];
 }
+// Stores through a two-element vector type: stored as the struct that cx<T> is, a
+// column pass's values took 8-12 more registers (192 FP32: 12-field y pass 87 ->
+// 73 us, step 650 -> 630; 128: 212 -> 208).
+template <typename T> using vec2 = T __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ __forceinline__ void st(T* base, int64_t idx, cx<T> v) {
-  reinterpret_cast<cx<T>*>(base)[idx] = v;
+  const vec2<T> w = {v.x, v.y};
+  reinterpret_cast<vec2<T>*>(base)[idx] = w;
+}
+
+// Store past the caches (nontemporal).
+template <typename T>
+__device__ __forceinline__ void st_stream(T* base, int64_t idx, cx<T> v) {
+  const vec2<T> w = {v.x, v.y};
+  __builtin_nontemporal_store(w, reinterpret_cast<vec2<T>*>(base) + idx);
 }
 
 template <typename T, class PL, int NT>
@@ -162,10 +184,28 @@ __device__ __forceinline__ TileField tile_field(int nfields) {
 // that were loaded from HBM while the previous item was being transformed
 // (up to MAXT input terms per element; the zero gap of a band input is never
 // loaded); the last pass stores straight to HBM (dropped modes skipped).
+// STREAM: from N = 512, and at 128 and 256, whose strides crowd into few cache sets,
+// outputs that do not fit in the memory-side cache are stored past the caches: they
+// would only displace what the next pass still finds there (256 FP32: 12-field inverse
+// y pass 257 -> 203 us, forward 241 -> 221, rho pass 35 -> 27; FP64 4-field inverse y
+// pass 143 -> 123; 512 FP32: 1682 -> 1560, 1563 -> 1490, 220 -> 190; 768: step 59.5 ->
+// 57.0 ms).  Outputs that fit stay (256 FP32, 4-field passes streamed: z 46 -> 52, y
+// 66 -> 73), and so do those of the forward z pass, which the next pass reads first
+// (512: 257 -> 273 streamed), and of the other sizes (FP64 192: 139 -> 163 and 137 ->
+// 150 streamed; 384: 1209 -> 1247 and 1193 -> 1205).  A launch chooses by its output
+// bytes (kStreamBytes); from 512 on every field list of a step is too large.  A branch
+// in one kernel instead costs it 8-12 registers (192 FP32 12-field inverse y pass 71 ->
+// 87 us).
 // Z: a z pass (else a y pass), fixed at compile time so that the column
 // geometry, the strides and the wavenumbers of the multipliers are constants
 // rather than uniform branches per element.
-template <typename T, int N, int S, int MAXT, bool MX, bool Z>
+enum ColStream { CS_NEVER, CS_BY_SIZE, CS_ALWAYS };
+template <int N, int S, bool Z> constexpr ColStream col_stream() {
+  if (Z && S < 0) return CS_NEVER;
+  if (N >= 512) return CS_ALWAYS;
+  return is_pow2(N) && N >= 128 ? CS_BY_SIZE : CS_NEVER;
+}
+template <typename T, int N, int S, int MAXT, bool MX, bool Z, bool STREAM>
 __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(const ColArgs<T> a) {
   using PL = PlanOf<N, MX>;
   constexpr int C = col_tile<T, N, MX, S, MAXT, Z>();
@@ -332,7 +372,8 @@ __global__ void __launch_bounds__((col_threads<T, N, MX, S, MAXT, Z>())) k_col(c
         l = pos_band<N>(q);
         if (l < 0) return;
       }
-      st(out, base_out + l * ls_out + c, val);
+      if constexpr (STREAM) st_stream(out, base_out + l * ls_out + c, val);
+      else st(out, base_out + l * ls_out + c, val);
     };
     fft_first_regs<T, PL, C, NT, C, 1, S, 0, 0>(tile, v, tid, C, store);
     if constexpr (!EARLY) {
@@ -374,20 +415,24 @@ template <typename T> struct Update {
   __device__ __forceinline__ bool at_u() const { return op != UP_RK_MID && op != UP_LAST && op != UP_STORE; }  // U = u
   __device__ __forceinline__ cx<T> old_u(int64_t off) const { return op != UP_STORE ? ld(u, off) : mk<T>(0, 0); }
   __device__ __forceinline__ cx<T> old_acc(int64_t off) const { return reads_acc() ? ld(acc, off) : mk<T>(0, 0); }
-  // u0, a0: old_u and old_acc of the entry
-  __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u0, cx<T> a0) const {
+  // u0, a0: old_u and old_acc of the entry; STREAM: store past the caches
+  template <bool STREAM = false> __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u0, cx<T> a0) const {
+    auto put = [&](T* p, cx<T> v) {
+      if constexpr (STREAM) st_stream(p, off, v);
+      else st(p, off, v);
+    };
     if (op == UP_STORE) {
-      st(rout, off, R);
+      put(rout, R);
     } else if (op == UP_AB2 || op == UP_PC_PRED) {
       cx<T> inc = cscale(R, ac);
       if (use_prev) inc = cfma(ap, a0, inc);
-      st(op == UP_AB2 ? u : us, off, cfma(dt, inc, u0));
-      st(acc, off, R);
+      put(op == UP_AB2 ? u : us, cfma(dt, inc, u0));
+      put(acc, R);
     } else if (op == UP_LAST) {
-      st(u, off, cfma(c, cadd(a0, R), u0));
+      put(u, cfma(c, cadd(a0, R), u0));
     } else {
-      st(acc, off, op == UP_RK_FIRST ? R : cfma(w, R, a0));
-      st(us, off, cfma(c, R, u0));
+      put(acc, op == UP_RK_FIRST ? R : cfma(w, R, a0));
+      put(us, cfma(c, R, u0));
     }
   }
 };
@@ -408,6 +453,7 @@ template <typename T> struct RhsMember {
     eta = T(a.eta[mem]);
     induction = f >= 4 && f <= 6;
   }
+  template <bool STREAM = false>
   __device__ __forceinline__ void apply(int64_t off, cx<T> R, cx<T> u0, cx<T> a0, int kx, int ky, int kz) const {
     const T k2 = T(kx * kx + ky * ky + kz * kz);
     if (induction) {
@@ -418,7 +464,7 @@ template <typename T> struct RhsMember {
       if (a.mu != 0.0) R = cfma(-(T(a.mu) * k2), ld(uhat, off), R);
       if (a.force) R = cadd(R, ld(force, off));
     }
-    up.apply(off, R, u0, a0);
+    up.template apply<STREAM>(off, R, u0, a0);
   }
 };
 
@@ -488,11 +534,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
     kz = band_k<N>(l);
     return (int64_t)l * LS + col;
   };
-  // The state (for the update, and B^ for the resistive term) and the history:
-  // FP32 from N = 512 loads them before the transforms, so that these loads are
-  // in flight while the flux groups are transformed (5% faster); the others
-  // after them (FP32 at 256: a resident workgroup lost to registers, 4% slower).
-  constexpr bool PRE = rhs_wide<T, N>() && N >= 512;
+  // The state (for the update, and B^ for the resistive term) and the history
   cx<T> u_pre[LP::CNT][LP::R], r_pre[LP::CNT][LP::R];
   auto load_old = [&](int i, int r) {
     u_pre[i][r] = mk<T>(0, 0);
@@ -509,7 +551,6 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
 #pragma unroll
       for (int r = 0; r < LP::R; ++r) load_old(i, r);
   };
-  if constexpr (PRE) load_all_old();
 
   load_twiddles<T, PL, NT>(stw, a.tw, tid);
   cx<T> acc[LP::CNT][LP::R];
@@ -518,58 +559,90 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
 #pragma unroll
     for (int r = 0; r < LP::R; ++r) acc[i][r] = mk<T>(0, 0);
 
-  for (int grp = 0; grp < 2; ++grp) {
-    const OutSpec& sp = grp == 0 ? a.A[f] : a.Z[f];
-    const int nt = sp.nterms;
-    if (nt == 0) continue;           // uniform across the block
-    if (grp == 1) __syncthreads();   // the LDS tile is about to be rewritten
-    const T* p0 = member_ptr(a.flux[sp.t[0].src], mem, ms);
-    const T* p1 = nt > 1 ? member_ptr(a.flux[sp.t[1].src], mem, ms) : p0;
-    // the multipliers, converted once per group rather than once per element
+  // Inputs of a flux group: value at (column c, position q)
+  struct Group {
+    const T *p0, *p1;
     T cf[2];
-    int ax[2];
+    int ax[2], nt;
+  };
+  auto group = [&](const OutSpec& sp) {
+    Group G;
+    G.nt = sp.nterms;
+    G.p0 = member_ptr(a.flux[G.nt > 0 ? sp.t[0].src : 0], mem, ms);
+    G.p1 = G.nt > 1 ? member_ptr(a.flux[sp.t[1].src], mem, ms) : G.p0;
+    // the multipliers, converted once per group rather than once per element
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      cf[t] = t < nt ? T(sp.t[t].coef) : T(0);
-      ax[t] = t < nt ? sp.t[t].axis : -1;
+      G.cf[t] = t < G.nt ? T(sp.t[t].coef) : T(0);
+      G.ax[t] = t < G.nt ? sp.t[t].axis : -1;
     }
-    auto load = [&](int c, int q) -> cx<T> {
-      const int col = c0 + c;
-      cx<T> v = mk<T>(0, 0);
-      const int kx = col - (col / NHP) * NHP;
-      if (col >= NCOLS || kx >= NH) return v;
-      const int ky = band_k<N>(col / NHP);
-      const int64_t idx = (int64_t)q * LSZ + col;
-      const cx<T> x0 = ld(p0, idx);
-      const cx<T> x1 = nt > 1 ? ld(p1, idx) : mk<T>(0, 0);
-      const cx<T> xs[2] = {x0, x1};
+    return G;
+  };
+  auto load = [&](const Group& G, int c, int q) -> cx<T> {
+    const int col = c0 + c;
+    cx<T> v = mk<T>(0, 0);
+    const int kx = col - (col / NHP) * NHP;
+    if (G.nt == 0 || col >= NCOLS || kx >= NH) return v;
+    const int ky = band_k<N>(col / NHP);
+    const int64_t idx = (int64_t)q * LSZ + col;
+    const cx<T> x0 = ld(G.p0, idx);
+    const cx<T> x1 = G.nt > 1 ? ld(G.p1, idx) : mk<T>(0, 0);
+    const cx<T> xs[2] = {x0, x1};
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        if (t < nt) {
-          if (ax[t] < 0) {
-            v = cfma(cf[t], xs[t], v);
-          } else {
-            const T ck = cf[t] * T(ax[t] == 0 ? kx : ky);
-            v = cfma(ck, ctimes_i(xs[t]), v);
-          }
+    for (int t = 0; t < 2; ++t) {
+      if (t < G.nt) {
+        if (G.ax[t] < 0) {
+          v = cfma(G.cf[t], xs[t], v);
+        } else {
+          const T ck = G.cf[t] * T(G.ax[t] == 0 ? kx : ky);
+          v = cfma(ck, ctimes_i(xs[t]), v);
         }
       }
-      return v;
-    };
-    auto store = [&](int i, int r, int, int q, cx<T> v) {
-      if (grp == 0) {
-        acc[i][r] = cadd(acc[i][r], v);
-      } else {  // + i kz v
-        const int l = pos_band<N>(q);
-        const T kz = T(l < 0 ? 0 : band_k<N>(l));
-        acc[i][r] = cfma(kz, ctimes_i(v), acc[i][r]);
+    }
+    return v;
+  };
+  auto add_A = [&](int i, int r, int, int, cx<T> v) { acc[i][r] = cadd(acc[i][r], v); };
+  auto add_Z = [&](int i, int r, int, int q, cx<T> v) {  // + i kz v
+    const int l = pos_band<N>(q);
+    const T kz = T(l < 0 ? 0 : band_k<N>(l));
+    acc[i][r] = cfma(kz, ctimes_i(v), acc[i][r]);
+  };
+  const Group GA = group(a.A[f]), GZ = group(a.Z[f]);
+  if constexpr (rhs_upfront<N>()) {
+    using FP = FirstPass<PL, C, NT>;
+    cx<T> x[FP::CNT][FP::R], z[FP::CNT][FP::R];
+    auto load_all = [&](const Group& G, cx<T> (&w)[FP::CNT][FP::R]) {
+#pragma unroll
+      for (int i = 0; i < FP::CNT; ++i) {
+        int c, j;
+        const bool ok = first_slot<C, FP::NBF, NT, 0>(tid, i, c, j);
+#pragma unroll
+        for (int r = 0; r < FP::R; ++r) w[i][r] = ok ? load(G, c, j + r * FP::NBF) : mk<T>(0, 0);
       }
     };
-    fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, load, store);
+    load_all(GA, x);
+    load_all(GZ, z);
+    __syncthreads();  // the twiddles
+    if (GA.nt > 0) {
+      fft_first_regs<T, PL, C, NT, C, 1, -1, 0, 0>(tile, x, tid, C, add_A);
+      fft_rest<T, PL, C, NT, C, 1, -1, 0, 0>(tile, stw, tid, C, add_A);
+    }
+    if (GZ.nt > 0) {
+      __syncthreads();  // the LDS tile is about to be rewritten
+      fft_first_regs<T, PL, C, NT, C, 1, -1, 0, 0>(tile, z, tid, C, add_Z);
+      fft_rest<T, PL, C, NT, C, 1, -1, 0, 0>(tile, stw, tid, C, add_Z);
+    }
+  } else {
+    if (GA.nt > 0)  // uniform across the block
+      fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, [&](int c, int q) { return load(GA, c, q); }, add_A);
+    if (GZ.nt > 0) {
+      if (GA.nt > 0) __syncthreads();
+      fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, [&](int c, int q) { return load(GZ, c, q); }, add_Z);
+    }
   }
   // epilogue over this thread's last-pass positions; all its loads go out
   // together, ahead of the first that is used
-  if constexpr (!PRE) load_all_old();
+  load_all_old();
 #pragma unroll
   for (int i = 0; i < LP::CNT; ++i) {
 #pragma unroll
@@ -577,7 +650,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
       int kx, ky, kz;
       const int64_t idx = out_index(i, r, kx, ky, kz);
       if (idx < 0) continue;
-      M.apply(idx, acc[i][r], u_pre[i][r], r_pre[i][r], kx, ky, kz);
+      M.template apply<(N >= 512)>(idx, acc[i][r], u_pre[i][r], r_pre[i][r], kx, ky, kz);
     }
   }
 }

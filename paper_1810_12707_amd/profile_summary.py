@@ -98,11 +98,11 @@ def per_kernel_kib(path: str, counter: str) -> dict:
 # ({mx}: false on the FP32 path, true on the mixed path, in the column passes;
 # the row and z-RHS passes are the same kernels on both).
 STEP_SEQUENCE = [
-    ("zinv_a", "k_col<float, {n}, 1, 1, {mx}, true>"), ("yinv_a", "k_col<float, {n}, 1, 1, {mx}, false>"),
-    ("xa", "k_row<float, {n}, 0"), ("yfwd_a", "k_col<float, {n}, -1, 1, {mx}, false>"),
-    ("zfwd_a", "k_col<float, {n}, -1, 1, {mx}, true>"), ("zinv_b", "k_col<float, {n}, 1, 3, {mx}, true>"),
-    ("yinv_b", "k_col<float, {n}, 1, 1, {mx}, false>"), ("xb", "k_row<float, {n}, 1"),
-    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false>"), ("rho", "k_rho_rhs<float>"), ("zrhs", "k_zfwd_rhs<float, {n}"),
+    ("zinv_a", "k_col<float, {n}, 1, 1, {mx}, true"), ("yinv_a", "k_col<float, {n}, 1, 1, {mx}, false"),
+    ("xa", "k_row<float, {n}, 0"), ("yfwd_a", "k_col<float, {n}, -1, 1, {mx}, false"),
+    ("zfwd_a", "k_col<float, {n}, -1, 1, {mx}, true"), ("zinv_b", "k_col<float, {n}, 1, 3, {mx}, true"),
+    ("yinv_b", "k_col<float, {n}, 1, 1, {mx}, false"), ("xb", "k_row<float, {n}, 1"),
+    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false"), ("rho", "k_rho_rhs<float>"), ("zrhs", "k_zfwd_rhs<float, {n}"),
 ]
 
 
