@@ -607,8 +607,8 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
     const T kz = T(l < 0 ? 0 : band_k<N>(l));
     acc[i][r] = cfma(kz, ctimes_i(v), acc[i][r]);
   };
-  const Group GA = group(a.A[f]), GZ = group(a.Z[f]);
   if constexpr (rhs_upfront<N>()) {
+    const Group GA = group(a.A[f]), GZ = group(a.Z[f]);
     using FP = FirstPass<PL, C, NT>;
     cx<T> x[FP::CNT][FP::R], z[FP::CNT][FP::R];
     auto load_all = [&](const Group& G, cx<T> (&w)[FP::CNT][FP::R]) {
@@ -623,7 +623,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
     load_all(GA, x);
     load_all(GZ, z);
     __syncthreads();  // the twiddles
-    if (GA.nt > 0) {
+    if (GA.nt > 0) {  // uniform across the block
       fft_first_regs<T, PL, C, NT, C, 1, -1, 0, 0>(tile, x, tid, C, add_A);
       fft_rest<T, PL, C, NT, C, 1, -1, 0, 0>(tile, stw, tid, C, add_A);
     }
@@ -632,8 +632,24 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
       fft_first_regs<T, PL, C, NT, C, 1, -1, 0, 0>(tile, z, tid, C, add_Z);
       fft_rest<T, PL, C, NT, C, 1, -1, 0, 0>(tile, stw, tid, C, add_Z);
     }
+  } else if constexpr (N <= 96) {
+    // one code for both groups, where the launch is short enough for its instruction
+    // fetch to show (64 FP32: 17.8 us written out, 16.2 as a loop)
+#pragma unroll 1
+    for (int grp = 0; grp < 2; ++grp) {
+      const Group G = group(grp == 0 ? a.A[f] : a.Z[f]);
+      if (G.nt == 0) continue;
+      if (grp == 1) __syncthreads();
+      fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, [&](int c, int q) { return load(G, c, q); },
+                                      [&](int i, int r, int c, int q, cx<T> v) {
+                                        if (grp == 0) add_A(i, r, c, q, v);
+                                        else add_Z(i, r, c, q, v);
+                                      });
+    }
   } else {
-    if (GA.nt > 0)  // uniform across the block
+    // written out, which takes fewer registers (256 FP32 70 -> 63: 224 -> 213 us)
+    const Group GA = group(a.A[f]), GZ = group(a.Z[f]);
+    if (GA.nt > 0)
       fft_reg<T, PL, C, NT, C, 1, -1>(tile, stw, tid, C, [&](int c, int q) { return load(GA, c, q); }, add_A);
     if (GZ.nt > 0) {
       if (GA.nt > 0) __syncthreads();
@@ -765,15 +781,20 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // of two (13% faster at 512) or three (3% at 256).  The FP32 velocity pass at
 // N = 256 takes 128: two waves of two fields each, whose 32-butterfly radix-8
 // passes then fill every lane (256 threads left half of them idle; 19%).
-// The FP64 flux pass at N = 512 and 384 takes 512 too (one workgroup per CU:
-// two waves per SIMD instead of one, 6.78 -> 5.63 ms at 512).
+// The FP64 velocity pass at 256 takes 128 as well (252 -> 173 us), and so do 96 (FP64
+// 18.9 -> 16.9), FP32 at 192 (55.3 -> 53.5) and at 512 (655 -> 629); FP32 at 384 takes
+// one wave (348 -> 324).
+// The FP64 flux pass at N = 512, 384 and 192 takes 512 too (at 512 one workgroup
+// per CU: two waves per SIMD instead of one, 6.78 -> 5.63 ms; 192 324 -> 307 us).
 // Below 256 (wave maps at 64 and 128): the velocity pass takes one wave per row
 // pair, which then needs no barrier (64: 11.1 -> 9.1 us FP64; 128: 36.6 ->
 // 32.4 us FP64, 22.6 -> 20.3 us FP32), the flux pass as many threads as let
 // every lane of a first pass hold a butterfly (128: 256 threads in FP32, 56.8 ->
 // 55.1 us) or half as many (64, and 128 in FP64 where the registers of two
 // butterflies fit: 20.2 -> 18.5 and 109 -> 89 us; FP32 at 128 would spill).
-// The kinematic pass (eight fields) takes a thread per first-pass butterfly.
+// The passes from and to real fields take a thread per first-pass butterfly at 384
+// and 512 (set_state at 512 FP32 4.15 -> 3.39 ms, FP64 10.55 -> 7.89).
+// The kinematic pass (eight fields) does the same.
 template <typename T, int N, int MODE> constexpr int row_threads() {
   if (MODE == RM_XK) {
     constexpr int w = 8 * (N / PlanOf<N>::r[0]);
@@ -781,8 +802,10 @@ template <typename T, int N, int MODE> constexpr int row_threads() {
   }
   if (MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
   if (MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
-  if (sizeof(T) == 4 && MODE == RM_XA && N == 256) return kThreads / 2;
-  if (MODE == RM_XA && (N == 64 || N == 128 || (sizeof(T) == 8 && N == 192))) return 64;
+  if (MODE == RM_XB && sizeof(T) == 8 && N == 192) return 2 * kThreads;
+  if (MODE == RM_XA && (N == 64 || N == 128 || (N == 192 && sizeof(T) == 8) || (N == 384 && sizeof(T) == 4))) return 64;
+  if (MODE == RM_XA && (N == 96 || N == 192 || N == 256 || (N == 512 && sizeof(T) == 4))) return kThreads / 2;
+  if ((MODE == RM_XFWD_REAL || MODE == RM_XINV_REAL) && (N == 384 || N == 512)) return 2 * kThreads;
   return (sizeof(T) == 4 && N >= 1024) ? 2 * kThreads : kThreads;
 }
 
@@ -869,7 +892,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   constexpr int RH = FP::R / 2;
   constexpr int FMAP = (FP::CNT % 2 == 0 && FP::NBF % 2 == 0) ? 2 : ((FP::NBF >= 2 && 64 % FP::NBF == 0) ? 3 : 1);
   constexpr int HC = FP::CNT / 2;
-  constexpr int FM1 = FMAP == 2 ? (WAVE ? 4 : 2) : RMAP;  // lane map of the first pass
+  constexpr int FM1 = !SPEC_IN ? 1 : (FMAP == 2 ? (WAVE ? 4 : 2) : RMAP);  // lane map of the first pass
   // first-pass rows r whose positions j + r NBF all lie in the dealiased gap:
   // known zeros, neither loaded nor assembled, and pruned from the DFT
   constexpr unsigned ZROWS = gap_rows<N, FP::NBF, FP::R, K>();
@@ -896,6 +919,28 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
       }
     }
   };
+  // Real rows, as row0 + i row1.  From N = 96 the next pair's are prefetched into the
+  // first-pass elements too (loaded, transformed and stored in turn the pass waits on
+  // memory three quarters of its time: set_state at 512 FP64 7.9 -> 6.4 ms, 384 FP32
+  // 1.49 -> 1.39; 192 178 -> 172 us); smaller ones go to the LDS, a point per thread
+  // (few of the threads hold a butterfly there).
+  constexpr bool REAL_REGS = !SPEC_IN && N >= 96;
+  auto real_pair = [&](auto* in, int64_t e) { return mk<T>(T(in[e]), T(in[e + N])); };
+  cx<T> rx[REAL_REGS ? FP::CNT : 1][FP::R];
+  auto issue_real = [&](int64_t item) {
+    auto rows = [&](auto* in) {
+#pragma unroll
+      for (int i = 0; i < FP::CNT; ++i) {
+        int b, j;
+        const bool ok = first_slot<NB, FP::NBF, NT, FM1>(tid, i, b, j) && b < nin;
+#pragma unroll
+        for (int r = 0; r < FP::R; ++r)
+          rx[i][r] = ok ? real_pair(in, b * a.g.n3 + 2 * item * N + j + r * FP::NBF) : mk<T>(0, 0);
+      }
+    };
+    if (a.real_dtype == 0) rows(static_cast<const double*>(a.real_in));
+    else rows(static_cast<const float*>(a.real_in));
+  };
   // per-workgroup accumulators of the diagnostic / status modes: the largest
   // signal speed (each point's speed is formed in T, and the thread's maximum
   // of T values is exact in T; it goes to FP64 at the workgroup's flush) and
@@ -913,6 +958,8 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   int64_t item = blockIdx.x;
   if constexpr (SPEC_IN) {
     if (item < nitems) issue(item);
+  } else if constexpr (REAL_REGS) {
+    if (item < nitems) issue_real(item);
   }
   int cur_m = -1;  // member whose CFL / non-finite status is being accumulated
   for (; item < nitems; item += gridDim.x) {
@@ -933,19 +980,16 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
     // that still reads them)
     if constexpr (!WAVE) __syncthreads();
     if constexpr (!SPEC_IN) {
-      // real rows -> packed complex row0 + i row1
-      for (int e = tid; e < nin * N; e += NT) {
-        const int fld = e / N, x = e - (e / N) * N;
-        const int64_t base = fld * a.g.n3 + row0 * N + x;
-        T r0, r1;
-        if (a.real_dtype == 0) {
-          r0 = T(static_cast<const double*>(a.real_in)[base]);
-          r1 = T(static_cast<const double*>(a.real_in)[base + N]);
-        } else {
-          r0 = T(static_cast<const float*>(a.real_in)[base]);
-          r1 = T(static_cast<const float*>(a.real_in)[base + N]);
+      if constexpr (REAL_REGS) {
+        fft_first_regs<T, PL, NB, NT, 1, BS, -1, FM1, LAY>(buf, rx, tid, nin, lds_store);
+        if (item + gridDim.x < nitems) issue_real(item + gridDim.x);
+      } else {
+        for (int e = tid; e < nin * N; e += NT) {
+          const int fld = e / N, x = e - (e / N) * N;
+          const int64_t base = fld * a.g.n3 + row0 * N + x;
+          buf[at(fld, x)] = a.real_dtype == 0 ? real_pair(static_cast<const double*>(a.real_in), base)
+                                              : real_pair(static_cast<const float*>(a.real_in), base);
         }
-        buf[at(fld, x)] = mk<T>(r0, r1);
       }
     } else {
       // inverse x transform: first pass from the prefetched registers
@@ -1018,7 +1062,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
       if (item + gridDim.x < nitems) issue(item + gridDim.x);  // next pair's loads overlap the rest
       fft_rest<T, PL, NB, NT, 1, BS, +1, RMAP, LAY, true>(buf, stw, tid, nin, lds_store);
     }
-    __syncthreads();
+    if constexpr (!REAL_REGS) __syncthreads();
 
     if constexpr (MODE == RM_XINV_REAL) {
       for (int e = tid; e < nout * N; e += NT) {
@@ -1210,8 +1254,13 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
     }
 
     if constexpr (MODE == RM_XA || FLUX || MODE == RM_XFWD_REAL) {
-      __syncthreads();
-      lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K>(buf, stw, tid, nout);  // only k <= K and N - k are read
+      // only k <= K and N - k are read
+      if constexpr (REAL_REGS) {
+        lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K, 1>(buf, stw, tid, nout);
+      } else {
+        if constexpr (SPEC_IN) __syncthreads();
+        lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K>(buf, stw, tid, nout);
+      }
       // unpack: X0[k] = (Z[k] + conj Z[N-k]) / 2, X1[k] = -i (Z[k] - conj Z[N-k]) / 2, k = 0..K,
       // stored doubled (2 X0, 2 X1): the forward y pass that reads these rows
       // applies the 1/2 with its copy coefficient (an exact power-of-two
