@@ -184,8 +184,8 @@ int mhd_rhs(mhd_ctx* ctx, const void* d_fields_in, void* d_rhs_out, int32_t dtyp
  * d_rhs_out: caller-owned [8][n][n][n] arrays of element type dtype, on the
  * current device; the work is enqueued on hip_stream (NULL = default stream)
  * after one synchronous upload of the twiddle table.  Sizes whose workspace
- * exceeds 64 MiB (mhd_workspace_bytes(p) > 64 MiB: n <= 64 fits in every
- * precision) return MHD_E_WORKSPACE.  Every call on a GPU shares that GPU's
+ * exceeds 64 MiB (mhd_workspace_bytes(p) > 64 MiB: n <= 64 fits in FP32 and
+ * mixed, n <= 48 in FP64) return MHD_E_WORKSPACE.  Every call on a GPU shares its
  * array and leaves its contents behind; nothing in it needs to start at zero
  * (every array the right-hand side reads is written earlier in the same
  * call).  Calls that overlap on one GPU (other streams, other host threads)
