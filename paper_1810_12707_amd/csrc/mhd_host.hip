@@ -728,9 +728,10 @@ struct Engine {
       case MHD_PASS_XA: return cbytes(0, 0, 7 + a4);
       case MHD_PASS_YFWD_A: return cbytes(0, 3 + a4, 3 + a4);
       case MHD_PASS_ZFWD_A: return cbytes(3 + a4, 3 + a4, 0);
-      case MHD_PASS_ZINV_B: return cbytes(7, 12, 0);
-      case MHD_PASS_YINV_B: return cbytes(0, 12, 12);
-      case MHD_PASS_XB: return cbytes(0, 0, 28);
+      // (the Laplacian viscous force needs no strains: 5 of the 12 fields and u^ not read)
+      case MHD_PASS_ZINV_B: return cbytes(7 - 3 * a4, 12 - 5 * a4, 0);
+      case MHD_PASS_YINV_B: return cbytes(0, 12 - 5 * a4, 12 - 5 * a4);
+      case MHD_PASS_XB: return cbytes(0, 0, 28 - 5 * a4);
       case MHD_PASS_YFWD_B: return cbytes(0, 12, 12);
       case MHD_PASS_ZRHS: return cbytes(28 + 4 * a4 + fo, 12, 0);
       case MHD_PASS_RHO: return cbytes(7 + 2 * fo, 0, 0);
@@ -995,16 +996,24 @@ struct Engine {
     // inputs: 0-2 B^, 3 E^, 4-6 u^
     const T* zi[7] = {spec_field(U, 4), spec_field(U, 5), spec_field(U, 6), spec_field(U, 7),
                       spec_field(uhat(), 0), spec_field(uhat(), 1), spec_field(uhat(), 2)};
+    // without the strains (5 of the 12) where the viscous force is the Laplacian
+    // (FP32 128: zinv_b 22 -> 15, yinv_b 24 -> 16, flux pass 57 -> 53 us; 256: 138 -> 79,
+    // 212 -> 108, 364 -> 327)
+    const bool strain = na() == 3;
+    const int nz = strain ? 12 : 7;
     OutSpec sp[12];
     flux_input_specs(sp);
+    if (!strain)
+      for (int f = 4; f < 7; ++f) sp[f] = sp[5 + f];
     T* zo[12];
-    for (int f = 0; f < 12; ++f) zo[f] = iz(f);
-    timed(MHD_PASS_ZINV_B, [&] { col(PK_ZINV, 12, zi, 7, zo, sp); });
+    for (int f = 0; f < nz; ++f) zo[f] = iz(f);
+    timed(MHD_PASS_ZINV_B, [&] { col(PK_ZINV, nz, zi, 7, zo, sp); });
     T* yo[12];
-    for (int f = 0; f < 12; ++f) yo[f] = iy(4 + f);
-    timed(MHD_PASS_YINV_B, [&] { y_copy(PK_YINV, 12, zo, yo); });
+    for (int f = 0; f < nz; ++f) yo[f] = iy(4 + f);
+    timed(MHD_PASS_YINV_B, [&] { y_copy(PK_YINV, nz, zo, yo); });
     const RowArgs<T> r = flux_args(record_status);
-    timed(MHD_PASS_XB, [&] { k.row(RM_XB, r, row_grid(RM_XB), c->stream); });
+    const int mode = strain ? RM_XB : RM_XL;
+    timed(MHD_PASS_XB, [&] { k.row(mode, r, row_grid(mode), c->stream); });
     T* fi[12];
     T* fo[12];
     for (int f = 0; f < 12; ++f) { fi[f] = iy(f); fo[f] = iz(f); }

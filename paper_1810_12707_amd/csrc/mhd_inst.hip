@@ -94,6 +94,7 @@ void with_row_mode(int mode, F&& fn) {
     case RM_XFWD_REAL: fn(std::integral_constant<int, RM_XFWD_REAL>()); break;
     case RM_XINV_REAL: fn(std::integral_constant<int, RM_XINV_REAL>()); break;
     case RM_XDIAG: fn(std::integral_constant<int, RM_XDIAG>()); break;
+    case RM_XL: fn(std::integral_constant<int, RM_XL>()); break;
     case RM_XK: fn(std::integral_constant<int, RM_XK>()); break;
     default: break;
   }

@@ -164,8 +164,8 @@ struct RhsArgs {
   double eta[kMaxMem];  // diffusivity, per member
 };
 
-enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5 };
-constexpr int kRowModes = 6;
+enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5, RM_XL = 6 };
+constexpr int kRowModes = 7;
 
 template <typename T>
 struct RowArgs {
@@ -178,7 +178,7 @@ struct RowArgs {
   int32_t real_dtype;       // 0 = double, 1 = float
   int32_t nf;               // fields of an I/O pass
   double* partials;         // per-block records (RM_XDIAG, single member)
-  double* status;           // RM_XB, RM_XK: status slots [kStatusSlots][2] (max signal speed, non-finite
+  double* status;           // RM_XB, RM_XL, RM_XK: status slots [kStatusSlots][2] (max signal speed, non-finite
                             // count), slot = workgroup id; null: no status (pure RHS evaluations)
   const T* tw;
   Geo g;

@@ -676,6 +676,7 @@ __global__ void __launch_bounds__((rhs_threads<T, N>()), (rhs_min_waves<T, N>())
 template <int MODE> struct RowShape;
 template <> struct RowShape<RM_XA> { static constexpr int NIN = 4, NOUT = 3, NB = 4; };
 template <> struct RowShape<RM_XB> { static constexpr int NIN = 16, NOUT = 12, NB = 16; };
+template <> struct RowShape<RM_XL> { static constexpr int NIN = 11, NOUT = 12, NB = 12; };
 template <> struct RowShape<RM_XFWD_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
 template <> struct RowShape<RM_XINV_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
 template <> struct RowShape<RM_XK> { static constexpr int NIN = 8, NOUT = 3, NB = 8; };
@@ -795,14 +796,17 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // The passes from and to real fields take a thread per first-pass butterfly at 384
 // and 512 (set_state at 512 FP32 4.15 -> 3.39 ms, FP64 10.55 -> 7.89).
 // The kinematic pass (eight fields) does the same.
+// The flux passes of a full run: RM_XL leaves out the strains (the Laplacian viscous
+// force of a run is added spectrally).
+constexpr bool is_flux(int mode) { return mode == RM_XB || mode == RM_XL; }
 template <typename T, int N, int MODE> constexpr int row_threads() {
   if (MODE == RM_XK) {
     constexpr int w = 8 * (N / PlanOf<N>::r[0]);
     return w <= 64 ? 64 : (w >= 512 ? 512 : (w + 63) / 64 * 64);
   }
-  if (MODE == RM_XB && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
-  if (MODE == RM_XB && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
-  if (MODE == RM_XB && sizeof(T) == 8 && N == 192) return 2 * kThreads;
+  if (is_flux(MODE) && (N == 512 || N == 384 || (sizeof(T) == 4 && N == 256))) return 2 * kThreads;
+  if (is_flux(MODE) && (N == 64 || (sizeof(T) == 8 && N == 128))) return kThreads / 2;
+  if (is_flux(MODE) && sizeof(T) == 8 && N == 192) return 2 * kThreads;
   if (MODE == RM_XA && (N == 64 || N == 128 || (N == 192 && sizeof(T) == 8) || (N == 384 && sizeof(T) == 4))) return 64;
   if (MODE == RM_XA && (N == 96 || N == 192 || N == 256 || (N == 512 && sizeof(T) == 4))) return kThreads / 2;
   if ((MODE == RM_XFWD_REAL || MODE == RM_XINV_REAL) && (N == 384 || N == 512)) return 2 * kThreads;
@@ -815,7 +819,7 @@ template <typename T, int N, int MODE> constexpr int row_threads() {
 // registers and then runs one wave per SIMD.
 template <typename T, int N, int MODE> constexpr int row_min_blocks() {
   if (sizeof(T) != 4 || row_threads<T, N, MODE>() < kThreads || MODE == RM_XK) return 1;
-  if (MODE == RM_XB && (N == 512 || N == 384 || N == 256)) return 2;
+  if (is_flux(MODE) && (N == 512 || N == 384 || N == 256)) return 2;
   return 2 * kThreads / row_threads<T, N, MODE>();
 }
 
@@ -833,8 +837,8 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   // (conflict-free LDS access, but more address arithmetic) where it measured
   // faster: the flux pass below N = 512 (3%) and the velocity pass from N = 512
   // (2%).  Otherwise one padding slot per 8 elements.
-  constexpr bool LIN = (MODE == RM_XB || MODE == RM_XDIAG) && N >= 1024;
-  constexpr bool SWZ = !LIN && N % 16 == 0 && N >= 128 && ((MODE == RM_XB && N < 512) || (MODE == RM_XA && N >= 512));
+  constexpr bool LIN = (is_flux(MODE) || MODE == RM_XDIAG) && N >= 1024;
+  constexpr bool SWZ = !LIN && N % 16 == 0 && N >= 128 && ((is_flux(MODE) && N < 512) || (MODE == RM_XA && N >= 512));
   constexpr int PADSH = 3;
   constexpr int LAY = SWZ ? kSwizzle : (PADSH | (LIN ? kLinear : 0));
   // row pitch in LDS: swizzled rows are shifted by 16 elements from row to
@@ -850,9 +854,9 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   // at 96 and 192 otherwise (their 12 and 32 first-pass butterflies per field
   // leave lanes of a wave idle: 96 FP32 flux pass 30.8 -> 35.7 us) or with fewer
   // fields than waves.
-  constexpr bool FLUX = MODE == RM_XB || MODE == RM_XK;  // forms fluxes and the status
+  constexpr bool FLUX = is_flux(MODE) || MODE == RM_XK;  // forms fluxes and the status
   constexpr bool WAVE = MODE == RM_XK ? is_pow2(N) && N >= 64
-                                      : (MODE == RM_XA || MODE == RM_XB) &&
+                                      : (MODE == RM_XA || is_flux(MODE)) &&
                                             (N >= 384 || N == 256 || N == 128 || N == 64 || (N == 192 && NT == 64)) &&
                                             NB >= NT / 64;
   constexpr int RMAP = WAVE ? 3 : 1;
@@ -1099,39 +1103,52 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
       }
     }
 
-    if constexpr (MODE == RM_XB) {
+    if constexpr (is_flux(MODE)) {
       // Real-space fluxes of Eqs. MHD2-MHD4 at every point of both rows.
       // Inputs: 0 rho, 1-3 m, 4-6 B, 7 E, 8 S_xx, 9 S_yy, 10 S_xy, 11 S_xz,
-      // 12 S_yz, 13-15 J.  Outputs: 0 Pi_xx, 1 Pi_yy, 2 Pi_zz, 3 Pi_xy,
+      // 12 S_yz, 13-15 J (RM_XL: 8-10 J).  Outputs: 0 Pi_xx, 1 Pi_yy, 2 Pi_zz, 3 Pi_xy,
       // 4 Pi_xz, 5 Pi_yz, 6-8 F^E, 9-11 e = u x B.
       const T gm1 = T(a.gamma[mem] - 1.0), gam = T(a.gamma[mem]), two_nu = T(2.0 * a.nu[mem]),
               eta = T(a.eta[mem]);
-      auto point = [&](const T (&v)[16], T (&out)[12]) {
+      constexpr bool STRAIN = MODE == RM_XB;
+      constexpr int NV = RowShape<MODE>::NIN;
+      auto point = [&](const T (&v)[NV], T (&out)[12]) {
         const T rho = v[0], mx = v[1], my = v[2], mz = v[3];
         const T Bx = v[4], By = v[5], Bz = v[6], E = v[7];
-        const T Sxx = v[8], Syy = v[9], Sxy = v[10], Sxz = v[11], Syz = v[12];
-        const T Szz = -(Sxx + Syy);
-        const T Jx = v[13], Jy = v[14], Jz = v[15];
+        const T Jx = v[NV - 3], Jy = v[NV - 2], Jz = v[NV - 1];
         const T ir = recip_(rho);
         const T ux = mx * ir, uy = my * ir, uz = mz * ir;
         const T B2 = Bx * Bx + By * By + Bz * Bz;
         const T P = gm1 * (E - T(0.5) * (mx * ux + my * uy + mz * uz) - T(0.5) * B2);
         const T Pt = P + T(0.5) * B2;
-        const T vr = two_nu * rho;
-        out[0] = mx * ux + Pt - Bx * Bx - vr * Sxx;
-        out[1] = my * uy + Pt - By * By - vr * Syy;
-        out[2] = mz * uz + Pt - Bz * Bz - vr * Szz;
-        out[3] = mx * uy - Bx * By - vr * Sxy;
-        out[4] = mx * uz - Bx * Bz - vr * Sxz;
-        out[5] = my * uz - By * Bz - vr * Syz;
+        out[0] = mx * ux + Pt - Bx * Bx;
+        out[1] = my * uy + Pt - By * By;
+        out[2] = mz * uz + Pt - Bz * Bz;
+        out[3] = mx * uy - Bx * By;
+        out[4] = mx * uz - Bx * Bz;
+        out[5] = my * uz - By * Bz;
         const T uB = ux * Bx + uy * By + uz * Bz;
         const T EP = E + Pt;
-        const T uSx = ux * Sxx + uy * Sxy + uz * Sxz;
-        const T uSy = ux * Sxy + uy * Syy + uz * Syz;
-        const T uSz = ux * Sxz + uy * Syz + uz * Szz;
-        out[6] = EP * ux - uB * Bx - vr * uSx - eta * (By * Jz - Bz * Jy);
-        out[7] = EP * uy - uB * By - vr * uSy - eta * (Bz * Jx - Bx * Jz);
-        out[8] = EP * uz - uB * Bz - vr * uSz - eta * (Bx * Jy - By * Jx);
+        out[6] = EP * ux - uB * Bx;
+        out[7] = EP * uy - uB * By;
+        out[8] = EP * uz - uB * Bz;
+        if constexpr (STRAIN) {
+          const T Sxx = v[8], Syy = v[9], Sxy = v[10], Sxz = v[11], Syz = v[12];
+          const T Szz = -(Sxx + Syy);
+          const T vr = two_nu * rho;
+          out[0] -= vr * Sxx;
+          out[1] -= vr * Syy;
+          out[2] -= vr * Szz;
+          out[3] -= vr * Sxy;
+          out[4] -= vr * Sxz;
+          out[5] -= vr * Syz;
+          out[6] -= vr * (ux * Sxx + uy * Sxy + uz * Sxz);
+          out[7] -= vr * (ux * Sxy + uy * Syy + uz * Syz);
+          out[8] -= vr * (ux * Sxz + uy * Syz + uz * Szz);
+        }
+        out[6] -= eta * (By * Jz - Bz * Jy);
+        out[7] -= eta * (Bz * Jx - Bx * Jz);
+        out[8] -= eta * (Bx * Jy - By * Jx);
         out[9] = uy * Bz - uz * By;
         out[10] = uz * Bx - ux * Bz;
         out[11] = ux * By - uy * Bx;
@@ -1152,23 +1169,23 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
         T* const bt = reinterpret_cast<T*>(buf);
         for (int e = tid; e < 2 * N; e += NT) {
           const int h = e >= N ? 1 : 0, x = e - h * N;
-          T v[16], o[12];
+          T v[NV], o[12];
 #pragma unroll
-          for (int f = 0; f < 16; ++f) v[f] = bt[2 * at(f, x) + h];
+          for (int f = 0; f < NV; ++f) v[f] = bt[2 * at(f, x) + h];
           point(v, o);
 #pragma unroll
           for (int k = 0; k < 12; ++k) bt[2 * at(k, x) + h] = o[k];
         }
       } else {
         for (int x = tid; x < N; x += NT) {
-          cx<T> v[16], o[12];
+          cx<T> v[NV], o[12];
 #pragma unroll
-          for (int f = 0; f < 16; ++f) v[f] = buf[at(f, x)];
+          for (int f = 0; f < NV; ++f) v[f] = buf[at(f, x)];
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            T vh[16], oh[12];
+            T vh[NV], oh[12];
 #pragma unroll
-            for (int f = 0; f < 16; ++f) vh[f] = h == 0 ? v[f].x : v[f].y;
+            for (int f = 0; f < NV; ++f) vh[f] = h == 0 ? v[f].x : v[f].y;
             point(vh, oh);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
@@ -1299,7 +1316,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
           const int fld = fl * W + wv;
           if (fld >= nout) break;
           cx<T>* const dst = row_out + fld * ost;
-          if constexpr (MODE == RM_XB && KIT <= 2) {
+          if constexpr (is_flux(MODE) && KIT <= 2) {
 #pragma unroll
             for (int it = 0; it < KIT; ++it) {
               const int k = (tid & 63) + 64 * it;
