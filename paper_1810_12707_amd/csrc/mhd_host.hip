@@ -844,7 +844,9 @@ struct Engine {
     const int64_t items = (int64_t)g.n * g.n / 2 * ms.n;
     if (blocks < 1) blocks = 1;
     if (blocks > items) blocks = items;
-    if (blocks > kStatusSlots) blocks = kStatusSlots;  // one status slot per flux-pass workgroup
+    // one status slot per flux-pass workgroup; the one-wave passes of a single field
+    // need more workgroups than that to fill the chip
+    if (blocks > kStatusSlots && mode != RM_XFWD_ONE && mode != RM_XINV_ONE) blocks = kStatusSlots;
     return dim3((unsigned)blocks);
   }
 
@@ -889,7 +891,8 @@ struct Engine {
     r.real_dtype = dtype == MHD_FP64 ? 0 : 1;
     r.nf = nf;
     set_out(r, 0);
-    k.row(RM_XFWD_REAL, r, row_grid(RM_XFWD_REAL), c->stream);
+    const int mode = nf == 1 ? RM_XFWD_ONE : RM_XFWD_REAL;
+    k.row(mode, r, row_grid(mode), c->stream);
     if (k.yzfwd) {
       ColArgs<T> a = fused_args(nf);
       for (int f = 0; f < nf; ++f) { a.in[f] = iy(f); a.out[f] = spec_field(dst, f); }
@@ -921,7 +924,8 @@ struct Engine {
     r.real_dtype = dtype == MHD_FP64 ? 0 : 1;
     r.nf = nf;
     set_in(r, 0);
-    k.row(RM_XINV_REAL, r, row_grid(RM_XINV_REAL), c->stream);
+    const int mode = nf == 1 ? RM_XINV_ONE : RM_XINV_REAL;
+    k.row(mode, r, row_grid(mode), c->stream);
   }
 
   // Outputs of phase A: u^ (3), and q^ = D F[|u|^2/2] with the viscous-force variant.
@@ -2070,7 +2074,7 @@ int mhd_spectra(mhd_ctx* c, double* h_eu, double* h_eb, double* h_mom) {
     r.real_dtype = sizeof(T) == 4 ? 1 : 0;
     r.nf = 1;
     e.set_in(r, 0);
-    e.k.row(RM_XINV_REAL, r, e.row_grid(RM_XINV_REAL), c->stream);
+    e.k.row(RM_XINV_ONE, r, e.row_grid(RM_XINV_ONE), c->stream);
     const int mb = (int)std::min<int64_t>((g.n3 + kThreads - 1) / kThreads, kSpecBlocks);
     hipLaunchKernelGGL((k_moments<T>), dim3(mb), dim3(kThreads), 0, c->stream, real, g.n3, shpart);
     e.reduce({shpart, shres + nb, mb, 2, 0u});

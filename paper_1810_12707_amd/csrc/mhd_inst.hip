@@ -96,6 +96,8 @@ void with_row_mode(int mode, F&& fn) {
     case RM_XDIAG: fn(std::integral_constant<int, RM_XDIAG>()); break;
     case RM_XL: fn(std::integral_constant<int, RM_XL>()); break;
     case RM_XK: fn(std::integral_constant<int, RM_XK>()); break;
+    case RM_XFWD_ONE: fn(std::integral_constant<int, RM_XFWD_ONE>()); break;
+    case RM_XINV_ONE: fn(std::integral_constant<int, RM_XINV_ONE>()); break;
     default: break;
   }
 }

@@ -164,8 +164,11 @@ struct RhsArgs {
   double eta[kMaxMem];  // diffusivity, per member
 };
 
-enum RowMode { RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5, RM_XL = 6 };
-constexpr int kRowModes = 7;
+enum RowMode {
+  RM_XA = 0, RM_XB = 1, RM_XFWD_REAL = 2, RM_XINV_REAL = 3, RM_XDIAG = 4, RM_XK = 5, RM_XL = 6,
+  RM_XFWD_ONE = 7, RM_XINV_ONE = 8  // the passes from and to real fields of one field
+};
+constexpr int kRowModes = 9;
 
 template <typename T>
 struct RowArgs {
@@ -173,8 +176,8 @@ struct RowArgs {
   int64_t in_stride;        // complex values between consecutive input fields
   T* out0;                  // first output I_y slot
   int64_t out_stride;
-  const void* real_in;      // [nf][n^3] real rows (RM_XFWD_REAL)
-  void* real_out;           // [nf][n^3] real rows (RM_XINV_REAL)
+  const void* real_in;      // [nf][n^3] real rows (RM_XFWD_REAL, RM_XFWD_ONE)
+  void* real_out;           // [nf][n^3] real rows (RM_XINV_REAL, RM_XINV_ONE)
   int32_t real_dtype;       // 0 = double, 1 = float
   int32_t nf;               // fields of an I/O pass
   double* partials;         // per-block records (RM_XDIAG, single member)

@@ -679,6 +679,8 @@ template <> struct RowShape<RM_XB> { static constexpr int NIN = 16, NOUT = 12, N
 template <> struct RowShape<RM_XL> { static constexpr int NIN = 11, NOUT = 12, NB = 12; };
 template <> struct RowShape<RM_XFWD_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
 template <> struct RowShape<RM_XINV_REAL> { static constexpr int NIN = 8, NOUT = 8, NB = 8; };
+template <> struct RowShape<RM_XFWD_ONE> { static constexpr int NIN = 1, NOUT = 1, NB = 1; };
+template <> struct RowShape<RM_XINV_ONE> { static constexpr int NIN = 1, NOUT = 1, NB = 1; };
 template <> struct RowShape<RM_XK> { static constexpr int NIN = 8, NOUT = 3, NB = 8; };
 template <> struct RowShape<RM_XDIAG> { static constexpr int NIN = kDiagFields, NOUT = 0, NB = kDiagFields; };
 
@@ -799,7 +801,15 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // The flux passes of a full run: RM_XL leaves out the strains (the Laplacian viscous
 // force of a run is added spectrally).
 constexpr bool is_flux(int mode) { return mode == RM_XB || mode == RM_XL; }
+// The passes from and to real fields of a call on one field (mhd_fft3d, the gradient
+// of mhd_spectra) take one wave and one field's LDS per row pair: in the eight-field
+// passes' workgroups seven of eight threads have nothing to do (mhd_fft3d in those ->
+// in these: 512 FP32 forward 420 -> 405 us, inverse 581 -> 412; 384 FP32 258 -> 181 and
+// 264 -> 187; 192 FP64 56 -> 41 and 63 -> 47; up to 64 within the launch time).
+constexpr bool from_real(int mode) { return mode == RM_XFWD_REAL || mode == RM_XFWD_ONE; }
+constexpr bool to_real(int mode) { return mode == RM_XINV_REAL || mode == RM_XINV_ONE; }
 template <typename T, int N, int MODE> constexpr int row_threads() {
+  if (MODE == RM_XFWD_ONE || MODE == RM_XINV_ONE) return 64;
   if (MODE == RM_XK) {
     constexpr int w = 8 * (N / PlanOf<N>::r[0]);
     return w <= 64 ? 64 : (w >= 512 ? 512 : (w + 63) / 64 * 64);
@@ -844,7 +854,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   // row pitch in LDS: swizzled rows are shifted by 16 elements from row to
   // row, so that a 32-lane read spanning two rows of N = 128 uses all banks
   constexpr int BS = SWZ ? N + 16 : N + (N >> PADSH) + 1;
-  constexpr bool SPEC_IN = MODE != RM_XFWD_REAL;
+  constexpr bool SPEC_IN = !from_real(MODE);
   // Wave maps: each field's transforms stay inside one wave, so a wave-level
   // fence replaces the workgroup barrier between passes and only the
   // pointwise stage, which reads every field at one point, is bracketed by
@@ -1068,7 +1078,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
     }
     if constexpr (!REAL_REGS) __syncthreads();
 
-    if constexpr (MODE == RM_XINV_REAL) {
+    if constexpr (to_real(MODE)) {
       for (int e = tid; e < nout * N; e += NT) {
         const int fld = e / N, x = e - (e / N) * N;
         const cx<T> z = buf[at(fld, x)];
@@ -1270,7 +1280,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
       }
     }
 
-    if constexpr (MODE == RM_XA || FLUX || MODE == RM_XFWD_REAL) {
+    if constexpr (MODE == RM_XA || FLUX || from_real(MODE)) {
       // only k <= K and N - k are read
       if constexpr (REAL_REGS) {
         lds_fft<T, PL, NB, NT, 1, BS, -1, RMAP, LAY, K, 1>(buf, stw, tid, nout);

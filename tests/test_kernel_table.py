@@ -1,0 +1,21 @@
+"""Launch shapes and scratch of the built kernels (CPU only: read from the library)."""
+import pytest
+
+from tests.kernel_table import kernel_table
+
+SIZES = (8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024)
+RM_XFWD_ONE, RM_XINV_ONE = 7, 8
+
+
+@pytest.fixture(scope="module")
+def table():
+    return kernel_table()
+
+
+@pytest.mark.parametrize("mode", [RM_XFWD_ONE, RM_XINV_ONE])
+def test_one_field_passes_take_one_wave(table, mode):
+    """A call on one field has N / r_0 <= 128 butterflies per row pair: one wave's work."""
+    for n in SIZES:
+        for t in ("float", "double") if n <= 512 else ("float",):
+            k = table[f"sched0::k_row<{t}, {n}, {mode}>"]
+            assert k["threads"] == 64 and k["scratch"] == 0, (t, n, k)
