@@ -796,7 +796,10 @@ __device__ __forceinline__ void flush_status(double cfl, int bad, double* slots,
 // 55.1 us) or half as many (64, and 128 in FP64 where the registers of two
 // butterflies fit: 20.2 -> 18.5 and 109 -> 89 us; FP32 at 128 would spill).
 // The passes from and to real fields take a thread per first-pass butterfly at 384
-// and 512 (set_state at 512 FP32 4.15 -> 3.39 ms, FP64 10.55 -> 7.89).
+// and 512 (set_state at 512 FP32 4.15 -> 3.39 ms, FP64 10.55 -> 7.89), and so does the
+// one to real fields at 768, whose three butterflies per thread at 256 threads could not
+// be paired (first_slot map 2: no mirror is read again; get_state 13.0 -> 12.0 ms mixed;
+// the one from real fields loses there, 11.1 -> 11.5).
 // The kinematic pass (eight fields) does the same.
 // The flux passes of a full run: RM_XL leaves out the strains (the Laplacian viscous
 // force of a run is added spectrally).
@@ -820,6 +823,7 @@ template <typename T, int N, int MODE> constexpr int row_threads() {
   if (MODE == RM_XA && (N == 64 || N == 128 || (N == 192 && sizeof(T) == 8) || (N == 384 && sizeof(T) == 4))) return 64;
   if (MODE == RM_XA && (N == 96 || N == 192 || N == 256 || (N == 512 && sizeof(T) == 4))) return kThreads / 2;
   if ((MODE == RM_XFWD_REAL || MODE == RM_XINV_REAL) && (N == 384 || N == 512)) return 2 * kThreads;
+  if (MODE == RM_XINV_REAL && N == 768) return 2 * kThreads;
   return (sizeof(T) == 4 && N >= 1024) ? 2 * kThreads : kThreads;
 }
 
@@ -843,11 +847,13 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   constexpr int NB = RowShape<MODE>::NB;
   // LDS row layout, chosen per pass by measurement.  Linear addressing where
   // the precomputed addresses would push a pass past 256 registers into
-  // spills (the flux and diagnostics passes at N = 1024).  The stage swizzle
+  // spills (the flux pass at N = 1024, the diagnostics pass from 768: 308 bytes of
+  // scratch there, 16.2 ms; linear 219 registers at 512 threads, 238 at 256, and
+  // diagnostics of 17.8 and 15.7 ms instead of 25.4).  The stage swizzle
   // (conflict-free LDS access, but more address arithmetic) where it measured
   // faster: the flux pass below N = 512 (3%) and the velocity pass from N = 512
   // (2%).  Otherwise one padding slot per 8 elements.
-  constexpr bool LIN = (is_flux(MODE) || MODE == RM_XDIAG) && N >= 1024;
+  constexpr bool LIN = (is_flux(MODE) && N >= 1024) || (MODE == RM_XDIAG && N >= 768);
   constexpr bool SWZ = !LIN && N % 16 == 0 && N >= 128 && ((is_flux(MODE) && N < 512) || (MODE == RM_XA && N >= 512));
   constexpr int PADSH = 3;
   constexpr int LAY = SWZ ? kSwizzle : (PADSH | (LIN ? kLinear : 0));

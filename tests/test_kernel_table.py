@@ -4,7 +4,7 @@ import pytest
 from tests.kernel_table import kernel_table
 
 SIZES = (8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024)
-RM_XFWD_ONE, RM_XINV_ONE = 7, 8
+RM_XDIAG, RM_XFWD_ONE, RM_XINV_ONE = 4, 7, 8
 
 
 @pytest.fixture(scope="module")
@@ -19,3 +19,12 @@ def test_one_field_passes_take_one_wave(table, mode):
         for t in ("float", "double") if n <= 512 else ("float",):
             k = table[f"sched0::k_row<{t}, {n}, {mode}>"]
             assert k["threads"] == 64 and k["scratch"] == 0, (t, n, k)
+
+
+def test_diagnostics_pass_does_not_spill(table):
+    """28 FP64 accumulators beside the butterflies: the pass that comes nearest to 256
+    registers.  The mixed path runs the FP32 one."""
+    for n in SIZES:
+        for t in ("float", "double") if n <= 512 else ("float",):
+            k = table[f"sched0::k_row<{t}, {n}, {RM_XDIAG}>"]
+            assert k["scratch"] == 0, (t, n, k)
