@@ -15,7 +15,7 @@ namespace {
 // a launch chooses, way of storing.
 template <typename T, int N, int S, int MAXT, bool MX, bool Z>
 void col_axis(const ColArgs<T>& a, dim3 g, hipStream_t s) {
-  constexpr ColStream cs = col_stream<N, S, Z>();
+  constexpr ColStream cs = col_stream<N, S, MAXT, MX, Z>();
   const dim3 nt(col_threads<T, N, MX, S, MAXT, Z>());
   if constexpr (cs != CS_NEVER) {
     if (cs == CS_ALWAYS || a.stream) {
@@ -45,7 +45,7 @@ template <typename T, int N, int S, int MAXT, bool MX, bool Z>
 ColClass col_occ(void) {
   ColClass c;
   c.width = col_tile<T, N, MX, S, MAXT, Z>();
-  constexpr bool st = col_stream<N, S, Z>() == CS_ALWAYS;
+  constexpr bool st = col_stream<N, S, MAXT, MX, Z>() == CS_ALWAYS;
   const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c.blocks, k_col<T, N, S, MAXT, MX, Z, st>,
                                                                     col_threads<T, N, MX, S, MAXT, Z>(), 0);
   if (e != hipSuccess || c.blocks < 1) c.blocks = 1;

@@ -184,24 +184,31 @@ __device__ __forceinline__ TileField tile_field(int nfields) {
 // that were loaded from HBM while the previous item was being transformed
 // (up to MAXT input terms per element; the zero gap of a band input is never
 // loaded); the last pass stores straight to HBM (dropped modes skipped).
-// STREAM: from N = 512, and at 128 and 256, whose strides crowd into few cache sets,
-// outputs that do not fit in the memory-side cache are stored past the caches: they
-// would only displace what the next pass still finds there (256 FP32: 12-field inverse
-// y pass 257 -> 203 us, forward 241 -> 221, rho pass 35 -> 27; FP64 4-field inverse y
-// pass 143 -> 123; 512 FP32: 1682 -> 1560, 1563 -> 1490, 220 -> 190; 768: step 59.5 ->
-// 57.0 ms).  Outputs that fit stay (256 FP32, 4-field passes streamed: z 46 -> 52, y
-// 66 -> 73), and so do those of the forward z pass, which the next pass reads first
-// (512: 257 -> 273 streamed), and of the other sizes (FP64 192: 139 -> 163 and 137 ->
-// 150 streamed; 384: 1209 -> 1247 and 1193 -> 1205).  A launch chooses by its output
-// bytes (kStreamBytes); from 512 on every field list of a step is too large.  A branch
-// in one kernel instead costs it 8-12 registers (192 FP32 12-field inverse y pass 71 ->
-// 87 us).
+// STREAM: at 128, 256, 512 and 768 (by measurement: the strides of powers of two crowd
+// into few cache sets), outputs that do not fit in the memory-side cache are stored past
+// the caches: they would only displace what the next pass still finds there (256 FP32: 12-field
+// inverse y pass 257 -> 203 us, forward 241 -> 221, rho pass 35 -> 27; FP64 4-field
+// inverse y pass 143 -> 123; 512 FP32: 1682 -> 1560, 1563 -> 1490, 220 -> 190; 768: step
+// 59.5 -> 57.0 ms).  An inverse z pass by itself may lose by it while the y pass after it
+// gains more, and the three-term one gains (512 FP32, z / y: 4 fields 367 -> 391 / 554 ->
+// 508 us, 12 fields 1076 -> 1089 / 1603 -> 1557, step 10.73 -> 10.67 ms; FP64 step 21.5 ->
+// 21.1, mixed 10.93 -> 10.80; 768 FP32 60.0 -> 59.2); only the mixed path's one-term z
+// pass at 768 has no such gain after it (1.44 -> 1.53 ms; kinematic step 18.4 -> 18.6).
+// Outputs that fit stay (256 FP32, 4-field passes streamed: z 46 -> 52, y 66 -> 73), and
+// so do those of the forward z pass, which the next pass reads first (512: 257 -> 273
+// streamed), and of the other sizes (FP64 192: 139 -> 163 and 137 -> 150 streamed; 384:
+// 1209 -> 1247 and 1193 -> 1205; 1024 FP32, 4 fields: z 3.82 -> 3.96, y 4.44 -> 4.91 and
+// 3.12 -> 3.76 ms, step 107.3-109.7 -> 110.9, mixed 104.7-107.1 -> 107.5).  A launch
+// chooses by its output bytes (kStreamBytes); at 512 and 768 every field list of a step
+// is too large.  A branch in one kernel instead costs it 8-12 registers (192 FP32
+// 12-field inverse y pass 71 -> 87 us).
 // Z: a z pass (else a y pass), fixed at compile time so that the column
 // geometry, the strides and the wavenumbers of the multipliers are constants
 // rather than uniform branches per element.
 enum ColStream { CS_NEVER, CS_BY_SIZE, CS_ALWAYS };
-template <int N, int S, bool Z> constexpr ColStream col_stream() {
+template <int N, int S, int MAXT, bool MX, bool Z> constexpr ColStream col_stream() {
   if (Z && S < 0) return CS_NEVER;
+  if (N == 1024 || (N == 768 && MX && Z && MAXT == 1)) return CS_NEVER;
   if (N >= 512) return CS_ALWAYS;
   return is_pow2(N) && N >= 128 ? CS_BY_SIZE : CS_NEVER;
 }

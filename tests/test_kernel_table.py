@@ -28,3 +28,11 @@ def test_diagnostics_pass_does_not_spill(table):
         for t in ("float", "double") if n <= 512 else ("float",):
             k = table[f"sched0::k_row<{t}, {n}, {RM_XDIAG}>"]
             assert k["scratch"] == 0, (t, n, k)
+
+
+def test_column_passes_stream_only_where_that_pays(table):
+    """Stores past the caches (the last argument of k_col): not at 1024, nor from the
+    mixed path's one-term inverse z pass at 768."""
+    streamed = [k for k in table if k.startswith("sched0::k_col<") and k.endswith(", true>")]
+    assert any("<float, 512, 1, 1, false, true, true>" in k for k in streamed)
+    assert not [k for k in streamed if "<float, 1024, " in k or "<float, 768, 1, 1, true, true," in k]
