@@ -950,8 +950,13 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   // first-pass elements too (loaded, transformed and stored in turn the pass waits on
   // memory three quarters of its time: set_state at 512 FP64 7.9 -> 6.4 ms, 384 FP32
   // 1.49 -> 1.39; 192 178 -> 172 us); smaller ones go to the LDS, a point per thread
-  // (few of the threads hold a butterfly there).
+  // (few of the threads hold a butterfly there), and so do FP64 rows of an FP32 run up to
+  // 128, whose conversion waits for the load and so undoes the prefetch (RUNTIME:
+  // set_state from FP64 at 128 prefetched 58.2, so 55.0 us; at 96 31.0 and 29.9; kept
+  // unconverted instead, twice the registers, 56.4 and 30.5, and FP32 rows slower).
   constexpr bool REAL_REGS = !SPEC_IN && N >= 96;
+  constexpr bool RUNTIME = REAL_REGS && sizeof(T) == 4 && N <= 128;
+  const bool real_regs = REAL_REGS && !(RUNTIME && a.real_dtype == 0);
   auto real_pair = [&](auto* in, int64_t e) { return mk<T>(T(in[e]), T(in[e + N])); };
   cx<T> rx[REAL_REGS ? FP::CNT : 1][FP::R];
   auto issue_real = [&](int64_t item) {
@@ -986,7 +991,7 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
   if constexpr (SPEC_IN) {
     if (item < nitems) issue(item);
   } else if constexpr (REAL_REGS) {
-    if (item < nitems) issue_real(item);
+    if (real_regs && item < nitems) issue_real(item);
   }
   int cur_m = -1;  // member whose CFL / non-finite status is being accumulated
   for (; item < nitems; item += gridDim.x) {
@@ -1007,15 +1012,21 @@ __global__ void __launch_bounds__((row_threads<T, N, MODE>()), (row_min_blocks<T
     // that still reads them)
     if constexpr (!WAVE) __syncthreads();
     if constexpr (!SPEC_IN) {
-      if constexpr (REAL_REGS) {
-        fft_first_regs<T, PL, NB, NT, 1, BS, -1, FM1, LAY>(buf, rx, tid, nin, lds_store);
-        if (item + gridDim.x < nitems) issue_real(item + gridDim.x);
+      if (real_regs) {
+        if constexpr (REAL_REGS) {
+          fft_first_regs<T, PL, NB, NT, 1, BS, -1, FM1, LAY>(buf, rx, tid, nin, lds_store);
+          if (item + gridDim.x < nitems) issue_real(item + gridDim.x);
+        }
       } else {
         for (int e = tid; e < nin * N; e += NT) {
           const int fld = e / N, x = e - (e / N) * N;
           const int64_t base = fld * a.g.n3 + row0 * N + x;
           buf[at(fld, x)] = a.real_dtype == 0 ? real_pair(static_cast<const double*>(a.real_in), base)
                                               : real_pair(static_cast<const float*>(a.real_in), base);
+        }
+        if constexpr (RUNTIME) {
+          __syncthreads();
+          fft_pass_valu<T, PL, NB, NT, 1, BS, -1, 0, RMAP, LAY>(buf, stw, tid, nin);
         }
       }
     } else {
