@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstdint>
 
 namespace mhd {
 
@@ -49,6 +50,20 @@ template <bool FAR> __host__ __device__ __forceinline__ CicAxis cic_axis(int n, 
   a.w1 = s - fl;
   a.w0 = 1.0 - a.w1;
   return a;
+}
+
+// Whether a call of nsteps steps on np particles, gathering nf fields of reals of `size`
+// bytes, interleaves them first (four values to a point) or gathers from the planes as
+// they are synthesised.  Interleaving is a launch and a pass over the grid; what it saves
+// is per particle and step, more of it with four fields, and not less per step than 28000
+// particles', whose latency a smaller call has too.  Microseconds a call, planes and
+// interleaved: 256^3 FP64 push 3x10^5 x 1: 371 and 493, 10^6 x 1: 599 and 580, 10^3 x 20:
+// 437 and 516; velocity 3x10^5: 512 and 624, 10^6: 833 and 706; 512^3 FP32 push 10^6 x 1:
+// 1570 and 1985, 10^6 x 4: 2280 and 2192; 128^3 FP32 push 10^3 x 1: 44 and 46, 10^3 x 4:
+// 58 and 50; 64^3 FP64 push 10^3 x 1: 30 and 31.
+constexpr bool cic_interleaves(int64_t np, int64_t nsteps, int nf, int64_t n3, int size) {
+  const double particles = np > 28000 ? double(np) : 28000.0;
+  return particles * double(nsteps) * (nf == 4 ? 64.0 : 36.0) >= double(n3) * (size / 4) + (1 << 19);
 }
 
 }  // namespace mhd

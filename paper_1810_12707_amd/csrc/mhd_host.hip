@@ -206,7 +206,9 @@ __global__ void __launch_bounds__(kThreads) k_force_abc(const T* __restrict__ st
 // step, at random places.  The fields are therefore interleaved first, four to a
 // grid point ([n^3][4], x fastest), so that a particle touches four runs of two
 // points instead of 24 or 32 separate words (10^6 particles in a 128^3 FP64 field,
-// 20 steps: 6.5 -> 2.0 ms a call).
+// 20 steps: 6.5 -> 2.0 ms a call), where the call is long enough to repay a pass over
+// the whole grid (cic_interleaves).
+//
 // Cloud-in-cell interpolation (mhd_cic.h).
 template <typename T> struct alignas(4 * sizeof(T)) Point4 {
   T v[4];
@@ -224,9 +226,25 @@ __global__ void __launch_bounds__(kThreads) k_interleave(const T* __restrict__ f
   p[i] = q;
 }
 
+// The four values at a grid point: interleaved, or NF planes of n3.
+template <typename T> struct GridPoints {
+  const Point4<T>* __restrict__ p;
+  __device__ __forceinline__ Point4<T> operator[](int64_t i) const { return p[i]; }
+};
+template <typename T, int NF> struct GridPlanes {
+  const T* __restrict__ f;
+  int64_t n3;
+  __device__ __forceinline__ Point4<T> operator[](int64_t i) const {
+    Point4<T> q;
+#pragma unroll
+    for (int c = 0; c < NF; ++c) q.v[c] = f[c * n3 + i];
+    return q;
+  }
+};
+
 // The eight corners of the cell at p and their weights, every load ahead of its use.
-template <bool FAR, typename T, typename F>
-__device__ __forceinline__ void cic_corners(const Point4<T>* __restrict__ g, int n, const double* p, F&& visit) {
+template <bool FAR, typename T, typename G, typename F>
+__device__ __forceinline__ void cic_corners(const G& g, int n, const double* p, F&& visit) {
   const CicAxis ax = cic_axis<FAR>(n, p[0]), ay = cic_axis<FAR>(n, p[1]), az = cic_axis<FAR>(n, p[2]);
   const int xi[2] = {ax.i0, ax.i1}, yi[2] = {ay.i0, ay.i1}, zi[2] = {az.i0, az.i1};
   const double xw[2] = {ax.w0, ax.w1}, yw[2] = {ay.w0, ay.w1}, zw[2] = {az.w0, az.w1};
@@ -239,14 +257,14 @@ __device__ __forceinline__ void cic_corners(const Point4<T>* __restrict__ g, int
 
 // Initial tracer velocity: the grid velocity u = m / rho (at the grid points:
 // rho, m_x, m_y, m_z of g) interpolated by CIC.
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_tracer_velocity(const Point4<T>* __restrict__ g, int n,
+template <typename T, typename G>
+__global__ void __launch_bounds__(kThreads) k_tracer_velocity(const G g, int n,
                                                              const double* __restrict__ pos, double* __restrict__ vel,
                                                              int64_t np) {
   const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (p >= np) return;
   double acc[3] = {0.0, 0.0, 0.0};
-  cic_corners<true>(g, n, pos + 3 * p, [&](const Point4<T>& q, double w) {
+  cic_corners<true, T>(g, n, pos + 3 * p, [&](const Point4<T>& q, double w) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) acc[c] += w * (double(q.v[1 + c]) / double(q.v[0]));
   });
@@ -258,8 +276,8 @@ __global__ void __launch_bounds__(kThreads) k_tracer_velocity(const Point4<T>* _
 // g's points): t = B dt / 2, s = 2 t / (1 + |t|^2), v' = v + v x t,
 // v <- v + v' x s, x <- x + v dt wrapped into [0, 2 pi); B is interpolated at each
 // step's start position.  One thread per particle.
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_tracer_push(const Point4<T>* __restrict__ g, int n,
+template <typename T, typename G>
+__global__ void __launch_bounds__(kThreads) k_tracer_push(const G g, int n,
                                                          double* __restrict__ pos, double* __restrict__ vel, int64_t np,
                                                          double dt, int nsteps) {
   const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -268,7 +286,7 @@ __global__ void __launch_bounds__(kThreads) k_tracer_push(const Point4<T>* __res
   double v[3] = {vel[3 * p], vel[3 * p + 1], vel[3 * p + 2]};
   auto step = [&](auto far) {
     double B[3] = {0.0, 0.0, 0.0};
-    cic_corners<decltype(far)::value>(g, n, x, [&](const Point4<T>& q, double w) {
+    cic_corners<decltype(far)::value, T>(g, n, x, [&](const Point4<T>& q, double w) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) B[c] += w * double(q.v[c]);
     });
@@ -2084,19 +2102,23 @@ int mhd_spectra(mhd_ctx* c, double* h_eu, double* h_eb, double* h_mom) {
   return MHD_OK;
 }
 
-// Tracers: the nf real-space fields they need (spectra at src) are synthesised
+// Tracers: the NF real-space fields they need (spectra at src) are synthesised
 // into the I_y scratch from slot 4 on, behind the inverse transform's own slots
-// 0-3, and interleaved behind them: 8 n^3 words in the 12 free slots (at least
-// 2 n^3 / 3 words each).
-extern "C++" template <typename E, typename T>
-static Point4<T>* tracer_grid(mhd_ctx* c, E& e, const T* src, int nf) {
+// 0-3, and where the call is long enough interleaved behind them: 8 n^3 words in the
+// 12 free slots (at least 2 n^3 / 3 words each).  launch(grid) gets either form.
+extern "C++" template <int NF, typename E, typename T, typename F>
+static void with_tracer_grid(mhd_ctx* c, E& e, const T* src, int64_t np, int64_t nsteps, F&& launch) {
   const int64_t n3 = c->g.n3;
   T* const real = e.iy(4);
-  e.inverse_real(src, nf, real, sizeof(T) == 4 ? MHD_FP32 : MHD_FP64);
+  e.inverse_real(src, NF, real, sizeof(T) == 4 ? MHD_FP32 : MHD_FP64);
+  if (!cic_interleaves(np, nsteps, NF, n3, sizeof(T))) {
+    launch(GridPlanes<T, NF>{real, n3});
+    return;
+  }
   Point4<T>* const grid = reinterpret_cast<Point4<T>*>(real + 4 * n3);
   hipLaunchKernelGGL((k_interleave<T>), dim3((unsigned)((n3 + kThreads - 1) / kThreads)), dim3(kThreads), 0, c->stream,
-                     real, nf, n3, grid);
-  return grid;
+                     real, NF, n3, grid);
+  launch(GridPoints<T>{grid});
 }
 
 int mhd_tracers_velocity(mhd_ctx* c, const double* d_pos, double* d_vel, int64_t np) {
@@ -2105,9 +2127,10 @@ int mhd_tracers_velocity(mhd_ctx* c, const double* d_pos, double* d_vel, int64_t
   if (np == 0) return MHD_OK;
   return with_engine(c, [&](auto& e) {
     using T = std::remove_pointer_t<decltype(e.state())>;
-    const Point4<T>* grid = tracer_grid<std::remove_reference_t<decltype(e)>, T>(c, e, e.state(), 4);  // rho, m
-    hipLaunchKernelGGL((k_tracer_velocity<T>), dim3((unsigned)((np + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       c->stream, grid, c->g.n, d_pos, d_vel, np);
+    with_tracer_grid<4>(c, e, e.state(), np, 1, [&](auto grid) {  // rho, m
+      hipLaunchKernelGGL((k_tracer_velocity<T, decltype(grid)>), dim3((unsigned)((np + kThreads - 1) / kThreads)),
+                         dim3(kThreads), 0, c->stream, grid, c->g.n, d_pos, d_vel, np);
+    });
     return check_launch(c, "mhd_tracers_velocity");
   });
 }
@@ -2118,10 +2141,10 @@ int mhd_tracers_push(mhd_ctx* c, double* d_pos, double* d_vel, int64_t np, doubl
   if (np == 0 || nsteps == 0) return MHD_OK;
   return with_engine(c, [&](auto& e) {
     using T = std::remove_pointer_t<decltype(e.state())>;
-    const Point4<T>* grid =
-        tracer_grid<std::remove_reference_t<decltype(e)>, T>(c, e, e.spec_field(e.state(), 4), 3);  // B
-    hipLaunchKernelGGL((k_tracer_push<T>), dim3((unsigned)((np + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       c->stream, grid, c->g.n, d_pos, d_vel, np, dt, (int)nsteps);
+    with_tracer_grid<3>(c, e, e.spec_field(e.state(), 4), np, nsteps, [&](auto grid) {  // B
+      hipLaunchKernelGGL((k_tracer_push<T, decltype(grid)>), dim3((unsigned)((np + kThreads - 1) / kThreads)),
+                         dim3(kThreads), 0, c->stream, grid, c->g.n, d_pos, d_vel, np, dt, (int)nsteps);
+    });
     return check_launch(c, "mhd_tracers_push");
   });
 }

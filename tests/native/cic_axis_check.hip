@@ -7,6 +7,13 @@
 
 #include "mhd_cic.h"
 
+// short calls gather from the planes, long ones interleave; no count overflows
+constexpr int64_t cube(int64_t n) { return n * n * n; }
+static_assert(!mhd::cic_interleaves(1000, 1, 3, cube(256), 8) && !mhd::cic_interleaves(1000, 1, 4, cube(512), 4), "");
+static_assert(!mhd::cic_interleaves(1, 1, 3, cube(1024), 4) && mhd::cic_interleaves(1, 1, 3, cube(32), 8), "");
+static_assert(mhd::cic_interleaves(1000003, 20, 3, cube(128), 8), "");
+static_assert(mhd::cic_interleaves(int64_t(1) << 40, 2147483647, 4, cube(1024), 4), "");
+
 int main() {
   const int sizes[] = {8, 12, 16, 24, 48, 96, 128, 192, 384, 768, 1024};
   long bad = 0;
