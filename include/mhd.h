@@ -369,7 +369,8 @@ size_t mhd_ens_workspace_bytes(const mhd_params* p, int32_t count);
  * enqueues on hip_stream (NULL = default stream).  The ensemble creates one
  * extra stream per group (default priority) for the graph's branches.
  * tune_cache_path: text file of tuned launch geometries (read at init,
- * appended to after tuning); NULL keeps tuning results in memory only; an
+ * appended to after tuning; lines that another build's kernels were tuned
+ * for are passed over); NULL keeps tuning results in memory only; an
  * empty string "" turns tuning off (every pass uses its resident-occupancy
  * grid).  Tuning runs at the first mhd_ens_step with all states set and
  * evaluates right-hand sides only, so it leaves every state unchanged. */

@@ -1689,7 +1689,13 @@ std::string tune_key(const EnsGroup& G, int cus) {
   return b;
 }
 
-// Cache lines: "mhd-ens-tune <n> <precision> <members> <CUs> <col_scale> <row_scale> <schedule>".
+// Cache lines: "mhd-ens-tune <n> <precision> <members> <CUs> <col_scale> <row_scale> <schedule> <kernels>".
+// kernels: which build's, a hash of the sources' code (build_lib.py).  A choice measured
+// for other kernels says nothing about these, so their lines are passed over.
+#ifndef MHD_KERNELS_ID
+#define MHD_KERNELS_ID 0
+#endif
+constexpr unsigned kKernelsId = MHD_KERNELS_ID;
 void tune_read(mhd_ens* E) {
   FILE* f = std::fopen(E->tune_path.c_str(), "r");
   if (!f) return;
@@ -1697,8 +1703,10 @@ void tune_read(mhd_ens* E) {
   while (std::fgets(line, sizeof(line), f)) {
     int n, pr, nm, cus, sc = 0;
     double cs, rs;
-    const int got = std::sscanf(line, "mhd-ens-tune %d %d %d %d %lf %lf %d", &n, &pr, &nm, &cus, &cs, &rs, &sc);
-    if (got < 6) continue;
+    unsigned id = 0;
+    const int got =
+        std::sscanf(line, "mhd-ens-tune %d %d %d %d %lf %lf %d %x", &n, &pr, &nm, &cus, &cs, &rs, &sc, &id);
+    if (got != 8 || id != kKernelsId) continue;
     if (!(cs > 0.0 && cs <= 4.0 && rs > 0.0 && rs <= 4.0) || sc < 0 || sc > 1) continue;
     for (EnsGroup& G : E->groups) {
       if (G.n == n && G.precision == pr && (int)G.members.size() == nm && E->num_cus == cus) {
@@ -1715,8 +1723,8 @@ void tune_read(mhd_ens* E) {
 void tune_write(mhd_ens* E, const EnsGroup& G) {
   FILE* f = std::fopen(E->tune_path.c_str(), "a");
   if (!f) return;  // an unwritable cache only costs a re-tune next time
-  std::fprintf(f, "mhd-ens-tune %s %.4f %.4f %d\n", tune_key(G, E->num_cus).c_str(), G.col_scale, G.row_scale,
-               G.sched);
+  std::fprintf(f, "mhd-ens-tune %s %.4f %.4f %d %x\n", tune_key(G, E->num_cus).c_str(), G.col_scale, G.row_scale,
+               G.sched, kKernelsId);
   std::fclose(f);
 }
 
