@@ -324,8 +324,10 @@ int mhd_profile(mhd_ctx* ctx, int32_t class_mask);
  * dropped launches through *dropped when non-NULL. */
 int mhd_profile_read(mhd_ctx* ctx, double* ms, int64_t* launches, double* bytes, int64_t* dropped);
 
-/* Algorithmic HBM bytes of one mhd_step of this context (sum over its
- * launches, each array read or written once), or 0 for a null context. */
+/* Algorithmic HBM bytes of one steady mhd_step of this context, pass by pass:
+ * the sum over the launch classes above, each array read or written once (up to
+ * n = 32 the fused passes of a step that is not recorded move less: no z
+ * intermediate, no u^).  0 for a null context. */
 double mhd_step_bytes(const mhd_ctx* ctx);
 
 /* Benchmark hook (not physics): enqueues one streaming copy of `bytes`
@@ -406,7 +408,8 @@ int32_t mhd_ens_num_groups(const mhd_ens* ens);
 int mhd_ens_group_info(const mhd_ens* ens, int32_t g, int32_t* n, int32_t* precision, int32_t* members,
                        double* col_scale, double* row_scale, int32_t* schedule);
 
-/* Algorithmic HBM bytes of one mhd_ens_step over all members. */
+/* The sum of mhd_step_bytes over all members: the algorithmic HBM bytes of one
+ * mhd_ens_step, pass by pass. */
 double mhd_ens_step_bytes(const mhd_ens* ens);
 
 /* Releases the ensemble's host state, streams, events and graph (not the

@@ -1232,8 +1232,12 @@ struct Engine {
     const double evals = c->p.scheme == MHD_RK4 ? 4 : (c->p.scheme == MHD_PC ? 2 : 1);
     // The launch classes count an AB2 update (8 fields: state and history read and
     // written, 32 S_c).  RK4's four updates move 24 + 32 + 32 + 24 and the three
-    // stage states' B (9) instead of 128; PC's two 32 + 24 + 3 instead of 64.
-    const double stage = c->p.scheme == MHD_RK4 ? cbytes(-7, 0, 0) : (c->p.scheme == MHD_PC ? cbytes(-5, 0, 0) : 0.0);
+    // stage states' B (9) instead of 128; PC's two 32 + 24 + 3 instead of 64.  Kinematic
+    // runs count 12 + 5 (the frozen fields' history read): RK4 moves 24 + 15 + 15 + 12
+    // instead of 68, PC 32 + 12 instead of 34 (the first update of a step moves the
+    // frozen fields, the others pass them by).
+    const double rk4 = kinematic() ? -2 : -7, pc = kinematic() ? 10 : -5;
+    const double stage = c->p.scheme == MHD_RK4 ? cbytes(rk4, 0, 0) : (c->p.scheme == MHD_PC ? cbytes(pc, 0, 0) : 0.0);
     return b * evals + stage;
   }
 
