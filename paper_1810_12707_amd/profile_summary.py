@@ -49,13 +49,19 @@ def source_sha256() -> str:
 
 def class_kernels(n: int) -> dict:
     """Launch classes whose kernel instance is used by that class alone in a
-    step (FP32 path): class -> substring of the demangled kernel name."""
+    step (FP32 path): class -> beginning of the demangled kernel name (is_kernel)."""
     return {
         "xa": f"k_row<float, {n}, 0",
         "xb": f"k_row<float, {n}, 1",
         "zrhs": f"k_zfwd_rhs<float, {n}",
-        "rho": "k_rho_rhs<float>",
+        "rho": "k_rho_rhs<float",
     }
+
+
+def is_kernel(name: str, start: str) -> bool:
+    """Whether a demangled kernel name is the one whose template arguments begin as
+    given: the last of them whole (12 is not 128), any further ones left open."""
+    return re.search(re.escape(start) + "[,>]", name) is not None
 
 
 def short_name(name: str) -> str:
@@ -102,7 +108,7 @@ STEP_SEQUENCE = [
     ("xa", "k_row<float, {n}, 0"), ("yfwd_a", "k_col<float, {n}, -1, 1, {mx}, false"),
     ("zfwd_a", "k_col<float, {n}, -1, 1, {mx}, true"), ("zinv_b", "k_col<float, {n}, 1, 3, {mx}, true"),
     ("yinv_b", "k_col<float, {n}, 1, 1, {mx}, false"), ("xb", "k_row<float, {n}, 1"),
-    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false"), ("rho", "k_rho_rhs<float>"), ("zrhs", "k_zfwd_rhs<float, {n}"),
+    ("yfwd_b", "k_col<float, {n}, -1, 1, {mx}, false"), ("rho", "k_rho_rhs<float"), ("zrhs", "k_zfwd_rhs<float, {n}"),
 ]
 
 
@@ -121,7 +127,7 @@ def per_class_kib(path: str, counter: str, n: int, mixed: bool = False) -> dict:
     acc = defaultdict(lambda: [0.0, 0])
     i = 0
     while i + len(seq) <= len(recs):
-        if all(sub in recs[i + t][1] for t, (_, sub) in enumerate(seq)):
+        if all(is_kernel(recs[i + t][1], start) for t, (_, start) in enumerate(seq)):
             for t, (c, _) in enumerate(seq):
                 acc[c][0] += recs[i + t][2]
                 acc[c][1] += 1
@@ -177,8 +183,8 @@ def cmd_traffic(a) -> int:
                 lines.append(f"| {c} | {fc[c][1]} | {rd:.3f} | {wr:.3f} | {rd + wr:.3f} | "
                              f"{al / 1e9 if al else float('nan'):.3f} | {ratio} |")
     out = {}
-    for cls, sub in class_kernels(a.n).items():
-        hit = [k for k in names if sub in k]
+    for cls, start in class_kernels(a.n).items():
+        hit = [k for k in names if is_kernel(k, start)]
         if len(hit) == 1:
             k = hit[0]
             out[cls] = (fetch[k][0] / ff + write[k][0] / wf) * 1024.0
