@@ -76,11 +76,11 @@ template <typename T, int N> constexpr int rhs_tile() {
 // 35).
 template <int N> constexpr bool rhs_upfront() { return N >= 512; }
 // Minimum resident waves per SIMD asked of the compiler (register cap).  FP32 from
-// 512: 64 registers, as above (68 uncapped at 1024).  FP32 at 128: seven waves, so
-// that the 1785 workgroups are resident at once.
+// 512: 64 registers, as above (68 uncapped at 1024, 8 bytes of scratch capped).  A cap of
+// seven waves at 128 FP32 measured nothing, for one run (28.0 us with, 28.0 without) or for
+// groups of 2 to 64 (64: step 13.85 and 13.86 ms).
 template <typename T, int N> constexpr int rhs_min_waves() {
   if (sizeof(T) == 4 && (N == 512 || N == 1024)) return 8;
-  if (sizeof(T) == 4 && N == 128 && MHD_SCHED == 0) return 7;
   return rhs_wide<T, N>() || rhs_threads<T, N>() > kThreads ? 1 : 3;
 }
 
