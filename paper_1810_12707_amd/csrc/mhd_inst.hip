@@ -110,6 +110,12 @@ void row(int mode, const RowArgs<T>& a, dim3 g, hipStream_t s) {
 }
 template <typename T, int N>
 int row_occupancy(int mode) {
+  if (mode == RM_XFWD_ONE || mode == RM_XINV_ONE) {
+    // one wave of at most 128 registers and its LDS; the runtime takes 50 us per kernel to
+    // say the same when the first context of a size is made
+    constexpr int lds = 2 * (int)sizeof(T) * (2 * N + N / 8 + 1);
+    return 160 * 1024 / lds < 16 ? 160 * 1024 / lds : 16;
+  }
   int blocks = 0;
   hipError_t e = hipSuccess;
   with_row_mode(mode, [&](auto m) {
