@@ -71,7 +71,7 @@ template <typename T, int N> constexpr int rhs_tile() {
 // kernel fits 64 registers there, so that two workgroups of 1024 threads share a CU
 // and one loads while the other transforms (512 FP32: 2032 us with one workgroup of
 // 94 registers -> 1650; capped without the early loads 1787; stored past the caches
-// 1592, 4.6 TB/s; FP64 120 registers, 4022 -> 3290; 1024: 21.4 -> 18.2 ms).  Below,
+// 1592, 4.6 TB/s; FP64 120 registers, 4022 -> 3290; 1024: 21.4 -> 16.8 ms).  Below,
 // the second group's registers cost resident waves (256 FP32: 213 -> 279, 128: 29 ->
 // 35).
 template <int N> constexpr bool rhs_upfront() { return N >= 512; }
